@@ -1,18 +1,18 @@
 // Encode kernels of the gfx950 ZipNN codec.
 //
-//   k_analyze  one workgroup per chunk: reads the chunk (16-byte loads, XOR
-//              with the base for a delta, paper §IV-B, exponent extraction
-//              when asked, §III-A), splits every word into its B byte groups
-//              (paper §III-A/§III-B) and histograms each group in LDS; wave k
-//              then builds the code of group k: optimal lengths <= L by
-//              package-merge (Larmore & Hirschberg, computed with parallel
-//              ranks, see build_lengths) and canonical codes (RFC 1951
+//   k_analyze  one workgroup of 16 waves per chunk: reads the chunk (16-byte
+//              loads, XOR with the base for a delta, paper §IV-B, exponent
+//              extraction when asked, §III-A), splits every word into its B
+//              byte groups (paper §III-A/§III-B) and histograms each group in
+//              LDS; one wave per code then builds the optimal lengths <= L by
+//              package-merge (Larmore & Hirschberg, lists merged in
+//              registers, see package_merge) and canonical codes (RFC 1951
 //              §3.2.2).  A group with one value becomes RLE (paper §III-B);
 //              a group whose most frequent byte fills half of it is also a ZG
 //              candidate (zero-aware coding, §IV-B).  For every candidate the
-//              four waves sum each lane's code bits lane group by lane
-//              group, which gives the exact payload sizes, so
-//              AUTO keeps the smallest of RAW, HUF and ZG (paper §III-B, §V-A).
+//              waves sum each lane's code bits, each over a range of steps of
+//              a lane group, which gives the exact payload sizes, so AUTO
+//              keeps the smallest of RAW, HUF and ZG (paper §III-B, §V-A).
 //              With a probe interval the probe chunks run first
 //              (compressibility probing, §III-B).
 //   k_place    one workgroup per tensor: exclusive scan of the 128-byte aligned
@@ -34,35 +34,28 @@ namespace zipnn {
 namespace {
 
 constexpr int kWaves = kBlock / 64;
-// The counting pass's histograms: kRep copies for all byte groups together
-// (16 / B copies of each), shared by the workgroup's waves; lane l of every
-// wave adds to copy l / (64 B / 16) of its group, whose bins start kRepShift *
-// copy words further on.  Lanes holding one value hit at most 4 B of the
-// same address in an instruction instead of 64 (LDS atomics on one address
-// serialise), and the shift puts the copies' equal bins on different banks.
-constexpr int kRep = 16;
-constexpr int kRepStride = 288;   // 256 bins + room for the shift
+// The analysis: one workgroup of kAnThreads threads per chunk, two on a CU
+// (at most 64 VGPRs).  One chunk's bytes are then spread over 16 waves, and
+// no more than 512 chunks are in flight on the chip: at 256 KiB they fit the
+// 256 MB last-level cache, which serves the size pass's second read.
+constexpr int kAnThreads = 1024;
+constexpr int kAnWaves = kAnThreads / 64;
+// The counting pass's histograms: kCopies copies of every bin, side by side;
+// a lane adds to copy (lane mod 32), so the lanes of half a wave always hit
+// 32 different banks, whatever the values (LDS atomics on one bank, let alone
+// one address, serialise).  Two byte groups share a copy's 32-bit counter
+// (16 bits each), so the counts are reduced every kPartVec 16-byte vectors,
+// before a half can overflow: a copy sees at most 32 threads x 128 vectors x 8
+// elements = 32768 values of a group in a part.
+constexpr uint32_t kCopies = 32;
+constexpr uint32_t kPartVec = (2u << 20) / 16;
 
-struct PmWave {                 // package-merge workspace of one wave
-    alignas(16) uint32_t leafw[256];   // leaf weights, ascending (f, symbol)
-    uint16_t leafsym[256];
-    alignas(16) uint32_t pk[256];      // package weights of the current level
-    union {
-        alignas(16) uint32_t key[256];   // the sort keys, used before the lists
-        uint32_t cur[512];               // current list weights
-    };
-    uint32_t leafbits[kMaxL][16];   // bit p: item p of the list of a level is a leaf
-    uint8_t len[256];           // code length per symbol
-};
-
-// Sized by the word width B (wave k < B builds the code of byte group k), so
-// that a BF16 workgroup takes 22 KB and seven fit on a CU.
+// Sized by the word width B.
 template <int B>
 union AnalyzeLds {
-    uint32_t rep[kRep][kRepStride];  // the counting pass's histogram copies
-    uint32_t hist[kWaves][B][256];   // per-wave sub-histograms (the ZG counting pass)
-    PmWave pm[B];                    // per-group code construction
-    uint32_t lgw[2][4][64];          // words per lane group: HUF, ZG (replay)
+    uint32_t copies[B == 4 ? 2 : 1][256][kCopies];   // the counting pass
+    uint32_t pm[3 * B][256];                         // the code constructions, one wave each
+    uint32_t seg[2][B][kAnThreads];                  // the size pass: bits << 5 | last pair, HUF and ZG
 };
 
 __device__ inline uint32_t wave_sum(uint32_t v)
@@ -72,180 +65,243 @@ __device__ inline uint32_t wave_sum(uint32_t v)
     return v;
 }
 
-// number of items of a sorted u32 array a[0..n) that are < x (strict) or <= x.
-// Up to 64 items (n uniform): a scan of 16-byte LDS reads, four in flight
-// (every lane of the wave reads the same words: a broadcast), instead of a
-// chain of dependent reads; a[] must be 16-byte aligned and hold 64 items.
-template <bool LE>
-__device__ inline uint32_t count_small(const uint32_t* a, uint32_t n, uint32_t x)
+// x of lane (lane ^ D), for the compare-exchange steps below
+template <int D>
+__device__ inline uint32_t lane_xor(uint32_t x)
 {
-    const uint4* v = reinterpret_cast<const uint4*>(a);
-    uint32_t c = 0;
-#pragma unroll 4
-    for (uint32_t q = 0; q < 16; q++) {
-        const uint4 y = v[q];
-        const uint32_t i = 4 * q;
-        c += uint32_t(i < n && (LE ? y.x <= x : y.x < x)) + uint32_t(i + 1 < n && (LE ? y.y <= x : y.y < x)) +
-             uint32_t(i + 2 < n && (LE ? y.z <= x : y.z < x)) + uint32_t(i + 3 < n && (LE ? y.w <= x : y.w < x));
+    static_assert(D == 1 || D == 2 || D == 4 || D == 8 || D == 16 || D == 32, "one bit of the lane");
+    if constexpr (D == 1) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);        // quad_perm 1,0,3,2
+    else if constexpr (D == 2) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);   // quad_perm 2,3,0,1
+    else if constexpr (D == 4)   // mirrored in halves of a row, then in quads
+        return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+    else if constexpr (D == 8) return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);  // row_ror:8
+    else if constexpr (D == 16) {
+        const auto y = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (threadIdx.x & 16) ? y[0] : y[1];
+    } else {
+        const auto y = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return (threadIdx.x & 32) ? y[0] : y[1];
     }
-    return c;
-}
-__device__ inline uint32_t count_lt(const uint32_t* a, uint32_t n, uint32_t x)
-{
-    if (n <= 64) return count_small<false>(a, n, x);
-    uint32_t lo = 0, hi = n;
-    while (lo < hi) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (a[mid] < x) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-__device__ inline uint32_t count_le(const uint32_t* a, uint32_t n, uint32_t x)
-{
-    if (n <= 64) return count_small<true>(a, n, x);
-    uint32_t lo = 0, hi = n;
-    while (lo < hi) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (a[mid] <= x) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
 }
 
-// Optimal code lengths <= L for the histogram held in registers (fv[r] =
-// f[lane + 64 r], at least two symbols with f > 0, `tot` = sum of f) into
-// P.len, by one wave.  With `shortcut` (policy AUTO) it returns false as soon
-// as a lower bound of the payload (`head` bytes + the coded bits) shows that
-// it cannot be smaller than `raw` bytes; the lengths are then not built.
+// One step of a bitonic sort of the wave's 64 R keys (key e = R lane + r in
+// x[r]): keys e and e ^ DIST, ascending where bit SIZE of e is clear.
+template <int R, int SIZE, int DIST>
+__device__ inline void sort_step(uint32_t* x)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    if constexpr (DIST >= R) {
+        constexpr uint32_t D = DIST / R;
+        const bool keep_min = (SIZE == 64 * R || ((R * lane) & SIZE) == 0) == ((lane & D) == 0);
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const uint32_t y = lane_xor<int(D)>(x[r]);
+            x[r] = keep_min ? min(x[r], y) : max(x[r], y);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (r & DIST) continue;
+            const bool asc = SIZE < R ? (r & SIZE) == 0 : ((R * lane) & SIZE) == 0;
+            const uint32_t a = min(x[r], x[r | DIST]), b = max(x[r], x[r | DIST]);
+            x[r] = asc ? a : b;
+            x[r | DIST] = asc ? b : a;
+        }
+    }
+    if constexpr (DIST > 1) sort_step<R, SIZE, DIST / 2>(x);
+}
+template <int R, int SIZE = 2>
+__device__ inline void sort_keys(uint32_t* x)
+{
+    sort_step<R, SIZE, SIZE / 2>(x);
+    if constexpr (SIZE < 64 * R) sort_keys<R, SIZE * 2>(x);
+}
+
+// One step of a merge over the lanes: every register's keys of lanes l and
+// l ^ D, the smaller to the lower lane.  Across rows two registers at a time:
+// the swap puts the lower lanes' keys of both in one and the upper lanes' in
+// the other, so minimum and maximum need no select.
+template <int N, int D>
+__device__ inline void merge_step(uint32_t* x)
+{
+    if constexpr (D >= 16) {
+#pragma unroll
+        for (int r = 0; r < N; r += 2) {
+            const auto y = D == 32 ? __builtin_amdgcn_permlane32_swap(x[r], x[r + 1], false, false)
+                                   : __builtin_amdgcn_permlane16_swap(x[r], x[r + 1], false, false);
+            const uint32_t a = min(y[0], y[1]), b = max(y[0], y[1]);
+            const auto z = D == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
+                                   : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+            x[r] = z[0];
+            x[r + 1] = z[1];
+        }
+    } else {
+        const bool upper = (threadIdx.x & D) != 0;
+#pragma unroll
+        for (int r = 0; r < N; r++) {
+            const uint32_t y = lane_xor<D>(x[r]);
+            x[r] = upper ? max(x[r], y) : min(x[r], y);
+        }
+    }
+    if constexpr (D > 1) merge_step<N, D / 2>(x);
+}
+
+// Optimal code lengths <= L of the n symbols whose sort keys (f << 8 |
+// symbol; f < 2^24) lie in buf[0, n), n <= 64 R, into len[256] (zero for the
+// others, cleared by the caller), by one wave; returns the coded bits.
 //
 // Package-merge with lists made of leaves and packages: list 0 = the leaves
 // sorted by (f, symbol); list d = the leaves merged with the packages of
 // consecutive pairs of list d-1, a leaf before a package of equal weight.
-// Merging two sorted sequences is done by ranks: leaf i lands at
-// i + #{packages lighter than it}, package j at j + #{leaves not heavier}.
-// The 2n'-2 first items of the top list are selected; the packages among the
+// The 2n-2 first items of the top list are selected; the packages among the
 // first m items of a list select the first 2*(their count) items of the list
-// below; leaf i is selected at a level iff i < (leaves among the selected
-// items), so its length is the number of such levels.  Each level keeps a
-// 512-bit mask of the list positions that hold leaves, so that count is a
-// popcount (16 words per level instead of a position per leaf: the LDS of a
-// workgroup fits four per CU).
-__device__ __attribute__((always_inline)) bool build_lengths(const uint32_t* fv, uint32_t tot, uint32_t raw, uint32_t head, uint32_t L,
-                              bool shortcut, PmWave& P, uint32_t& T_out)
+// below; leaf i is selected at a level iff fewer than (leaves among the
+// selected items) leaves precede it, so its length is the number of such
+// levels.  Only the weights and kinds of a list's items matter, not which
+// package is which: an item is the key weight * 2 + (1 for a package), and a
+// list is a bitonic merge of two sorted runs in registers, R keys of each per
+// lane (lower and upper half of the list).  The packages pass through LDS to
+// come out in reverse order, as the merge wants them.  A level takes about
+// 700 (R = 1) to 1500 cycles; with the ranks taken by searches in LDS over
+// the whole workgroup a code took 22000 cycles, and LDS time is what the
+// counting pass next to it is short of.
+template <int R>
+__device__ __attribute__((always_inline)) uint32_t package_merge(uint32_t* buf, uint32_t n, uint32_t L, uint8_t* len)
 {
-    T_out = 0;
-    const int lane = threadIdx.x & 63;
-    uint32_t d = 0;
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t leaf[R], sym[R];
 #pragma unroll
-    for (int r = 0; r < 4; r++) d += __popcll(__ballot(fv[r] > 0));
-    if (shortcut) {
-        // Any prefix code spends at least the empirical entropy, sum f log2(tot/f)
-        // bits.  If even that bound gives a payload no smaller than the raw
-        // bytes, AUTO cannot keep this code (the decision is the one the exact
-        // size would give), and it need not be built.  In single precision
-        // (v_log_f32): each log2 of a count below 2^23 is within about 2^-18
-        // of the truth, so the terms err by under 10^-5 bits per symbol in
-        // all, and rounding the products and the sum errs by under 10^-6 of
-        // the sum; the margins below (10^-4 relative, 10^-4 bits per symbol)
-        // keep the bound a lower bound.  Near the boundary the code is built
-        // and sized exactly, as without the test.
-        const float lt = __log2f(float(tot));
-        float h = 0.0f;
+    for (int r = 0; r < R; r++) leaf[r] = R * lane + r < n ? buf[R * lane + r] : ~0u;
+    sort_keys<R>(leaf);
 #pragma unroll
-        for (int r = 0; r < 4; r++)
-            if (fv[r]) h += float(fv[r]) * (lt - __log2f(float(fv[r])));
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) h += __shfl_xor(h, o, 64);
-        const float lb = h * (1.0f - 1e-4f) - 1e-4f * float(tot) - 1.0f;
-        const uint64_t words_lb = lb > 0.0f ? uint64_t(lb / 32.0f) : 0u;   // floor: a lower bound too
-        if (uint64_t(head) + 4 * words_lb >= raw) return false;
+    for (int r = 0; r < R; r++) {
+        sym[r] = leaf[r] & 0xFFu;
+        leaf[r] = leaf[r] == ~0u ? ~0u : (leaf[r] >> 8) << 1;
     }
-    // sort the leaves by key = f << 8 | symbol (f < 2^24 since m <= 2^22)
+    uint32_t x[2 * R];   // the list: items R lane + r, then 64 R + R lane + r
 #pragma unroll
-    for (int r = 0; r < 4; r++) P.key[lane + 64 * r] = fv[r] ? ((fv[r] << 8) | uint32_t(lane + 64 * r)) : 0xFFFFFFFFu;
-    __builtin_amdgcn_wave_barrier();
-    {
-        // rank of each key among all 256 (keys are distinct): four keys per
-        // 16-byte LDS read, shared by the lane's four symbols
-        uint32_t k4[4], rank[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int r = 0; r < 4; r++) k4[r] = P.key[lane + 64 * r];
-        const uint4* kv = reinterpret_cast<const uint4*>(P.key);
-#pragma unroll 4
-        for (int s = 0; s < 64; s++) {
-            const uint4 kk = kv[s];
-#pragma unroll
-            for (int r = 0; r < 4; r++)
-                rank[r] += uint32_t(kk.x < k4[r]) + uint32_t(kk.y < k4[r]) + uint32_t(kk.z < k4[r]) +
-                           uint32_t(kk.w < k4[r]);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            if (fv[r]) {
-                P.leafw[rank[r]] = fv[r];
-                P.leafsym[rank[r]] = uint16_t(lane + 64 * r);
-            }
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    const uint32_t n = d;
-    // level 0: the leaves alone
-    for (uint32_t i = lane; i < n; i += 64) P.cur[i] = P.leafw[i];
-    for (uint32_t x = lane; x < kMaxL * 16; x += 64) {
-        const uint32_t lo = 32 * (x & 15);
-        (&P.leafbits[0][0])[x] = x < 16 ? (n >= lo + 32 ? ~0u : (n > lo ? (1u << (n - lo)) - 1u : 0u)) : 0u;
-    }
-    uint32_t curlen = n;
-    __builtin_amdgcn_wave_barrier();
+    for (int r = 0; r < R; r++) x[r] = leaf[r], x[R + r] = ~0u;
+    // per level, which of this lane's items are leaves (2 R bits), the last
+    // level lowest
+    uint64_t kind0 = 0, kind1 = 0;
     for (uint32_t lev = 1; lev < L; lev++) {
-        const uint32_t npk = curlen / 2;
-        for (uint32_t j = lane; j < npk; j += 64) P.pk[j] = P.cur[2 * j] + P.cur[2 * j + 1];
         __builtin_amdgcn_wave_barrier();
-        for (uint32_t i = lane; i < n; i += 64) {
-            uint32_t p = i + count_lt(P.pk, npk, P.leafw[i]);
-            atomicOr(&P.leafbits[lev][p >> 5], 1u << (p & 31));
-            P.cur[p] = P.leafw[i];
-        }
-        for (uint32_t j = lane; j < npk; j += 64) {
-            uint32_t p = j + count_le(P.leafw, n, P.pk[j]);
-            P.cur[p] = P.pk[j];
-        }
-        curlen = n + npk;
-        __builtin_amdgcn_wave_barrier();
-    }
-    // selection, top level first
-    uint32_t lens_local[4] = {0, 0, 0, 0};   // for leaves i = lane + 64 r
-    uint32_t sel = 2 * n - 2;
-    for (int lev = int(L) - 1; lev >= 0; lev--) {
-        // leaves among the first sel items of the level's list
-        uint32_t c = 0;
-        if (lane < 16) {
-            const uint32_t lo = 32u * uint32_t(lane), wbits = P.leafbits[lev][lane];
-            c = sel >= lo + 32 ? __popc(wbits) : (sel > lo ? __popc(wbits & ((1u << (sel - lo)) - 1u)) : 0u);
-        }
-        c = wave_sum(c);
+        if constexpr (R == 1) {
 #pragma unroll
-        for (int r = 0; r < 4; r++) lens_local[r] += (uint32_t(lane + 64 * r) < c) ? 1u : 0u;
+            for (int h = 0; h < 2; h++) {
+                const uint32_t y = lane_xor<1>(x[h]);   // even lanes: the pair's second item
+                const uint32_t pk = y == ~0u ? ~0u : ((x[h] & ~1u) + (y & ~1u)) | 1u;
+                if (!(lane & 1)) buf[32 * h + lane / 2] = pk;
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; h++)
+#pragma unroll
+                for (int r = 0; r < R; r += 2) {
+                    const uint32_t a = x[R * h + r], b = x[R * h + r + 1];
+                    buf[32 * R * h + R / 2 * lane + r / 2] = b == ~0u ? ~0u : ((a & ~1u) + (b & ~1u)) | 1u;
+                }
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const uint32_t pk = buf[64 * R - 1 - (R * lane + r)];
+            x[r] = min(leaf[r], pk);
+            x[R + r] = max(leaf[r], pk);
+        }
+        merge_step<2 * R, 32>(x);
+#pragma unroll
+        for (int dist = R / 2; dist >= 1; dist /= 2)
+#pragma unroll
+            for (int h = 0; h < 2; h++)
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    if (r & dist) continue;
+                    uint32_t &a = x[R * h + r], &b = x[R * h + (r | dist)];
+                    const uint32_t lo = min(a, b), hi = max(a, b);
+                    a = lo;
+                    b = hi;
+                }
+        uint32_t f = 0;
+#pragma unroll
+        for (int r = 0; r < 2 * R; r++) f |= ((x[r] & 1u) ^ 1u) << r;
+        if constexpr (R > 1) kind1 = (kind1 << (2 * R)) | (kind0 >> (64 - 2 * R));
+        kind0 = (kind0 << (2 * R)) | f;
+    }
+    uint32_t ln[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) ln[r] = 0;
+    uint32_t sel = 2 * n - 2;
+    for (uint32_t lev = L - 1; lev >= 1; lev--) {
+        uint32_t c = 0;   // leaves among the first sel items
+#pragma unroll
+        for (int r = 0; r < 2 * R; r++) {
+            const uint32_t item = (r >= R ? 64 * R : 0) + R * lane + (r % R);
+            c += uint32_t(__popcll(__ballot(((kind0 >> r) & 1) != 0 && item < sel)));
+        }
+        kind0 >>= 2 * R;
+        if constexpr (R > 1) {
+            kind0 |= kind1 << (64 - 2 * R);
+            kind1 >>= 2 * R;
+        }
+#pragma unroll
+        for (int r = 0; r < R; r++) ln[r] += R * lane + r < c ? 1u : 0u;
         sel = 2 * (sel - c);
     }
-    // lengths per symbol, cost T
-    uint32_t T = 0;
-    for (int r = 0; r < 4; r++) P.len[lane + 64 * r] = 0;
-    __builtin_amdgcn_wave_barrier();
+    const uint32_t c = min(sel, n);   // list 0 holds the leaves alone
+    uint32_t bits = 0;
+#pragma unroll
+    for (int r = 0; r < R; r++)
+        if (R * lane + r < n) {
+            ln[r] += R * lane + r < c ? 1u : 0u;
+            len[sym[r]] = uint8_t(ln[r]);
+            bits += (leaf[r] >> 1) * ln[r];
+        }
+    return wave_sum(bits);
+}
+
+// The code lengths of the histogram fv[r] = f[lane + 64 r] (at least two
+// symbols with f > 0), by one wave, with 256 words of LDS; returns the coded bits.
+__device__ __attribute__((always_inline)) uint32_t build_lengths(const uint32_t* fv, uint32_t* buf, uint32_t L,
+                                                                 uint8_t* len)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint32_t n = 0;
 #pragma unroll
     for (int r = 0; r < 4; r++) {
-        uint32_t i = lane + 64 * r;
-        if (i < n) {
-            P.len[P.leafsym[i]] = uint8_t(lens_local[r]);
-            T += P.leafw[i] * lens_local[r];
-        }
+        const uint64_t msk = __ballot(fv[r] > 0);
+        const uint32_t s = lane + 64 * r;
+        if (fv[r]) buf[n + uint32_t(__popcll(msk & lt_mask))] = (fv[r] << 8) | s;
+        len[s] = 0;
+        n += uint32_t(__popcll(msk));
     }
-    T = wave_sum(T);
-    T_out = T;
     __builtin_amdgcn_wave_barrier();
-    // the payload holds at least its head and ceil(T/8) bytes
-    return !(shortcut && head + (T + 7) / 8 >= raw);
+    return n <= 64 ? package_merge<1>(buf, n, L, len) : package_merge<4>(buf, n, L, len);
+}
+
+// Whether even the empirical entropy of a histogram held by one wave (fv[r] =
+// f[lane + 64 r], sum tot) leaves a payload of `head` bytes and coded bits no
+// smaller than the raw bytes: any prefix code spends at least
+// sum f log2(tot/f) bits, so AUTO cannot keep this code (the decision is the
+// one the exact size would give), and it need not be built.  In single
+// precision (v_log_f32): each log2 of a count below 2^23 is within about
+// 2^-18 of the truth, so the terms err by under 10^-5 bits per symbol in all,
+// and rounding the products and the sum errs by under 10^-6 of the sum; the
+// margins below (10^-4 relative, 10^-4 bits per symbol) keep the bound a lower
+// bound.  Near the boundary the code is built and sized exactly.
+__device__ inline bool entropy_says_raw(const uint32_t* fv, uint32_t tot, uint32_t head, uint32_t raw)
+{
+    const float lt = __log2f(float(tot));
+    float h = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+        if (fv[r]) h += float(fv[r]) * (lt - __log2f(float(fv[r])));
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) h += __shfl_xor(h, o, 64);
+    const float lb = h * (1.0f - 1e-4f) - 1e-4f * float(tot) - 1.0f;
+    const uint64_t words_lb = lb > 0.0f ? uint64_t(lb / 32.0f) : 0u;   // floor: a lower bound too
+    return uint64_t(head) + 4 * words_lb >= raw;
 }
 
 // Canonical codes (RFC 1951 §3.2.2) of the lengths len[256], by one wave:
@@ -276,31 +332,43 @@ __device__ __attribute__((always_inline)) void canonical_codes(const uint8_t* le
     for (int r = 0; r < 4; r++) codes[lane + 64 * r] = l4[r] ? (code4[r] | (l4[r] << 16)) : 0u;
 }
 
+// The tensor holding chunk g: the last i with prefix[i] <= g, by a whole wave
+// (64 candidates a step: one dependent load for up to 64 tensors, two for
+// 4096, where a binary search made six and twelve).
 __device__ inline int find_desc(const uint32_t* prefix, int n_desc, uint32_t g)
 {
-    int lo = 0, hi = n_desc - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= g) lo = mid;
-        else hi = mid - 1;
+    const int lane = int(threadIdx.x & 63);
+    int lo = 0, n = n_desc;   // it is in [lo, lo + n)
+    while (n > 1) {
+        const int step = (n + 63) / 64;
+        const int i = lane * step;
+        const int c = __popcll(__ballot(i < n && prefix[lo + min(i, n - 1)] <= g)) - 1;
+        lo += c * step;
+        n = min(step, n - c * step);
     }
     return lo;
 }
 
-// Load NB bytes (NB in {2,4,8,16,32,64}) from p into 32-bit words.
+// Load NB bytes (NB in {2,4,8,16,32,64}) of device memory into 32-bit words
+// (global loads: a generic pointer's flat loads would also wait for LDS).
+template <class T>
+using global_ptr = const T __attribute__((address_space(1)))*;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <int NB>
 __device__ inline void loadNB(const uint8_t* p, uint32_t* w)
 {
-    if constexpr (NB == 2) w[0] = *(const uint16_t*)p;
-    else if constexpr (NB == 4) w[0] = *(const uint32_t*)p;
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    if constexpr (NB == 2) w[0] = *(global_ptr<uint16_t>)a;
+    else if constexpr (NB == 4) w[0] = *(global_ptr<uint32_t>)a;
     else if constexpr (NB == 8) {
-        uint2 v = *(const uint2*)p;
+        const u32x2 v = *(global_ptr<u32x2>)a;
         w[0] = v.x;
         w[1] = v.y;
     } else {
 #pragma unroll
         for (int i = 0; i < NB / 16; i++) {
-            uint4 v = *(const uint4*)(p + 16 * i);
+            const u32x4 v = *(global_ptr<u32x4>)(a + 16 * i);
             w[4 * i] = v.x;
             w[4 * i + 1] = v.y;
             w[4 * i + 2] = v.z;
@@ -380,45 +448,37 @@ __device__ inline bool marked(const uint32_t* wd, int k, uint32_t gcnt, uint32_t
     return mk;
 }
 
-// Histograms of the ZG candidates (bit k of zc, fill value z[k]) over the
-// groups that hold a value other than z: h[k][s] of this wave, except the
-// count of z itself, which is returned per stream (summed over the wave).
+// The symbols of stream k that lie in groups of g made of z[k] alone, for the
+// streams in zc, summed over the wave.  Every value other than z lies in a
+// marked group, so the histogram over the marked groups is the main one with
+// this many taken off the count of z.
 template <int B, int G>
-__device__ __attribute__((always_inline)) void zg_count(const uint8_t* src, const uint8_t* base, uint32_t zc, const uint32_t* z, uint32_t m,
-                         uint32_t (*h)[256], uint32_t* zcount, bool xf)
+__device__ __attribute__((always_inline)) void zg_unmarked(const uint8_t* src, const uint8_t* base, uint32_t zc,
+                                                           const uint32_t* z, uint32_t m, uint32_t* un, bool xf)
 {
     constexpr int NB = B * G;
     constexpr int NW = NB >= 4 ? NB / 4 : 1;
-    constexpr uint32_t CB = 4;   // groups in flight per thread
+    constexpr uint32_t CB = NB >= 16 ? 2 : 4;   // groups in flight per thread
     const uint32_t Gtot = (m + G - 1) / G;
-    uint32_t nz[B];
 #pragma unroll
-    for (int k = 0; k < B; k++) nz[k] = 0;
-    for (uint32_t q0 = threadIdx.x; q0 < Gtot; q0 += CB * kBlock) {
+    for (int k = 0; k < B; k++) un[k] = 0;
+    for (uint32_t q0 = threadIdx.x; q0 < Gtot; q0 += CB * kAnThreads) {
         uint32_t wds[CB][NW];
 #pragma unroll
         for (uint32_t u = 0; u < CB; u++)
-            if (q0 + u * kBlock < Gtot) group_words<B, G>(src, base, q0 + u * kBlock, m, wds[u], xf);
+            if (q0 + u * kAnThreads < Gtot) group_words<B, G>(src, base, q0 + u * kAnThreads, m, wds[u], xf);
 #pragma unroll
         for (uint32_t u = 0; u < CB; u++) {
-            const uint32_t q = q0 + u * kBlock;
+            const uint32_t q = q0 + u * kAnThreads;
             if (q >= Gtot) continue;
             const uint32_t gcnt = min(uint32_t(G), m - q * G);
 #pragma unroll
-            for (int k = 0; k < B; k++) {
-                if (!((zc >> k) & 1) || !marked<B, G>(wds[u], k, gcnt, z[k])) continue;
-#pragma unroll
-                for (int i = 0; i < G; i++) {
-                    if (uint32_t(i) >= gcnt) continue;
-                    const uint32_t v = sym_of<B>(wds[u], k, i);
-                    if (v == z[k]) nz[k]++;
-                    else atomicAdd(&h[k][v], 1u);
-                }
-            }
+            for (int k = 0; k < B; k++)
+                if (((zc >> k) & 1) && !marked<B, G>(wds[u], k, gcnt, z[k])) un[k] += gcnt;
         }
     }
 #pragma unroll
-    for (int k = 0; k < B; k++) zcount[k] = wave_sum(nz[k]);
+    for (int k = 0; k < B; k++) un[k] = wave_sum(un[k]);
 }
 
 // Bytes of stream k of the g elements of a group's words, packed little-endian
@@ -445,16 +505,17 @@ __device__ inline uint32_t gather_stream(const uint32_t* wd, int k)
     }
 }
 
-// Count the words each candidate's lane group j of one chunk takes: HUF
-// candidates (bit k of hc, lengths lens[k]) over every group, ZG candidates
-// (bit k of zgc, lengths lens2[k], fill value z[k]) over the groups holding
-// another value.  A lane's count follows from its code bits and those of its
-// last pair alone (see the end of the function).  Lane 0 of the wave writes
-// the counts to lgw[0][k][j] and lgw[1][k][j].
+// Code bits of steps [s0, s1) of lane group j of one chunk, per lane and
+// candidate: HUF candidates (bit k of hc, lengths lens[k]) over every group,
+// ZG candidates (bit k of zgc, lengths lens2[k], fill value z[k]) over the
+// groups holding another value.  out[v][k] = bits << 5 | bits of the last
+// pair coded here (at most 4096 * 11 bits in all, 22 in a pair).
 template <int B, int G>
-__device__ __attribute__((always_inline)) void count_lane_group(const uint8_t* src, const uint8_t* base, uint32_t hc, uint32_t zgc,
-                                 const uint8_t (*lens)[256], const uint8_t (*lens2)[256], const uint32_t* z,
-                                 uint32_t L, uint32_t j, uint32_t W, uint32_t m, uint32_t (*lgw)[4][64], bool xf)
+__device__ __attribute__((always_inline)) void count_steps(const uint8_t* src, const uint8_t* base, uint32_t hc,
+                                                           uint32_t zgc, const uint8_t (*lens)[256],
+                                                           const uint8_t (*lens2)[256], const uint32_t* z, uint32_t j,
+                                                           uint32_t s0, uint32_t s1, uint32_t W, uint32_t m,
+                                                           uint32_t (*out)[B], bool xf)
 {
     constexpr int NB = B * G;
     constexpr int NW = NB >= 4 ? NB / 4 : 1;
@@ -462,22 +523,66 @@ __device__ __attribute__((always_inline)) void count_lane_group(const uint8_t* s
     const uint32_t w = 64 * j + lane;
     const uint32_t Gtot = (m + G - 1) / G, Gfull = m / G, rem = m - Gfull * G;
     const uint32_t ng = (w < W && w < Gtot) ? (Gtot - 1 - w) / W + 1 : 0;
-    // per candidate: the lane's code bits and those of its last pair (a lane
-    // with no pair takes no word)
+    const uint32_t end = min(ng, s1);
     uint32_t bits[2][B], last[2][B];
 #pragma unroll
     for (int k = 0; k < B; k++) bits[0][k] = bits[1][k] = last[0][k] = last[1][k] = 0;
-    constexpr uint32_t CB = 4;   // groups in flight per lane
-    for (uint32_t j0 = 0; j0 < ng; j0 += CB) {
+    if (zgc == 0 && s1 > s0 && 64 * j + 64 <= W && 64 * j + 63 + (s1 - 1) * W < Gfull) {
+        // HUF alone and a full group for every lane at every step: no
+        // conditions, so the table reads of several groups are in flight
+        constexpr uint32_t FB = NB >= 32 ? 1 : (NB >= 16 ? 2 : (NB >= 8 ? 4 : 8));
+        uint32_t lw[NW];
+        auto add = [&](auto nb_const, uint32_t jj) __attribute__((always_inline)) {
+            constexpr uint32_t N = decltype(nb_const)::value;
+            uint32_t wds[N][NW];
+#pragma unroll
+            for (uint32_t u = 0; u < N; u++) {
+                const uint64_t o = uint64_t(w + (jj + u) * W) * NB;
+                loadNB<NB>(src + o, wds[u]);
+                if (base) {
+                    uint32_t bw[NW];
+                    loadNB<NB>(base + o, bw);
+#pragma unroll
+                    for (int x = 0; x < NW; x++) wds[u][x] ^= bw[x];
+                }
+                if (xf)
+#pragma unroll
+                    for (int x = 0; x < NW; x++) wds[u][x] = exp_fwd<B>(wds[u][x]);
+            }
+#pragma unroll
+            for (int k = 0; k < B; k++) {
+                if (!((hc >> k) & 1)) continue;
+#pragma unroll
+                for (uint32_t u = 0; u < N; u++)
+#pragma unroll
+                    for (int i = 0; i < G; i++) bits[0][k] += lens[k][sym_of<B>(wds[u], k, i)];
+            }
+#pragma unroll
+            for (int x = 0; x < NW; x++) lw[x] = wds[N - 1][x];
+        };
+        uint32_t jj = s0;
+        for (; (s1 - jj) % FB; jj++) add(std::integral_constant<uint32_t, 1>{}, jj);
+        for (; jj < s1; jj += FB) add(std::integral_constant<uint32_t, FB>{}, jj);
+#pragma unroll
+        for (int k = 0; k < B; k++) {
+            if ((hc >> k) & 1)
+                last[0][k] = uint32_t(lens[k][sym_of<B>(lw, k, G - 2)]) + lens[k][sym_of<B>(lw, k, G - 1)];
+            out[0][k] = (bits[0][k] << 5) | last[0][k];
+            out[1][k] = 0;
+        }
+        return;
+    }
+    constexpr uint32_t CB = NB >= 32 ? 1 : (NB >= 16 ? 2 : 4);   // groups in flight per lane
+    for (uint32_t j0 = s0; j0 < end; j0 += CB) {
         uint32_t wds[CB][NW];
 #pragma unroll
         for (uint32_t u = 0; u < CB; u++)
-            if (j0 + u < ng) group_words<B, G>(src, base, w + (j0 + u) * W, m, wds[u], xf);
+            if (j0 + u < end) group_words<B, G>(src, base, w + (j0 + u) * W, m, wds[u], xf);
 #pragma unroll
         for (uint32_t u = 0; u < CB; u++) {
             const uint32_t jj = j0 + u;
             const uint32_t q = w + jj * W;
-            const uint32_t gcnt = jj >= ng ? 0u : (q < Gfull ? G : rem);
+            const uint32_t gcnt = jj >= end ? 0u : (q < Gfull ? G : rem);
             const uint32_t* wd = wds[u];
 #pragma unroll
             for (int k = 0; k < B; k++) {
@@ -499,17 +604,10 @@ __device__ __attribute__((always_inline)) void count_lane_group(const uint8_t* s
             }
         }
     }
-    // before each pair a lane holding fewer than 2L bits takes a word, so
-    // after that check 32 * taken - consumed lies in [2L, 2L + 31]: a lane
-    // takes ceil((consumed before its last pair + 2L) / 32) words in all
 #pragma unroll
     for (int k = 0; k < B; k++) {
-#pragma unroll
-        for (int v = 0; v < 2; v++) {
-            const uint32_t req = bits[v][k] ? (bits[v][k] - last[v][k] + 2 * L + 31) / 32 : 0u;
-            const uint32_t tot = wave_sum(req);
-            if (lane == 0) lgw[v][k][j] = tot;
-        }
+        out[0][k] = (bits[0][k] << 5) | last[0][k];
+        out[1][k] = (bits[1][k] << 5) | last[1][k];
     }
 }
 
@@ -518,16 +616,18 @@ struct AnalyzeTail {
     uint8_t lens[B][256];    // HUF code lengths
     uint8_t lens2[B][256];   // ZG code lengths
     uint32_t z[4];           // ZG fill value: the most frequent byte (smallest on ties)
+    uint32_t zn[4];          // its count over the marked groups
     uint32_t open;           // bit k: mode still to be decided (neither forced RAW nor RLE)
+    uint32_t build[3];       // bit k: codes to build: HUF, ZG, HUF where a forced ZG falls back to it
     uint32_t hc;             // bit k: HUF candidate
-    uint32_t zc;             // bit k: ZG considered (histogram over marked groups needed)
+    uint32_t zc;             // bit k: ZG considered (its histogram is needed)
     uint32_t zgc;            // bit k: ZG candidate
     uint32_t fin;            // bit k: ZG chosen (else HUF) for a coded stream
     uint32_t coded;          // bit k: coded (HUF or ZG chosen)
     uint32_t words[2][4];    // words over all lane groups, per stream: HUF, ZG
     uint32_t T[2][4];        // coded bits of the candidates: HUF, ZG
     int pol[4];              // policy of each group in this chunk (RAW where probing skips it)
-    uint32_t specok;         // bit k: the main pass's count of zeros in marked groups holds (z = 0)
+    uint32_t specok;         // bit k: the main pass's count of zeros in unmarked groups holds (z = 0)
     uint32_t amb;            // staged packing: bit k, the mode decision needs exact sizes
 };
 
@@ -536,33 +636,31 @@ struct AnalyzeTail {
 // others, where a byte group that the run's probe chunk stored raw is stored
 // raw without analysis under AUTO: compressibility probing, paper §III-B):
 //   1. histogram f of every byte group;
-//   2. wave k classifies group k: forced RAW, RLE (one value), else HUF
-//      lengths of f (unless ZG is forced) and, when ZG is forced or (AUTO)
-//      the most frequent value z fills half the group, a ZG candidate;
-//   3. for ZG candidates: histogram over the groups of g symbols that hold a
-//      value other than z, and ZG lengths of it;
-//   4. the four waves count the words of every candidate lane group by lane
-//      group for every candidate, which gives the exact sizes;
+//   2. wave k classifies group k: forced RAW, RLE (one value), else a HUF
+//      candidate (unless ZG is forced) and, when ZG is forced or (AUTO) the
+//      most frequent value z fills half the group, a ZG candidate, whose
+//      histogram counts only the groups of g symbols that hold another value;
+//   3. the workgroup builds the candidates' code lengths;
+//   4. its waves sum the code bits of every candidate, each wave a range of
+//      steps of a lane group, which gives the exact sizes;
 //   5. the mode of each group (AUTO: the smallest of RAW, HUF, ZG, ties to
 //      RAW then HUF), its entry, its lane-group word counts and its canonical
 //      code table.
-// (analyze_chunk below; k_analyze runs it over the chunks, k_analyze_pack
-// packs each chunk after it.)
 
 // Shared memory of the analysis of one chunk.
 template <int BB>
 struct AnalyzeShared {
     AnalyzeLds<BB> S;
     uint32_t hist[BB][256];
+    uint32_t lgw[2][BB][64];        // words per lane group: HUF, ZG
     AnalyzeTail<BB> A;
-    uint32_t zsum[kWaves][4];
-    uint32_t zspec[kWaves][4];
+    uint32_t zsum[kAnWaves][4];     // symbols in unmarked groups, per wave
 };
 
-// The analysis of chunk gc by one workgroup (steps 1-5 above).  Returns
-// false when the probing phase leaves the chunk to the other launch.
+// The analysis of chunk gc by one workgroup (steps 1-5 above); a chunk that
+// the probing phase leaves to the other launch is passed over.
 template <int BB>
-__device__ __attribute__((always_inline)) bool analyze_chunk(uint32_t gc, const EncDesc* __restrict__ descs,
+__device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const EncDesc* __restrict__ descs,
                                                              int n_desc, const uint32_t* __restrict__ chunk_prefix,
                                                              const EncParams& p, int phase,
                                                              EncEntry* __restrict__ entries, CodeWord* __restrict__ codes,
@@ -571,16 +669,15 @@ __device__ __attribute__((always_inline)) bool analyze_chunk(uint32_t gc, const 
     AnalyzeLds<BB>& S = sh.S;
     auto& hist = sh.hist;
     AnalyzeTail<BB>& A = sh.A;
-    auto& zsum = sh.zsum;
-    auto& zspec = sh.zspec;
-    const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
     constexpr uint32_t B = BB;
     const int di = find_desc(chunk_prefix, n_desc, gc);
     const EncDesc d = descs[di];
     const uint32_t c = gc - chunk_prefix[di];
     const uint32_t run = p.skip + 1;
     const bool probe = c % run == 0;
-    if ((phase == 0 && !probe) || (phase == 1 && probe)) return false;
+    if ((phase == 0 && !probe) || (phase == 1 && probe)) return;
     // the groups this chunk analyses (uniform: every thread reads the same entries)
     uint32_t live = (1u << B) - 1;
     if (!probe)
@@ -602,10 +699,13 @@ __device__ __attribute__((always_inline)) bool analyze_chunk(uint32_t gc, const 
             e.bytes = m;
             entries[uint64_t(gc) * B + t] = e;
         }
-        return true;
+        return;
     }
-    for (uint32_t i = t; i < kRep * kRepStride; i += kBlock) (&S.rep[0][0])[i] = 0;
-    if (t == 0) A.open = A.hc = A.zc = A.zgc = A.fin = A.coded = A.specok = A.amb = 0;
+    constexpr uint32_t kCopyWords = sizeof(S.copies) / 4;
+    for (uint32_t i = t; i < kCopyWords / 4; i += kAnThreads)
+        reinterpret_cast<uint4*>(&S.copies[0][0][0])[i] = make_uint4(0, 0, 0, 0);
+    for (uint32_t i = t; i < B * 256; i += kAnThreads) (&hist[0][0])[i] = 0;
+    if (t == 0) A.open = A.build[0] = A.build[1] = A.build[2] = A.hc = A.zc = A.zgc = A.fin = A.coded = A.specok = A.amb = 0;
     if (t < 8) (&A.words[0][0])[t] = 0;
     if (t < 4) A.pol[t] = ((live >> t) & 1) ? int(p.policy[t]) : ZIPNN_RAW;
     __syncthreads();
@@ -613,45 +713,41 @@ __device__ __attribute__((always_inline)) bool analyze_chunk(uint32_t gc, const 
     const uint8_t* base = d.base ? d.base + e0 * B : nullptr;
     const uint32_t nbytes = m * B;
     const bool xf = (p.flags & kFlagExp) != 0;
-    // this lane's copy of every byte group's histogram
-    constexpr uint32_t R = kRep / B;
-    const uint32_t rc = uint32_t(lane) / (64 / R);
-    const uint32_t rshift = rc * (32 / R);
-    auto bin = [&](uint32_t k, uint32_t v) { return &S.rep[k * R + rc][v + rshift]; };
     // 16-byte vectors; the element boundary is aligned since 16 % B == 0
     const uint32_t nvec = nbytes / 16;
-    // a stream whose bytes agree across an eighth of the wave's lanes in
-    // the first vector is taken as skewed: there, the lanes holding the
-    // first active lane's value add together, since LDS atomics on one
-    // bin serialise (the rule only changes how the counts are summed)
-    uint32_t skew = 0;
-    if (uint32_t(t) < nvec) {
-        uint4 x = ((const uint4*)src)[t];
+    auto load = [&](uint32_t v, uint32_t* x) __attribute__((always_inline)) {
+        loadNB<16>(src + uint64_t(v) * 16, x);
         if (base) {
-            const uint4 y = ((const uint4*)base)[t];
-            x.x ^= y.x;
+            uint32_t y[4];
+            loadNB<16>(base + uint64_t(v) * 16, y);
+#pragma unroll
+            for (int i = 0; i < 4; i++) x[i] ^= y[i];
         }
-        if (xf) x.x = exp_fwd<B>(x.x);
-        for (uint32_t k = 0; k < B; k++) {
-            const uint32_t byte = (x.x >> (8 * (B - 1 - k))) & 0xFFu;
-            const uint32_t hot = __builtin_amdgcn_readfirstlane(byte);
-            if (__popcll(__ballot(byte == hot)) >= 8) skew |= 1u << k;
-        }
-    }
-    skew = __builtin_amdgcn_readfirstlane(skew);
-    // Delta-like groups (zero bytes in at least half of the first 64
-    // vectors; the same vectors in every wave, so the choice is uniform)
-    // also count, in this pass, the zero bytes that lie in groups of g
-    // holding a nonzero byte.  Every nonzero byte lies in such a group, so
-    // if 0 turns out to be the most frequent value, the ZG histogram is
-    // this pass's histogram with that count in place of the count of 0,
-    // and the ZG pass over the data is not needed.
+        if (xf)
+#pragma unroll
+            for (int i = 0; i < 4; i++) x[i] = exp_fwd<B>(x[i]);
+    };
+    // this lane's copy of the counters: B = 1 counts in 32 bits, else byte
+    // groups 2a and 2a+1 in the halves of array a
+    const uint32_t copy = uint32_t(lane) % kCopies;
+    auto add = [&](uint32_t k, uint32_t v) __attribute__((always_inline)) {
+        atomicAdd(&S.copies[k / 2][v][copy], (B > 1 && (k & 1)) ? 0x10000u : 1u);
+    };
+    // Delta-like groups (zero bytes in at least half of the first 64 vectors;
+    // the same vectors in every wave, so the choice is uniform) also count, in
+    // this pass, the groups of g zero bytes.  If 0 turns out to be the most
+    // frequent value, that gives the ZG histogram without a pass of its own.
+    const uint32_t gB = p.g * B;
     uint32_t spec = 0;
-    if (nbytes % 16 == 0 && p.g * B <= 16) {
+    if (nbytes % 16 == 0 && gB <= 16) {
         uint32_t x0 = 0;
         if (uint32_t(lane) < nvec) {
-            x0 = ((const uint32_t*)src)[4 * lane];
-            if (base) x0 ^= ((const uint32_t*)base)[4 * lane];
+            loadNB<4>(src + 16 * lane, &x0);
+            if (base) {
+                uint32_t y0;
+                loadNB<4>(base + 16 * lane, &y0);
+                x0 ^= y0;
+            }
             if (xf) x0 = exp_fwd<B>(x0);
         }
         for (uint32_t k = 0; k < B; k++) {
@@ -661,152 +757,136 @@ __device__ __attribute__((always_inline)) bool analyze_chunk(uint32_t gc, const 
         }
     }
     spec = __builtin_amdgcn_readfirstlane(spec);
-    uint32_t zin[4] = {0, 0, 0, 0};   // zero bytes in marked groups, per group of bytes
-    const uint32_t G = p.g;
-    // SK: the skewed streams, known here (or -1: tested per byte)
-    // LV: every group is live (no per-byte test)
-    // SP: count the zeros in marked groups of the streams in `spec`
-    auto count = [&](auto sk_const, auto lv_const, auto sp_const) {
-        constexpr int SK = decltype(sk_const)::value;
+    uint32_t unz[B];   // zero bytes in unmarked groups
+#pragma unroll
+    for (uint32_t k = 0; k < B; k++) unz[k] = 0;
+    // LV: every group is live (no per-byte test); SP: count the groups of
+    // zeros of the streams in `spec`
+    auto count = [&](auto lv_const, auto sp_const, uint32_t v_begin, uint32_t v_end) {
         constexpr bool LV = decltype(lv_const)::value;
         constexpr bool SP = decltype(sp_const)::value;
         constexpr uint32_t HB = 4;   // vectors in flight per lane (with the base: 8 loads)
-        for (uint32_t v0 = t; v0 < nvec; v0 += HB * kBlock) {
-          uint4 xs[HB];
+        for (uint32_t v0 = v_begin + t; v0 < v_end; v0 += HB * kAnThreads) {
+            uint32_t xs[HB][4];
 #pragma unroll
-          for (uint32_t i = 0; i < HB; i++) {
-              const uint32_t v = v0 + i * kBlock;
-              if (v < nvec) {
-                  xs[i] = ((const uint4*)src)[v];
-                  if (base) {
-                      const uint4 y = ((const uint4*)base)[v];
-                      xs[i].x ^= y.x;
-                      xs[i].y ^= y.y;
-                      xs[i].z ^= y.z;
-                      xs[i].w ^= y.w;
-                  }
-                  if (xf) {
-                      xs[i].x = exp_fwd<B>(xs[i].x);
-                      xs[i].y = exp_fwd<B>(xs[i].y);
-                      xs[i].z = exp_fwd<B>(xs[i].z);
-                      xs[i].w = exp_fwd<B>(xs[i].w);
-                  }
-              }
-          }
+            for (uint32_t i = 0; i < HB; i++)
+                if (v0 + i * kAnThreads < v_end) load(v0 + i * kAnThreads, xs[i]);
 #pragma unroll
-          for (uint32_t i = 0; i < HB; i++) {
-            if (v0 + i * kBlock < nvec) {
-            const uint32_t wds[4] = {xs[i].x, xs[i].y, xs[i].z, xs[i].w};
+            for (uint32_t i = 0; i < HB; i++) {
+                if (v0 + i * kAnThreads >= v_end) continue;
+                const uint32_t* x = xs[i];
 #pragma unroll
-            for (int jb = 0; jb < 16; jb++) {
-                const uint32_t byte = (wds[jb >> 2] >> (8 * (jb & 3))) & 0xFF;
-                const int k = int(B) - 1 - (jb % int(B));   // byte jb%B of a word -> stream B-1-jb%B
-                if (!LV && !((live >> k) & 1)) continue;
-                const bool sk = SK >= 0 ? ((SK >> k) & 1) != 0 : ((skew >> k) & 1) != 0;
-                if (sk) {
-                    const uint32_t hot = __builtin_amdgcn_readfirstlane(byte);
-                    const uint64_t msk = __ballot(byte == hot);
-                    if (byte != hot) atomicAdd(bin(k, byte), 1u);
-                    else if (__builtin_amdgcn_mbcnt_hi(uint32_t(msk >> 32),
-                                                       __builtin_amdgcn_mbcnt_lo(uint32_t(msk), 0u)) == 0)
-                        atomicAdd(bin(k, hot), uint32_t(__popcll(msk)));
-                } else {
-                    atomicAdd(bin(k, byte), 1u);
+                for (int jb = 0; jb < 16; jb++) {
+                    const uint32_t byte = (x[jb >> 2] >> (8 * (jb & 3))) & 0xFFu;
+                    const int k = int(B) - 1 - (jb % int(B));   // byte jb%B of a word -> stream B-1-jb%B
+                    if (!LV && !((live >> k) & 1)) continue;
+                    add(uint32_t(k), byte);
+                }
+                if constexpr (SP) {
+#pragma unroll
+                    for (int k = 0; k < int(B); k++) {
+                        if (!((spec >> k) & 1)) continue;
+                        // the stream's bytes of the four words
+                        constexpr uint32_t kAll = B == 1 ? 0xFFFFFFFFu : (B == 2 ? 0x00FF00FFu : 0x000000FFu);
+                        const uint32_t km = B == 1 ? kAll : kAll << (8 * (int(B) - 1 - k));
+                        uint32_t un = 0;   // groups of zeros in this vector
+                        if (gB == 2) {
+#pragma unroll
+                            for (int y = 0; y < 4; y++)
+                                un += uint32_t((x[y] & km & 0xFFFFu) == 0) + uint32_t((x[y] & km & 0xFFFF0000u) == 0);
+                        } else if (gB == 4) {
+#pragma unroll
+                            for (int y = 0; y < 4; y++) un += uint32_t((x[y] & km) == 0);
+                        } else if (gB == 8) {
+                            un += uint32_t(((x[0] | x[1]) & km) == 0) + uint32_t(((x[2] | x[3]) & km) == 0);
+                        } else {
+                            un += uint32_t(((x[0] | x[1] | x[2] | x[3]) & km) == 0);
+                        }
+                        unz[k] += un * p.g;
+                    }
                 }
             }
-            if constexpr (SP) {
-#pragma unroll
-                for (int k = 0; k < int(B); k++) {
-                    if (!((spec >> k) & 1)) continue;
-                    uint32_t nz = 0;   // bit e: element e's byte of group k is nonzero
-#pragma unroll
-                    for (int e = 0; e < 16 / int(B); e++) {
-                        const int jb = e * int(B) + (int(B) - 1 - k);
-                        nz |= uint32_t(((wds[jb >> 2] >> (8 * (jb & 3))) & 0xFFu) != 0) << e;
-                    }
-                    uint32_t mk = 0;   // bit e: element e's group of g holds a nonzero byte
-                    for (uint32_t g0 = 0; g0 < 16 / B; g0 += G) {
-                        const uint32_t gm = ((1u << G) - 1) << g0;
-                        if (nz & gm) mk |= gm;
-                    }
-                    zin[k] += __popc(mk & ~nz);
-                }
-            }
-            }
-          }
         }
     };
-    {
-        using std::integral_constant;
-        using T = integral_constant<bool, true>;
-        using F = integral_constant<bool, false>;
-        if (live != (1u << B) - 1) count(integral_constant<int, -1>{}, F{}, F{});
-        else if (spec) count(integral_constant<int, -1>{}, T{}, T{});
-        else if (skew == 0) count(integral_constant<int, 0>{}, T{}, F{});
-        else if (skew == 1) count(integral_constant<int, 1>{}, T{}, F{});
-        else if (B >= 2 && skew == 3) count(integral_constant<int, B >= 2 ? 3 : -1>{}, T{}, F{});
-        else count(integral_constant<int, -1>{}, T{}, F{});
-    }
-    if (spec)
-        for (uint32_t k = 0; k < B; k++) {
-            const uint32_t zs = wave_sum(zin[k]);
-            if (lane == 0) zspec[wv][k] = zs;
+    for (uint32_t part = 0;; part += kPartVec) {
+        const uint32_t v_end = min(nvec, part + kPartVec);
+        using T = std::integral_constant<bool, true>;
+        using F = std::integral_constant<bool, false>;
+        if (spec) count(F{}, T{}, part, v_end);
+        else if (live != (1u << B) - 1) count(F{}, F{}, part, v_end);
+        else count(T{}, F{}, part, v_end);
+        const bool done = v_end == nvec;
+        if (done)   // the elements after the last whole vector
+            for (uint32_t e = nvec * 16 / B + t; e < m; e += kAnThreads) {
+                const uint32_t v = element_word<B>(src, base, e, xf);
+                for (uint32_t b = 0; b < B; b++)
+                    if ((live >> (B - 1 - b)) & 1) add(B - 1 - b, (v >> (8 * b)) & 0xFFu);
+            }
+        __syncthreads();
+        // the copies of a bin: four threads sum eight counters each
+        const uint32_t s = uint32_t(t) >> 2, q = uint32_t(t) & 3;
+        static_assert(kAnThreads == 1024 && kCopies == 32, "four threads per bin");
+        for (uint32_t a = 0; a < (B == 4 ? 2u : 1u); a++) {
+            uint4* cp = reinterpret_cast<uint4*>(&S.copies[a][s][8 * q]);
+            const uint4 x = cp[0], y = cp[1];
+            if (!done) cp[0] = cp[1] = make_uint4(0, 0, 0, 0);
+            const uint32_t w8[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+            uint32_t lo = 0, hi = 0;
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                lo += B == 1 ? w8[i] : (w8[i] & 0xFFFFu);
+                hi += w8[i] >> 16;
+            }
+            lo += __shfl_xor(lo, 1, 64);
+            lo += __shfl_xor(lo, 2, 64);
+            hi += __shfl_xor(hi, 1, 64);
+            hi += __shfl_xor(hi, 2, 64);
+            if (q == 0) {
+                hist[2 * a][s] += lo;
+                if (B > 1) hist[2 * a + 1][s] += hi;
+            }
         }
-    // the elements after the last whole vector
-    for (uint32_t e = nvec * 16 / B + t; e < m; e += kBlock) {
-        const uint32_t v = element_word<B>(src, base, e, xf);
-        for (uint32_t b = 0; b < B; b++)
-            if ((live >> (B - 1 - b)) & 1) atomicAdd(bin(B - 1 - b, (v >> (8 * b)) & 0xFFu), 1u);
+        __syncthreads();
+        if (done) break;
     }
-    __syncthreads();
-    for (uint32_t i = t; i < B * 256; i += kBlock) {
-        const uint32_t k = i >> 8, s = i & 255;
-        uint32_t v = 0;
-        for (uint32_t r = 0; r < R; r++) v += S.rep[k * R + r][s + r * (32 / R)];
-        hist[k][s] = v;
+    if (spec) {
+#pragma unroll
+        for (uint32_t k = 0; k < B; k++) {
+            const uint32_t un = wave_sum(unz[k]);
+            if (lane == 0) sh.zsum[wv][k] = un;
+        }
     }
-    __syncthreads();
-    // 2. classification and HUF lengths, wave k for group k
+    // 2. classification, wave k for group k
     if (uint32_t(wv) < B) {
         const int k = wv;
         const int policy = A.pol[k];
-        uint32_t fv[4], d = 0, best = 0, arg = 0;
+        uint32_t fv[4], nd = 0, best = 0;
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             fv[r] = hist[k][lane + 64 * r];
-            d += __popcll(__ballot(fv[r] > 0));
+            nd += __popcll(__ballot(fv[r] > 0));
             // most frequent value, smallest on ties: key f << 8 | (255 - s)
-            const uint32_t key = (fv[r] << 8) | uint32_t(255 - (lane + 64 * r));
-            if (key > best) best = key;
+            best = max(best, (fv[r] << 8) | uint32_t(255 - (lane + 64 * r)));
         }
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) best = max(best, uint32_t(__shfl_xor(best, o, 64)));
-        arg = 255 - (best & 0xFFu);
-        const uint64_t ei = uint64_t(gc) * B + k;
-        if (policy == ZIPNN_RAW || d <= 1) {
+        const uint32_t arg = 255 - (best & 0xFFu);
+        if (policy == ZIPNN_RAW || nd <= 1) {
             if (lane == 0) {
                 EncEntry e;
                 e.pad = 0;
-                const bool rle = policy != ZIPNN_RAW && d == 1;
+                const bool rle = policy != ZIPNN_RAW && nd == 1;
                 e.mode = rle ? kModeRle : kModeRaw;
                 e.rle = rle ? uint8_t(arg) : 0;
                 e.bytes = rle ? 0 : m;
-                entries[ei] = e;
+                entries[uint64_t(gc) * B + k] = e;
             }
         } else {
-            bool hc = false;
-            if (policy != ZIPNN_ZG) {
-                uint32_t T;
-                hc = build_lengths(fv, m, m, head, p.L, policy == ZIPNN_AUTO, S.pm[k], T);
-                if (lane == 0) A.T[0][k] = T;
-                if (hc)
-#pragma unroll
-                    for (int r = 0; r < 4; r++) A.lens[k][lane + 64 * r] = S.pm[k].len[lane + 64 * r];
-            }
+            const bool huf = policy == ZIPNN_HUF || (policy == ZIPNN_AUTO && !entropy_says_raw(fv, m, head, m));
             const bool zc = policy == ZIPNN_ZG || (policy == ZIPNN_AUTO && 2 * (best >> 8) >= m);
             if (lane == 0) {
                 atomicOr(&A.open, 1u << k);
-                if (hc) atomicOr(&A.hc, 1u << k);
+                if (huf) atomicOr(&A.build[0], 1u << k);
                 if (zc) atomicOr(&A.zc, 1u << k);
                 if (zc && ((spec >> k) & 1) && arg == 0) atomicOr(&A.specok, 1u << k);
                 A.z[k] = arg;
@@ -814,74 +894,70 @@ __device__ __attribute__((always_inline)) bool analyze_chunk(uint32_t gc, const 
         }
     }
     __syncthreads();
-    // 3. ZG: histogram over the marked groups, then lengths
+    // the ZG histograms
     if (A.zc) {
-        // groups whose ZG histogram the main pass could not give: one more
-        // pass over the data
+        // groups whose count of unmarked symbols the main pass could not
+        // give: one more pass over the data
         const uint32_t need = A.zc & ~A.specok;
         if (need) {
-            for (uint32_t i = t; i < kWaves * B * 256; i += kBlock) (&S.hist[0][0][0])[i] = 0;
-            __syncthreads();
-            uint32_t zn[4] = {0, 0, 0, 0};
+            uint32_t un[B];
             switch (p.g) {
-            case 2: zg_count<BB, 2>(src, base, need, A.z, m, S.hist[wv], zn, xf); break;
-            case 4: zg_count<BB, 4>(src, base, need, A.z, m, S.hist[wv], zn, xf); break;
-            default: zg_count<BB, 8>(src, base, need, A.z, m, S.hist[wv], zn, xf); break;
+            case 2: zg_unmarked<BB, 2>(src, base, need, A.z, m, un, xf); break;
+            case 4: zg_unmarked<BB, 4>(src, base, need, A.z, m, un, xf); break;
+            default: zg_unmarked<BB, 8>(src, base, need, A.z, m, un, xf); break;
             }
-            if (lane == 0)
-                for (uint32_t k = 0; k < B; k++) zsum[wv][k] = zn[k];
-            __syncthreads();
-            for (uint32_t i = t; i < B * 256; i += kBlock) {
-                const uint32_t k = i >> 8, s = i & 255;
-                uint32_t v = S.hist[0][k][s] + S.hist[1][k][s] + S.hist[2][k][s] + S.hist[3][k][s];
-                if (s == A.z[k]) v += zsum[0][k] + zsum[1][k] + zsum[2][k] + zsum[3][k];
-                S.hist[0][k][s] = v;
-            }
-            __syncthreads();
-        }
-        uint32_t fv[4] = {0, 0, 0, 0}, tot = 0, d2 = 0;
-        if (uint32_t(wv) < B) {
-            const bool fromspec = (A.specok >> wv) & 1;
-            const uint32_t z0 = zspec[0][wv] + zspec[1][wv] + zspec[2][wv] + zspec[3][wv];
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const uint32_t sym = lane + 64 * r;
-                fv[r] = fromspec ? (sym == 0 ? z0 : hist[wv][sym]) : S.hist[0][wv][sym];
-                tot += fv[r];
-                d2 += __popcll(__ballot(fv[r] > 0));
-            }
-            tot = wave_sum(tot);
+            for (uint32_t k = 0; k < B; k++)
+                if (lane == 0 && ((need >> k) & 1)) sh.zsum[wv][k] = un[k];
+            __syncthreads();
         }
-        __syncthreads();   // the sums are read before the workspace is reused
         if (uint32_t(wv) < B && ((A.zc >> wv) & 1)) {
             const int k = wv;
-            const int policy = A.pol[k];
-            if (d2 >= 2) {
-                uint32_t T;
-                const bool zgc = build_lengths(fv, tot, m, head_z, p.L, policy == ZIPNN_AUTO, S.pm[k], T);
-                if (lane == 0) A.T[1][k] = T;
-                if (zgc) {
+            const uint32_t z = A.z[k];
+            uint32_t zn = hist[k][z];
+            for (int i = 0; i < kAnWaves; i++) zn -= sh.zsum[i][k];
+            uint32_t fv[4], tot = 0, nd = 0;
 #pragma unroll
-                    for (int r = 0; r < 4; r++) A.lens2[k][lane + 64 * r] = S.pm[k].len[lane + 64 * r];
-                    if (lane == 0) atomicOr(&A.zgc, 1u << k);
-                }
-            } else if (policy == ZIPNN_ZG) {
+            for (int r = 0; r < 4; r++) {
+                fv[r] = uint32_t(lane + 64 * r) == z ? zn : hist[k][lane + 64 * r];
+                tot += fv[r];
+                nd += __popcll(__ballot(fv[r] > 0));
+            }
+            tot = wave_sum(tot);
+            const bool zg = nd >= 2 && !(A.pol[k] == ZIPNN_AUTO && entropy_says_raw(fv, tot, head_z, m));
+            if (lane == 0) {
+                A.zn[k] = zn;
+                if (zg) atomicOr(&A.build[1], 1u << k);
                 // the marked groups hold a single value: forced ZG falls back to HUF
-                uint32_t f[4];
-#pragma unroll
-                for (int r = 0; r < 4; r++) f[r] = hist[k][lane + 64 * r];
-                uint32_t T;
-                build_lengths(f, m, m, head, p.L, false, S.pm[k], T);
-#pragma unroll
-                for (int r = 0; r < 4; r++) A.lens[k][lane + 64 * r] = S.pm[k].len[lane + 64 * r];
-                if (lane == 0) atomicOr(&A.hc, 1u << k);
+                if (nd < 2 && A.pol[k] == ZIPNN_ZG) atomicOr(&A.build[2], 1u << k);
             }
         }
         __syncthreads();
     }
+    // 3. the code lengths, one wave per code: HUF, ZG, fallback HUF
+    if (uint32_t(wv) < 3 * B) {
+        const int v = wv / int(B), k = wv % int(B);
+        if ((A.build[v] >> k) & 1) {
+            uint32_t fv[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const uint32_t s = uint32_t(lane) + 64 * r;
+                fv[r] = v == 1 && s == A.z[k] ? A.zn[k] : hist[k][s];
+            }
+            const uint32_t bits = build_lengths(fv, S.pm[wv], p.L, v == 1 ? A.lens2[k] : A.lens[k]);
+            // under AUTO a payload of at least its head and coded bits that
+            // is no smaller than the raw bytes is out
+            if (lane == 0) {
+                A.T[v == 1][k] = bits;
+                if (A.pol[k] != ZIPNN_AUTO || (v == 1 ? head_z : head) + (bits + 7) / 8 < m)
+                    atomicOr(v == 1 ? &A.zgc : &A.hc, 1u << k);
+            }
+        }
+    }
+    __syncthreads();
     // AUTO with both candidates: a candidate that loses even at its best
     // (head + coded bits) against the other at its worst (plus two words
-    // of padding per sub-stream) needs no replay; ties go to HUF
+    // of padding per sub-stream) needs no count; ties go to HUF
     if (uint32_t(t) < B && A.pol[t] == ZIPNN_AUTO && ((A.hc & A.zgc) >> t & 1)) {
         const uint64_t h_lo = head + (A.T[0][t] + 7) / 8, h_hi = h_lo + 8 * W;
         const uint64_t z_lo = head_z + (A.T[1][t] + 7) / 8, z_hi = z_lo + 8 * W;
@@ -908,20 +984,64 @@ __device__ __attribute__((always_inline)) bool analyze_chunk(uint32_t gc, const 
     }
     __syncthreads();
     const bool exact = !staged || A.amb != 0;
-    // 4. the words of every candidate, one lane group per wave
-    if ((A.hc | A.zgc) && exact) {
-        for (uint32_t j0 = 0; j0 < NG; j0 += kWaves) {
-            const uint32_t j = j0 + wv;
-            if (j < NG) {
-                switch (p.g) {
-                case 2: count_lane_group<BB, 2>(src, base, A.hc, A.zgc, A.lens, A.lens2, A.z, p.L, j, W, m, S.lgw, xf); break;
-                case 4: count_lane_group<BB, 4>(src, base, A.hc, A.zgc, A.lens, A.lens2, A.z, p.L, j, W, m, S.lgw, xf); break;
-                default: count_lane_group<BB, 8>(src, base, A.hc, A.zgc, A.lens, A.lens2, A.z, p.L, j, W, m, S.lgw, xf); break;
-                }
-                if (lane == 0) {
+    // 4. the words of every candidate.  A lane group's steps are cut into
+    // nseg ranges, one wave each, when there are fewer lane groups than waves.
+    const uint32_t hc = __builtin_amdgcn_readfirstlane(A.hc), zgc = __builtin_amdgcn_readfirstlane(A.zgc);
+    if ((hc | zgc) && exact) {
+        const uint32_t Gtot = (m + p.g - 1) / p.g;
+        const uint32_t steps = (Gtot - 1) / W + 1;   // of lane 0 of the first lane group, the most
+        const uint32_t nseg = NG < uint32_t(kAnWaves) ? uint32_t(kAnWaves) / NG : 1u;
+        const uint32_t per = (steps + nseg - 1) / nseg;
+        auto steps_of = [&](uint32_t j, uint32_t s0, uint32_t s1, uint32_t (*out)[BB]) __attribute__((always_inline)) {
+            switch (p.g) {
+            case 2: count_steps<BB, 2>(src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
+            case 4: count_steps<BB, 4>(src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
+            default: count_steps<BB, 8>(src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
+            }
+        };
+        // wave wv: range wv / NG of lane group wv % NG, or (nseg = 1) all of
+        // lane groups wv, wv + kAnWaves, ...
+        for (uint32_t j0 = 0; j0 < NG; j0 += kAnWaves) {
+            const uint32_t sg = nseg > 1 ? uint32_t(wv) / NG : 0u, j = nseg > 1 ? uint32_t(wv) % NG : j0 + wv;
+            uint32_t out[2][BB];
+            const bool mine = nseg > 1 ? sg < nseg : j < NG;
+            if (mine) steps_of(j, sg * per, min(steps, (sg + 1) * per), out);
+            if (nseg > 1) {
+                if (mine) {
+#pragma unroll
                     for (uint32_t k = 0; k < B; k++) {
-                        if ((A.hc >> k) & 1) atomicAdd(&A.words[0][k], S.lgw[0][k][j]);
-                        if ((A.zgc >> k) & 1) atomicAdd(&A.words[1][k], S.lgw[1][k][j]);
+                        S.seg[0][k][t] = out[0][k];
+                        S.seg[1][k][t] = out[1][k];
+                    }
+                }
+                __syncthreads();
+            }
+            const uint32_t jw = j0 + wv;   // this wave sums up lane group jw
+            if (jw >= NG) continue;
+#pragma unroll
+            for (int k = 0; k < BB; k++) {
+#pragma unroll
+                for (int v = 0; v < 2; v++) {
+                    if (!(((v ? zgc : hc) >> k) & 1)) continue;
+                    uint32_t bits = 0, last = 0;
+                    if (nseg == 1) {
+                        bits = out[v][k] >> 5;
+                        last = out[v][k] & 31;
+                    } else {
+                        for (uint32_t g = 0; g < nseg; g++) {
+                            const uint32_t x = S.seg[v][k][64 * (g * NG + jw) + lane];
+                            bits += x >> 5;
+                            last = x ? x & 31 : last;
+                        }
+                    }
+                    // before each pair a lane holding fewer than 2L bits takes
+                    // a word, so after that check 32 * taken - consumed lies in
+                    // [2L, 2L + 31]: a lane takes ceil((consumed before its
+                    // last pair + 2L) / 32) words in all, none without a pair
+                    const uint32_t tot = wave_sum(bits ? (bits - last + 2 * p.L + 31) / 32 : 0u);
+                    if (lane == 0) {
+                        sh.lgw[v][k][jw] = tot;
+                        atomicAdd(&A.words[v][k], tot);
                     }
                 }
             }
@@ -934,15 +1054,15 @@ __device__ __attribute__((always_inline)) bool analyze_chunk(uint32_t gc, const 
     // counts.
     if (uint32_t(t) < B && ((A.open >> t) & 1)) {
         const int policy = A.pol[t];
-        const bool hc = (A.hc >> t) & 1, zgc = (A.zgc >> t) & 1;
+        const bool hc1 = (A.hc >> t) & 1, zgc1 = (A.zgc >> t) & 1;
         const uint32_t size_h = exact ? head + 4 * A.words[0][t] : head + (A.T[0][t] + 7) / 8;
         const uint32_t size_z = exact ? head_z + 4 * A.words[1][t] : head_z + (A.T[1][t] + 7) / 8;
         int mode = kModeRaw;
         uint32_t bytes = m;
         if (policy == ZIPNN_AUTO) {
-            if (hc && size_h < bytes) mode = kModeHuf, bytes = size_h;
-            if (zgc && size_z < bytes) mode = kModeZg, bytes = size_z;
-        } else if (zgc) {
+            if (hc1 && size_h < bytes) mode = kModeHuf, bytes = size_h;
+            if (zgc1 && size_z < bytes) mode = kModeZg, bytes = size_z;
+        } else if (zgc1) {
             mode = kModeZg, bytes = size_z;
         } else {
             mode = kModeHuf, bytes = size_h;
@@ -961,28 +1081,19 @@ __device__ __attribute__((always_inline)) bool analyze_chunk(uint32_t gc, const 
         const uint64_t ei = uint64_t(gc) * B + wv;
         const int v = (A.fin >> wv) & 1;
         canonical_codes(v ? A.lens2[wv] : A.lens[wv], p.L, codes + ei * 256);
-        if (!staged && uint32_t(lane) < NG) nwords[ei * 64 + lane] = S.lgw[v][wv][lane];
+        if (!staged && uint32_t(lane) < NG) nwords[ei * 64 + lane] = sh.lgw[v][wv][lane];
     }
     __syncthreads();
-    return true;
 }
 
-// Occupancy matters more than spills here: the passes are latency-bound per
-// workgroup.  Four waves per SIMD (128 VGPRs) were 5-9% faster than three;
-// for 2-byte words five (96 VGPRs, some spills in the counting loop) encoded
-// the BF16 checkpoint 5% and its XOR delta 10% faster than four, and six (80
-// VGPRs) are faster again: the checkpoint 1-3% at 256 and 512 KiB chunks, the
-// Huffman-only delta 8%.  WV sets the waves per SIMD of the instances for
-// 2-byte words.  Where a group of a launch with an XOR base may take ZG, two
-// codes are built per group, and seven waves (72 VGPRs) encode the delta 5%
-// faster than six (the Huffman-only delta would lose 2%).  Launches with a
-// base use these instances only when they take the exact path; staged ones
-// run k_analyze_pack.
-template <int BB, int WV>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WV, 8))) void k_analyze(const EncDesc* __restrict__ descs, int n_desc,
-                                                    const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
-                                                    EncParams p, int phase, EncEntry* __restrict__ entries,
-                                                    CodeWord* __restrict__ codes, uint32_t* __restrict__ nwords)
+// Two workgroups of 1024 threads per CU, a few spills outside the counting
+// loop.  Against one wave per code and four waves per chunk (8 MiB of BF16:
+// 146 us; nine layers and the embedding of an 8B checkpoint, 5 GB: 3450 us;
+// 256 MiB of FP32: 240 us) this takes 30, 2360 and 170 us.
+template <int BB>
+__global__ __launch_bounds__(kAnThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_analyze(
+    const EncDesc* __restrict__ descs, int n_desc, const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
+    EncParams p, int phase, EncEntry* __restrict__ entries, CodeWord* __restrict__ codes, uint32_t* __restrict__ nwords)
 {
     __shared__ AnalyzeShared<BB> sh;
     for (uint32_t gc = blockIdx.x; gc < total_chunks; gc += gridDim.x)
@@ -1576,33 +1687,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BB == 2 
         pack_chunk<BB, GG>(gc, descs, n_desc, chunk_prefix, p, entries, codes, offsets, totals, nwords, P);
 }
 
-template <int BB>
-union FusedLds {
-    AnalyzeShared<BB> a;
-    PackLds pk;
-};
-
-// Staged launches: a workgroup analyses a chunk and packs it at once into its
-// staging slots, which need no placement first; a chunk's analysis and
-// packing thus share a launch, and the workgroups on a CU mix the two (the
-// checkpoint's XOR delta: Huffman-only encode 16.9 -> 16.0 ms, zero-aware
-// 18.4 -> 17.5 ms).  For 2-byte words seven waves per SIMD (72 VGPRs):
-// faster than six by 5% on the Huffman-only delta, and by about 10% than
-// five.
-template <int BB, int GG, int WV>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WV, 8))) void k_analyze_pack(
-    const EncDesc* __restrict__ descs, int n_desc, const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
-    EncParams p, int phase, EncEntry* entries, CodeWord* codes, uint32_t* nwords)
-{
-    __shared__ FusedLds<BB> u;
-    for (uint32_t gc = blockIdx.x; gc < total_chunks; gc += gridDim.x) {
-        if (!analyze_chunk<BB>(gc, descs, n_desc, chunk_prefix, p, phase, entries, codes, nwords, u.a)) continue;
-        __syncthreads();   // the chunk's entries and code tables, written above, are read below
-        pack_chunk<BB, GG>(gc, descs, n_desc, chunk_prefix, p, entries, codes, nullptr, nullptr, nwords, u.pk);
-        __syncthreads();
-    }
-}
-
 // Staged packing, last step: for each chunk, its map entries, and for each
 // coded stream the head (nibble table, word counts, padding), the ZG bitmap
 // and the lane groups' words copied from their staging slots to their places;
@@ -1709,43 +1793,26 @@ hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_p
 {
     const uint32_t grid = min(max(total_chunks, 1u), 1u << 16);
     const bool xb = (p.flags & kFlagDelta) != 0;   // some tensor has an XOR base
-    bool zg_possible = false;                       // some group may take ZG
-    for (uint32_t k = 0; k < p.B && k < 4; k++) zg_possible |= p.policy[k] == ZIPNN_AUTO || p.policy[k] == ZIPNN_ZG;
     const bool staged = p.stage != nullptr;
     if (total_chunks) {
         // with probing, the probe chunks first: the others read their entries
         for (int phase = p.skip ? 0 : -1; phase <= (p.skip ? 1 : -1); phase++) {
-            bool launched = false;
-            if (staged) {
-#define ZIPNN_FUSED(B_, G_, WV_)                                                                                 \
-    if (!launched && p.B == B_ && p.g == G_) {                                                                  \
-        k_analyze_pack<B_, G_, WV_><<<grid, kBlock, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p,   \
-                                                            phase, entries, codes, nwords);                      \
-        launched = true;                                                                                        \
-    }
-                ZIPNN_FUSED(1, 2, 4) ZIPNN_FUSED(1, 4, 4) ZIPNN_FUSED(1, 8, 4)
-                ZIPNN_FUSED(2, 2, 7) ZIPNN_FUSED(2, 4, 7) ZIPNN_FUSED(2, 8, 7)
-                ZIPNN_FUSED(4, 2, 4) ZIPNN_FUSED(4, 4, 4) ZIPNN_FUSED(4, 8, 4)
-#undef ZIPNN_FUSED
-            } else {
-#define ZIPNN_ANALYZE(B_, WV_)                                                                                   \
-    k_analyze<B_, WV_><<<grid, kBlock, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries, \
-                                               codes, nwords)
-                launched = true;
-                if (p.B == 1) ZIPNN_ANALYZE(1, 4);
-                else if (p.B == 2 && xb && zg_possible) ZIPNN_ANALYZE(2, 7);
-                else if (p.B == 2) ZIPNN_ANALYZE(2, 6);
-                else if (p.B == 4) ZIPNN_ANALYZE(4, 4);
-                else launched = false;
+            bool launched = true;
+#define ZIPNN_ANALYZE(B_)                                                                                         \
+    k_analyze<B_><<<grid, kAnThreads, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries, codes, \
+                                              nwords)
+            if (p.B == 1) ZIPNN_ANALYZE(1);
+            else if (p.B == 2) ZIPNN_ANALYZE(2);
+            else if (p.B == 4) ZIPNN_ANALYZE(4);
+            else launched = false;
 #undef ZIPNN_ANALYZE
-            }
             if (!launched) return hipErrorInvalidValue;
             if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
         }
     }
     // exact: analysis, placement, arena, then packing into the containers;
-    // staged: analysis with packing into the staging slots, placement from
-    // the word counts, arena, then the compaction into the containers
+    // staged: analysis, packing into the staging slots, placement from the
+    // word counts, arena, then the compaction into the containers
     auto pack_or_compact = [&](bool compact) -> hipError_t {
         if (!total_chunks) return hipSuccess;
         bool launched = false;
@@ -1769,6 +1836,10 @@ hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_p
         if (!launched) return hipErrorInvalidValue;
         return hipGetLastError() == hipSuccess ? hipSuccess : hipErrorLaunchFailure;
     };
+    if (staged) {
+        const hipError_t e = pack_or_compact(false);
+        if (e != hipSuccess) return e;
+    }
     k_place<<<n_desc, kBlock, 0, s>>>(d_descs, p, entries, offsets, totals, nwords);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     k_arena<<<1, kBlock, 0, s>>>(d_descs, n_desc, p, arena, cap, totals, arena_off);
