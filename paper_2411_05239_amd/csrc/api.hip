@@ -312,7 +312,7 @@ static int encode_tensors(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, in
     if (hipMemcpyAsync(d_descs, hd, size_t(n) * sizeof(EncDesc), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(d_prefix, hp, size_t(n + 1) * sizeof(uint32_t), hipMemcpyHostToDevice, s) != hipSuccess ||
         launch_encode(d_descs, n, d_prefix, uint32_t(total_chunks), ep, (uint8_t*)arena, cap,
-                      (EncEntry*)(sc + lay.entries), (CodeWord*)(sc + lay.codes), (uint32_t*)(sc + lay.nwords),
+                      (EncEntry*)(sc + lay.entries), sc + lay.codes, (uint32_t*)(sc + lay.nwords),
                       (uint64_t*)(sc + lay.offsets), (uint64_t*)(sc + lay.totals), d_aoff, s) != hipSuccess ||
         hipMemcpyAsync(ho, d_aoff, size_t(n + 1) * sizeof(uint64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
@@ -370,7 +370,7 @@ int zipnn_compress_noalloc(zipnn_ctx ctx, const void* src, int dtype, uint64_t n
     const EncParams ep = make_params(dtype, *p, one.base != nullptr);
     if (launch_fill_desc(one, uint32_t(nc), d_descs, d_prefix, s) != hipSuccess ||
         launch_encode(d_descs, 1, d_prefix, uint32_t(nc), ep, (uint8_t*)dst, dst_cap, (EncEntry*)(sc + lay.entries),
-                      (CodeWord*)(sc + lay.codes), (uint32_t*)(sc + lay.nwords), (uint64_t*)(sc + lay.offsets),
+                      sc + lay.codes, (uint32_t*)(sc + lay.nwords), (uint64_t*)(sc + lay.offsets),
                       (uint64_t*)(sc + lay.totals), d_aoff, s) != hipSuccess ||
         hipMemcpyAsync(ho, d_aoff, sizeof(ho), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
@@ -467,7 +467,7 @@ int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, int
         return ZIPNN_E_HIP;
     }
     hipError_t le = launch_encode(d_descs, n, d_prefix, uint32_t(total_chunks), ep, (uint8_t*)arena, cap,
-                                  (EncEntry*)(sc + lay.entries), (CodeWord*)(sc + lay.codes),
+                                  (EncEntry*)(sc + lay.entries), sc + lay.codes,
                                   (uint32_t*)(sc + lay.nwords), (uint64_t*)(sc + lay.offsets),
                                   (uint64_t*)(sc + lay.totals), d_aoff, e->capst);
     if (le == hipSuccess)

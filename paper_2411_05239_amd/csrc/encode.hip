@@ -34,12 +34,9 @@ namespace zipnn {
 namespace {
 
 constexpr int kWaves = kBlock / 64;
-// The analysis: one workgroup of kAnThreads threads per chunk, two on a CU
-// (at most 64 VGPRs).  One chunk's bytes are then spread over 16 waves, and
-// no more than 512 chunks are in flight on the chip: at 256 KiB they fit the
-// 256 MB last-level cache, which serves the size pass's second read.
-constexpr int kAnThreads = 1024;
-constexpr int kAnWaves = kAnThreads / 64;
+// The analysis runs one workgroup of NT = 512 or 1024 threads per chunk, full
+// CUs of 32 waves at 64 VGPRs: a chunk's bytes are spread over all its waves,
+// and the chunks of a CU are in different phases.
 // The counting pass's histograms: kCopies copies of every bin, side by side;
 // a lane adds to copy (lane mod 32), so the lanes of half a wave always hit
 // 32 different banks, whatever the values (LDS atomics on one bank, let alone
@@ -51,18 +48,40 @@ constexpr uint32_t kCopies = 32;
 constexpr uint32_t kPartVec = (2u << 20) / 16;
 
 // Sized by the word width B.
-template <int B>
+template <int B, int NT>
 union AnalyzeLds {
     uint32_t copies[B == 4 ? 2 : 1][256][kCopies];   // the counting pass
     uint32_t pm[3 * B][256];                         // the code constructions, one wave each
-    uint32_t seg[2][B][kAnThreads];                  // the size pass: bits << 5 | last pair, HUF and ZG
+    uint32_t seg[2][B][NT];                          // the size pass: bits << 5 | last pair, HUF and ZG
 };
 
+// Reductions over a full wave in the vector unit (DPP row shifts, then row
+// broadcasts; lane 63 ends with the result): shuffles through LDS would queue
+// behind the counting passes' atomics.
+template <class F>
+__device__ __attribute__((always_inline)) inline uint32_t wave_reduce(uint32_t v, F op)   // op(0, x) = x
+{
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true));   // row_shr:1
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true));
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true));
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true));
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return __builtin_amdgcn_readlane(v, 63);
+}
 __device__ inline uint32_t wave_sum(uint32_t v)
 {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
+    return wave_reduce(v, [](uint32_t a, uint32_t b) { return a + b; });
+}
+__device__ inline uint32_t wave_max(uint32_t v)
+{
+    return wave_reduce(v, [](uint32_t a, uint32_t b) { return max(a, b); });
+}
+__device__ inline float wave_fsum(float v)
+{
+    return __uint_as_float(wave_reduce(__float_as_uint(v), [](uint32_t a, uint32_t b) {
+        return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+    }));
 }
 
 // x of lane (lane ^ D), for the compare-exchange steps below
@@ -297,39 +316,21 @@ __device__ inline bool entropy_says_raw(const uint32_t* fv, uint32_t tot, uint32
 #pragma unroll
     for (int r = 0; r < 4; r++)
         if (fv[r]) h += float(fv[r]) * (lt - __log2f(float(fv[r])));
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) h += __shfl_xor(h, o, 64);
+    h = wave_fsum(h);
     const float lb = h * (1.0f - 1e-4f) - 1e-4f * float(tot) - 1.0f;
     const uint64_t words_lb = lb > 0.0f ? uint64_t(lb / 32.0f) : 0u;   // floor: a lower bound too
     return uint64_t(head) + 4 * words_lb >= raw;
 }
 
-// Canonical codes (RFC 1951 §3.2.2) of the lengths len[256], by one wave:
-// codes[s] = code | length << 16 (0 for absent symbols).  The first code of
-// each length follows from the counts of the shorter ones; within a length
-// the codes follow the symbol order.
-__device__ __attribute__((always_inline)) void canonical_codes(const uint8_t* len, uint32_t L, CodeWord* codes)
+// One workgroup per chunk over a two-dimensional grid (chunk_grid).  A loop
+// over chunks in the kernel has the compiler compute every address that does
+// not depend on the chunk before it and keep it in scratch memory: 27 spilled
+// registers of the analysis, 1 GB written per 5 GB of input.
+__device__ inline uint32_t chunk_of_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+inline dim3 chunk_grid(uint32_t chunks)
 {
-    const int lane = threadIdx.x & 63;
-    uint32_t l4[4];
-#pragma unroll
-    for (int r = 0; r < 4; r++) l4[r] = len[lane + 64 * r];
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    uint32_t code4[4] = {0, 0, 0, 0};
-    uint32_t first = 0, prev = 0;
-    for (uint32_t l = 1; l <= L; l++) {
-        first = (first + prev) << 1;
-        uint32_t run = 0;
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const uint64_t msk = __ballot(l4[r] == l);
-            if (l4[r] == l) code4[r] = first + run + __popcll(msk & lt_mask);
-            run += __popcll(msk);
-        }
-        prev = run;
-    }
-#pragma unroll
-    for (int r = 0; r < 4; r++) codes[lane + 64 * r] = l4[r] ? (code4[r] | (l4[r] << 16)) : 0u;
+    const uint32_t x = min(max(chunks, 1u), 1u << 16);
+    return dim3(x, (max(chunks, 1u) + x - 1) / x);
 }
 
 // The tensor holding chunk g: the last i with prefix[i] <= g, by a whole wave
@@ -375,6 +376,56 @@ __device__ inline void loadNB(const uint8_t* p, uint32_t* w)
             w[4 * i + 3] = v.w;
         }
     }
+}
+
+// A chunk's bytes as a buffer resource: a load's address is a lane offset
+// and a scalar offset (no 64-bit address per load in vector registers), and
+// reads past the end give zero.
+__device__ inline __amdgpu_buffer_rsrc_t in_rsrc(const uint8_t* p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p), (short)0, int(bytes), 0x00020000);
+}
+template <int NB>
+__device__ __attribute__((always_inline)) inline void buf_in(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
+                                                             uint32_t* w)
+{
+    if constexpr (NB == 2) w[0] = __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
+    else if constexpr (NB == 4) w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0);
+    else if constexpr (NB == 8) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+        w[0] = v.x;
+        w[1] = v.y;
+    } else {
+#pragma unroll
+        for (int i = 0; i < NB / 16; i++) {
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff + 16 * i, soff, 0);
+            w[4 * i] = v.x;
+            w[4 * i + 1] = v.y;
+            w[4 * i + 2] = v.z;
+            w[4 * i + 3] = v.w;
+        }
+    }
+}
+// The same of the chunk XORed with its base, exponent extracted when xf.
+struct ChunkIn {
+    __amdgpu_buffer_rsrc_t src, base;
+    bool delta, xf;
+};
+template <int B, int NB>
+__device__ __attribute__((always_inline)) inline void chunk_in(const ChunkIn& in, uint32_t voff, uint32_t soff,
+                                                               uint32_t* w)
+{
+    constexpr int NW = NB >= 4 ? NB / 4 : 1;
+    buf_in<NB>(in.src, voff, soff, w);
+    if (in.delta) {
+        uint32_t y[NW];
+        buf_in<NB>(in.base, voff, soff, y);
+#pragma unroll
+        for (int x = 0; x < NW; x++) w[x] ^= y[x];
+    }
+    if (in.xf)
+#pragma unroll
+        for (int x = 0; x < NW; x++) w[x] = exp_fwd<B>(w[x]);
 }
 
 // The words of group q of a chunk (g elements, XORed with the base, then with
@@ -452,7 +503,7 @@ __device__ inline bool marked(const uint32_t* wd, int k, uint32_t gcnt, uint32_t
 // streams in zc, summed over the wave.  Every value other than z lies in a
 // marked group, so the histogram over the marked groups is the main one with
 // this many taken off the count of z.
-template <int B, int G>
+template <int B, int G, int NT>
 __device__ __attribute__((always_inline)) void zg_unmarked(const uint8_t* src, const uint8_t* base, uint32_t zc,
                                                            const uint32_t* z, uint32_t m, uint32_t* un, bool xf)
 {
@@ -462,14 +513,14 @@ __device__ __attribute__((always_inline)) void zg_unmarked(const uint8_t* src, c
     const uint32_t Gtot = (m + G - 1) / G;
 #pragma unroll
     for (int k = 0; k < B; k++) un[k] = 0;
-    for (uint32_t q0 = threadIdx.x; q0 < Gtot; q0 += CB * kAnThreads) {
+    for (uint32_t q0 = threadIdx.x; q0 < Gtot; q0 += CB * NT) {
         uint32_t wds[CB][NW];
 #pragma unroll
         for (uint32_t u = 0; u < CB; u++)
-            if (q0 + u * kAnThreads < Gtot) group_words<B, G>(src, base, q0 + u * kAnThreads, m, wds[u], xf);
+            if (q0 + u * NT < Gtot) group_words<B, G>(src, base, q0 + u * NT, m, wds[u], xf);
 #pragma unroll
         for (uint32_t u = 0; u < CB; u++) {
-            const uint32_t q = q0 + u * kAnThreads;
+            const uint32_t q = q0 + u * NT;
             if (q >= Gtot) continue;
             const uint32_t gcnt = min(uint32_t(G), m - q * G);
 #pragma unroll
@@ -511,7 +562,7 @@ __device__ inline uint32_t gather_stream(const uint32_t* wd, int k)
 // groups holding another value.  out[v][k] = bits << 5 | bits of the last
 // pair coded here (at most 4096 * 11 bits in all, 22 in a pair).
 template <int B, int G>
-__device__ __attribute__((always_inline)) void count_steps(const uint8_t* src, const uint8_t* base, uint32_t hc,
+__device__ __attribute__((always_inline)) void count_steps(const ChunkIn& in, const uint8_t* src, const uint8_t* base, uint32_t hc,
                                                            uint32_t zgc, const uint8_t (*lens)[256],
                                                            const uint8_t (*lens2)[256], const uint32_t* z, uint32_t j,
                                                            uint32_t s0, uint32_t s1, uint32_t W, uint32_t m,
@@ -527,46 +578,47 @@ __device__ __attribute__((always_inline)) void count_steps(const uint8_t* src, c
     uint32_t bits[2][B], last[2][B];
 #pragma unroll
     for (int k = 0; k < B; k++) bits[0][k] = bits[1][k] = last[0][k] = last[1][k] = 0;
-    if (zgc == 0 && s1 > s0 && 64 * j + 64 <= W && 64 * j + 63 + (s1 - 1) * W < Gfull) {
+    if (zgc == 0 && s1 > s0 && min(W, 64 * j + 64) - 1 + (s1 - 1) * W < Gfull) {
         // HUF alone and a full group for every lane at every step: no
         // conditions, so the table reads of several groups are in flight
-        constexpr uint32_t FB = NB >= 32 ? 1 : (NB >= 16 ? 2 : (NB >= 8 ? 4 : 8));
-        uint32_t lw[NW];
-        auto add = [&](auto nb_const, uint32_t jj) __attribute__((always_inline)) {
-            constexpr uint32_t N = decltype(nb_const)::value;
-            uint32_t wds[N][NW];
+        constexpr uint32_t FB = NB >= 32 ? 2 : (NB >= 16 ? 4 : 8);
+        if (w < W) {
+            uint32_t lw[NW];
+            auto add = [&](auto n_const, uint32_t jj) __attribute__((always_inline)) {
+                constexpr uint32_t N = decltype(n_const)::value;
+                uint32_t wds[N][NW];
 #pragma unroll
-            for (uint32_t u = 0; u < N; u++) {
-                const uint64_t o = uint64_t(w + (jj + u) * W) * NB;
-                loadNB<NB>(src + o, wds[u]);
-                if (base) {
-                    uint32_t bw[NW];
-                    loadNB<NB>(base + o, bw);
+                for (uint32_t u = 0; u < N; u++) chunk_in<B, NB>(in, w * NB, (jj + u) * W * NB, wds[u]);
 #pragma unroll
-                    for (int x = 0; x < NW; x++) wds[u][x] ^= bw[x];
+                for (int k = 0; k < B; k++) {
+                    if (!((hc >> k) & 1)) continue;
+                    // 8 reads in flight (left alone, the compiler waits for
+                    // every two)
+                    constexpr uint32_t U = N * G > 8 ? 8 / G : N;
+#pragma unroll
+                    for (uint32_t u0 = 0; u0 < N; u0 += U) {
+                        uint32_t e[U * G];
+#pragma unroll
+                        for (uint32_t i = 0; i < U * G; i++)
+                            e[i] = lens[k][sym_of<B>(wds[u0 + i / G], k, int(i % G))];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (uint32_t i = 0; i < U * G; i++) bits[0][k] += e[i];
+                    }
                 }
-                if (xf)
 #pragma unroll
-                    for (int x = 0; x < NW; x++) wds[u][x] = exp_fwd<B>(wds[u][x]);
-            }
+                for (int x = 0; x < NW; x++) lw[x] = wds[N - 1][x];
+            };
+            uint32_t jj = s0;
+            for (; (s1 - jj) % FB; jj++) add(std::integral_constant<uint32_t, 1>{}, jj);
+            for (; jj < s1; jj += FB) add(std::integral_constant<uint32_t, FB>{}, jj);
 #pragma unroll
-            for (int k = 0; k < B; k++) {
-                if (!((hc >> k) & 1)) continue;
-#pragma unroll
-                for (uint32_t u = 0; u < N; u++)
-#pragma unroll
-                    for (int i = 0; i < G; i++) bits[0][k] += lens[k][sym_of<B>(wds[u], k, i)];
-            }
-#pragma unroll
-            for (int x = 0; x < NW; x++) lw[x] = wds[N - 1][x];
-        };
-        uint32_t jj = s0;
-        for (; (s1 - jj) % FB; jj++) add(std::integral_constant<uint32_t, 1>{}, jj);
-        for (; jj < s1; jj += FB) add(std::integral_constant<uint32_t, FB>{}, jj);
+            for (int k = 0; k < B; k++)
+                if ((hc >> k) & 1)
+                    last[0][k] = uint32_t(lens[k][sym_of<B>(lw, k, G - 2)]) + lens[k][sym_of<B>(lw, k, G - 1)];
+        }
 #pragma unroll
         for (int k = 0; k < B; k++) {
-            if ((hc >> k) & 1)
-                last[0][k] = uint32_t(lens[k][sym_of<B>(lw, k, G - 2)]) + lens[k][sym_of<B>(lw, k, G - 1)];
             out[0][k] = (bits[0][k] << 5) | last[0][k];
             out[1][k] = 0;
         }
@@ -613,8 +665,8 @@ __device__ __attribute__((always_inline)) void count_steps(const uint8_t* src, c
 
 template <int B>
 struct AnalyzeTail {
-    uint8_t lens[B][256];    // HUF code lengths
-    uint8_t lens2[B][256];   // ZG code lengths
+    alignas(4) uint8_t lens[B][256];    // HUF code lengths
+    alignas(4) uint8_t lens2[B][256];   // ZG code lengths
     uint32_t z[4];           // ZG fill value: the most frequent byte (smallest on ties)
     uint32_t zn[4];          // its count over the marked groups
     uint32_t open;           // bit k: mode still to be decided (neither forced RAW nor RLE)
@@ -648,25 +700,26 @@ struct AnalyzeTail {
 //      code table.
 
 // Shared memory of the analysis of one chunk.
-template <int BB>
+template <int BB, int NT>
 struct AnalyzeShared {
-    AnalyzeLds<BB> S;
+    AnalyzeLds<BB, NT> S;
     uint32_t hist[BB][256];
     uint32_t lgw[2][BB][64];        // words per lane group: HUF, ZG
     AnalyzeTail<BB> A;
-    uint32_t zsum[kAnWaves][4];     // symbols in unmarked groups, per wave
+    uint32_t zsum[NT / 64][4];      // symbols in unmarked groups, per wave
 };
 
 // The analysis of chunk gc by one workgroup (steps 1-5 above); a chunk that
 // the probing phase leaves to the other launch is passed over.
-template <int BB>
+template <int BB, int NT>
 __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const EncDesc* __restrict__ descs,
                                                              int n_desc, const uint32_t* __restrict__ chunk_prefix,
                                                              const EncParams& p, int phase,
-                                                             EncEntry* __restrict__ entries, CodeWord* __restrict__ codes,
-                                                             uint32_t* __restrict__ nwords, AnalyzeShared<BB>& sh)
+                                                             EncEntry* __restrict__ entries, uint8_t* __restrict__ lens,
+                                                             uint32_t* __restrict__ nwords, AnalyzeShared<BB, NT>& sh)
 {
-    AnalyzeLds<BB>& S = sh.S;
+    constexpr int kWavesA = NT / 64;
+    AnalyzeLds<BB, NT>& S = sh.S;
     auto& hist = sh.hist;
     AnalyzeTail<BB>& A = sh.A;
     const int t = threadIdx.x, lane = t & 63;
@@ -702,9 +755,9 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
         return;
     }
     constexpr uint32_t kCopyWords = sizeof(S.copies) / 4;
-    for (uint32_t i = t; i < kCopyWords / 4; i += kAnThreads)
+    for (uint32_t i = t; i < kCopyWords / 4; i += NT)
         reinterpret_cast<uint4*>(&S.copies[0][0][0])[i] = make_uint4(0, 0, 0, 0);
-    for (uint32_t i = t; i < B * 256; i += kAnThreads) (&hist[0][0])[i] = 0;
+    for (uint32_t i = t; i < B * 256; i += NT) (&hist[0][0])[i] = 0;
     if (t == 0) A.open = A.build[0] = A.build[1] = A.build[2] = A.hc = A.zc = A.zgc = A.fin = A.coded = A.specok = A.amb = 0;
     if (t < 8) (&A.words[0][0])[t] = 0;
     if (t < 4) A.pol[t] = ((live >> t) & 1) ? int(p.policy[t]) : ZIPNN_RAW;
@@ -715,18 +768,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
     const bool xf = (p.flags & kFlagExp) != 0;
     // 16-byte vectors; the element boundary is aligned since 16 % B == 0
     const uint32_t nvec = nbytes / 16;
-    auto load = [&](uint32_t v, uint32_t* x) __attribute__((always_inline)) {
-        loadNB<16>(src + uint64_t(v) * 16, x);
-        if (base) {
-            uint32_t y[4];
-            loadNB<16>(base + uint64_t(v) * 16, y);
-#pragma unroll
-            for (int i = 0; i < 4; i++) x[i] ^= y[i];
-        }
-        if (xf)
-#pragma unroll
-            for (int i = 0; i < 4; i++) x[i] = exp_fwd<B>(x[i]);
-    };
+    const ChunkIn in{in_rsrc(src, nbytes), in_rsrc(base ? base : src, nbytes), base != nullptr, xf};
     // this lane's copy of the counters: B = 1 counts in 32 bits, else byte
     // groups 2a and 2a+1 in the halves of array a
     const uint32_t copy = uint32_t(lane) % kCopies;
@@ -757,90 +799,106 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
         }
     }
     spec = __builtin_amdgcn_readfirstlane(spec);
-    uint32_t unz[B];   // zero bytes in unmarked groups
+    uint32_t ung[B];   // unmarked groups (of zeros)
 #pragma unroll
-    for (uint32_t k = 0; k < B; k++) unz[k] = 0;
+    for (uint32_t k = 0; k < B; k++) ung[k] = 0;
     // LV: every group is live (no per-byte test); SP: count the groups of
-    // zeros of the streams in `spec`
-    auto count = [&](auto lv_const, auto sp_const, uint32_t v_begin, uint32_t v_end) {
+    // zeros of the streams in `spec`; DL: there is an XOR base
+    auto count = [&](auto lv_const, auto sp_const, auto dl_const, uint32_t v_begin, uint32_t v_end) {
         constexpr bool LV = decltype(lv_const)::value;
         constexpr bool SP = decltype(sp_const)::value;
-        constexpr uint32_t HB = 4;   // vectors in flight per lane (with the base: 8 loads)
-        for (uint32_t v0 = v_begin + t; v0 < v_end; v0 += HB * kAnThreads) {
-            uint32_t xs[HB][4];
+        ChunkIn cin = in;
+        cin.delta = decltype(dl_const)::value;
+        // vectors in flight per lane (loading the next batch ahead of this
+        // one's atomics took registers and measured 5% slower)
+        constexpr uint32_t HB = decltype(dl_const)::value ? 2 : 4;
+        auto load = [&](uint32_t v0, uint32_t (*xs)[4]) __attribute__((always_inline)) {
 #pragma unroll
-            for (uint32_t i = 0; i < HB; i++)
-                if (v0 + i * kAnThreads < v_end) load(v0 + i * kAnThreads, xs[i]);
+            for (uint32_t i = 0; i < HB; i++) chunk_in<B, 16>(cin, uint32_t(t) * 16, (v0 + i * NT) * 16, xs[i]);
+        };
+        auto one = [&](const uint32_t* x) __attribute__((always_inline)) {
 #pragma unroll
-            for (uint32_t i = 0; i < HB; i++) {
-                if (v0 + i * kAnThreads >= v_end) continue;
-                const uint32_t* x = xs[i];
+            for (int jb = 0; jb < 16; jb++) {
+                const uint32_t byte = (x[jb >> 2] >> (8 * (jb & 3))) & 0xFFu;
+                const int k = int(B) - 1 - (jb % int(B));   // byte jb%B of a word -> stream B-1-jb%B
+                if (!LV && !((live >> k) & 1)) continue;
+                add(uint32_t(k), byte);
+            }
+            if constexpr (SP) {
 #pragma unroll
-                for (int jb = 0; jb < 16; jb++) {
-                    const uint32_t byte = (x[jb >> 2] >> (8 * (jb & 3))) & 0xFFu;
-                    const int k = int(B) - 1 - (jb % int(B));   // byte jb%B of a word -> stream B-1-jb%B
-                    if (!LV && !((live >> k) & 1)) continue;
-                    add(uint32_t(k), byte);
-                }
-                if constexpr (SP) {
+                for (int k = 0; k < int(B); k++) {
+                    if (!((spec >> k) & 1)) continue;
+                    // the stream's bytes of the four words
+                    constexpr uint32_t kAll = B == 1 ? 0xFFFFFFFFu : (B == 2 ? 0x00FF00FFu : 0x000000FFu);
+                    const uint32_t km = B == 1 ? kAll : kAll << (8 * (int(B) - 1 - k));
+                    uint32_t un = 0;   // groups of zeros in this vector
+                    if (gB == 8) {
+                        un += uint32_t(((x[0] | x[1]) & km) == 0) + uint32_t(((x[2] | x[3]) & km) == 0);
+                    } else if (gB == 4) {
 #pragma unroll
-                    for (int k = 0; k < int(B); k++) {
-                        if (!((spec >> k) & 1)) continue;
-                        // the stream's bytes of the four words
-                        constexpr uint32_t kAll = B == 1 ? 0xFFFFFFFFu : (B == 2 ? 0x00FF00FFu : 0x000000FFu);
-                        const uint32_t km = B == 1 ? kAll : kAll << (8 * (int(B) - 1 - k));
-                        uint32_t un = 0;   // groups of zeros in this vector
-                        if (gB == 2) {
+                        for (int y = 0; y < 4; y++) un += uint32_t((x[y] & km) == 0);
+                    } else if (gB == 2) {
 #pragma unroll
-                            for (int y = 0; y < 4; y++)
-                                un += uint32_t((x[y] & km & 0xFFFFu) == 0) + uint32_t((x[y] & km & 0xFFFF0000u) == 0);
-                        } else if (gB == 4) {
-#pragma unroll
-                            for (int y = 0; y < 4; y++) un += uint32_t((x[y] & km) == 0);
-                        } else if (gB == 8) {
-                            un += uint32_t(((x[0] | x[1]) & km) == 0) + uint32_t(((x[2] | x[3]) & km) == 0);
-                        } else {
-                            un += uint32_t(((x[0] | x[1] | x[2] | x[3]) & km) == 0);
-                        }
-                        unz[k] += un * p.g;
+                        for (int y = 0; y < 4; y++)
+                            un += uint32_t((x[y] & km & 0xFFFFu) == 0) + uint32_t((x[y] & km & 0xFFFF0000u) == 0);
+                    } else {
+                        un += uint32_t(((x[0] | x[1] | x[2] | x[3]) & km) == 0);
                     }
+                    ung[k] += un;
                 }
             }
+        };
+        auto batch = [&](uint32_t v0, const uint32_t (*xs)[4]) __attribute__((always_inline)) {
+            if (v0 + HB * NT <= v_end) {
+#pragma unroll
+                for (uint32_t i = 0; i < HB; i++) one(xs[i]);
+            } else {
+#pragma unroll
+                for (uint32_t i = 0; i < HB; i++)
+                    if (v0 + i * NT + t < v_end) one(xs[i]);
+            }
+        };
+        uint32_t xs[1][HB][4];
+        for (uint32_t v0 = v_begin; v0 < v_end; v0 += HB * NT) {
+            load(v0, xs[0]);
+            batch(v0, xs[0]);
         }
     };
     for (uint32_t part = 0;; part += kPartVec) {
         const uint32_t v_end = min(nvec, part + kPartVec);
         using T = std::integral_constant<bool, true>;
         using F = std::integral_constant<bool, false>;
-        if (spec) count(F{}, T{}, part, v_end);
-        else if (live != (1u << B) - 1) count(F{}, F{}, part, v_end);
-        else count(T{}, F{}, part, v_end);
+        if (live != (1u << B) - 1) in.delta ? count(F{}, T{}, T{}, part, v_end) : count(F{}, T{}, F{}, part, v_end);
+        else if (spec) in.delta ? count(T{}, T{}, T{}, part, v_end) : count(T{}, T{}, F{}, part, v_end);
+        else in.delta ? count(T{}, F{}, T{}, part, v_end) : count(T{}, F{}, F{}, part, v_end);
         const bool done = v_end == nvec;
         if (done)   // the elements after the last whole vector
-            for (uint32_t e = nvec * 16 / B + t; e < m; e += kAnThreads) {
+            for (uint32_t e = nvec * 16 / B + t; e < m; e += NT) {
                 const uint32_t v = element_word<B>(src, base, e, xf);
                 for (uint32_t b = 0; b < B; b++)
                     if ((live >> (B - 1 - b)) & 1) add(B - 1 - b, (v >> (8 * b)) & 0xFFu);
             }
         __syncthreads();
-        // the copies of a bin: four threads sum eight counters each
-        const uint32_t s = uint32_t(t) >> 2, q = uint32_t(t) & 3;
-        static_assert(kAnThreads == 1024 && kCopies == 32, "four threads per bin");
+        // the copies of a bin: kPer neighbouring threads sum kEach counters each
+        constexpr uint32_t kPer = NT / 256, kEach = kCopies / kPer;
+        static_assert(kPer >= 1 && kPer <= 4 && kEach % 4 == 0, "threads per bin");
+        const uint32_t s = uint32_t(t) / kPer, q = uint32_t(t) % kPer;
         for (uint32_t a = 0; a < (B == 4 ? 2u : 1u); a++) {
-            uint4* cp = reinterpret_cast<uint4*>(&S.copies[a][s][8 * q]);
-            const uint4 x = cp[0], y = cp[1];
-            if (!done) cp[0] = cp[1] = make_uint4(0, 0, 0, 0);
-            const uint32_t w8[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+            uint4* cp = reinterpret_cast<uint4*>(&S.copies[a][s][kEach * q]);
             uint32_t lo = 0, hi = 0;
 #pragma unroll
-            for (int i = 0; i < 8; i++) {
-                lo += B == 1 ? w8[i] : (w8[i] & 0xFFFFu);
-                hi += w8[i] >> 16;
+            for (uint32_t i = 0; i < kEach / 4; i++) {
+                const uint4 x = cp[i];
+                if (!done) cp[i] = make_uint4(0, 0, 0, 0);
+                if (B == 1) {
+                    lo += x.x + x.y + x.z + x.w;
+                } else {
+                    lo += (x.x & 0xFFFFu) + (x.y & 0xFFFFu) + (x.z & 0xFFFFu) + (x.w & 0xFFFFu);
+                    hi += (x.x >> 16) + (x.y >> 16) + (x.z >> 16) + (x.w >> 16);
+                }
             }
-            lo += __shfl_xor(lo, 1, 64);
-            lo += __shfl_xor(lo, 2, 64);
-            hi += __shfl_xor(hi, 1, 64);
-            hi += __shfl_xor(hi, 2, 64);
+            if (kPer >= 2) lo += lane_xor<1>(lo), hi += lane_xor<1>(hi);
+            if (kPer >= 4) lo += lane_xor<2>(lo), hi += lane_xor<2>(hi);
             if (q == 0) {
                 hist[2 * a][s] += lo;
                 if (B > 1) hist[2 * a + 1][s] += hi;
@@ -852,12 +910,13 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
     if (spec) {
 #pragma unroll
         for (uint32_t k = 0; k < B; k++) {
-            const uint32_t un = wave_sum(unz[k]);
+            const uint32_t un = wave_sum(ung[k]) * p.g;
             if (lane == 0) sh.zsum[wv][k] = un;
         }
     }
     // 2. classification, wave k for group k
     if (uint32_t(wv) < B) {
+        __builtin_amdgcn_s_setprio(3);
         const int k = wv;
         const int policy = A.pol[k];
         uint32_t fv[4], nd = 0, best = 0;
@@ -868,8 +927,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
             // most frequent value, smallest on ties: key f << 8 | (255 - s)
             best = max(best, (fv[r] << 8) | uint32_t(255 - (lane + 64 * r)));
         }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) best = max(best, uint32_t(__shfl_xor(best, o, 64)));
+        best = wave_max(best);
         const uint32_t arg = 255 - (best & 0xFFu);
         if (policy == ZIPNN_RAW || nd <= 1) {
             if (lane == 0) {
@@ -902,9 +960,9 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
         if (need) {
             uint32_t un[B];
             switch (p.g) {
-            case 2: zg_unmarked<BB, 2>(src, base, need, A.z, m, un, xf); break;
-            case 4: zg_unmarked<BB, 4>(src, base, need, A.z, m, un, xf); break;
-            default: zg_unmarked<BB, 8>(src, base, need, A.z, m, un, xf); break;
+            case 2: zg_unmarked<BB, 2, NT>(src, base, need, A.z, m, un, xf); break;
+            case 4: zg_unmarked<BB, 4, NT>(src, base, need, A.z, m, un, xf); break;
+            default: zg_unmarked<BB, 8, NT>(src, base, need, A.z, m, un, xf); break;
             }
 #pragma unroll
             for (uint32_t k = 0; k < B; k++)
@@ -915,7 +973,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
             const int k = wv;
             const uint32_t z = A.z[k];
             uint32_t zn = hist[k][z];
-            for (int i = 0; i < kAnWaves; i++) zn -= sh.zsum[i][k];
+            for (int i = 0; i < kWavesA; i++) zn -= sh.zsum[i][k];
             uint32_t fv[4], tot = 0, nd = 0;
 #pragma unroll
             for (int r = 0; r < 4; r++) {
@@ -938,6 +996,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
     if (uint32_t(wv) < 3 * B) {
         const int v = wv / int(B), k = wv % int(B);
         if ((A.build[v] >> k) & 1) {
+            __builtin_amdgcn_s_setprio(3);
             uint32_t fv[4];
 #pragma unroll
             for (int r = 0; r < 4; r++) {
@@ -954,6 +1013,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
             }
         }
     }
+    __builtin_amdgcn_s_setprio(0);
     __syncthreads();
     // AUTO with both candidates: a candidate that loses even at its best
     // (head + coded bits) against the other at its worst (plus two words
@@ -990,18 +1050,18 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
     if ((hc | zgc) && exact) {
         const uint32_t Gtot = (m + p.g - 1) / p.g;
         const uint32_t steps = (Gtot - 1) / W + 1;   // of lane 0 of the first lane group, the most
-        const uint32_t nseg = NG < uint32_t(kAnWaves) ? uint32_t(kAnWaves) / NG : 1u;
+        const uint32_t nseg = NG < uint32_t(kWavesA) ? uint32_t(kWavesA) / NG : 1u;
         const uint32_t per = (steps + nseg - 1) / nseg;
         auto steps_of = [&](uint32_t j, uint32_t s0, uint32_t s1, uint32_t (*out)[BB]) __attribute__((always_inline)) {
             switch (p.g) {
-            case 2: count_steps<BB, 2>(src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
-            case 4: count_steps<BB, 4>(src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
-            default: count_steps<BB, 8>(src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
+            case 2: count_steps<BB, 2>(in, src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
+            case 4: count_steps<BB, 4>(in, src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
+            default: count_steps<BB, 8>(in, src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
             }
         };
         // wave wv: range wv / NG of lane group wv % NG, or (nseg = 1) all of
-        // lane groups wv, wv + kAnWaves, ...
-        for (uint32_t j0 = 0; j0 < NG; j0 += kAnWaves) {
+        // lane groups wv, wv + kWavesA, ...
+        for (uint32_t j0 = 0; j0 < NG; j0 += kWavesA) {
             const uint32_t sg = nseg > 1 ? uint32_t(wv) / NG : 0u, j = nseg > 1 ? uint32_t(wv) % NG : j0 + wv;
             uint32_t out[2][BB];
             const bool mine = nseg > 1 ? sg < nseg : j < NG;
@@ -1028,6 +1088,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
                         bits = out[v][k] >> 5;
                         last = out[v][k] & 31;
                     } else {
+#pragma unroll 4
                         for (uint32_t g = 0; g < nseg; g++) {
                             const uint32_t x = S.seg[v][k][64 * (g * NG + jw) + lane];
                             bits += x >> 5;
@@ -1080,24 +1141,29 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
     if (uint32_t(wv) < B && ((A.coded >> wv) & 1)) {
         const uint64_t ei = uint64_t(gc) * B + wv;
         const int v = (A.fin >> wv) & 1;
-        canonical_codes(v ? A.lens2[wv] : A.lens[wv], p.L, codes + ei * 256);
+        reinterpret_cast<uint32_t*>(lens + ei * 256)[lane] =
+            reinterpret_cast<const uint32_t*>(v ? A.lens2[wv] : A.lens[wv])[lane];
         if (!staged && uint32_t(lane) < NG) nwords[ei * 64 + lane] = sh.lgw[v][wv][lane];
     }
     __syncthreads();
 }
 
-// Two workgroups of 1024 threads per CU, a few spills outside the counting
-// loop.  Against one wave per code and four waves per chunk (8 MiB of BF16:
-// 146 us; nine layers and the embedding of an 8B checkpoint, 5 GB: 3450 us;
-// 256 MiB of FP32: 240 us) this takes 30, 2360 and 170 us.
-template <int BB>
-__global__ __launch_bounds__(kAnThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_analyze(
+// What bounds it: on full launches the two reads of every chunk (the counting
+// and the size pass; the second one misses L2, and the last-level cache serves
+// it at 7.5 TB/s against HBM's 6.2).  5 GB of an 8B checkpoint (BF16, 256 KiB
+// chunks) take 1.43 ms, 7.0 TB/s of both reads; four waves per chunk with
+// one wave building each code in LDS took 3.45 ms.  On small launches, the
+// chain count - code - sizes of one chunk: an 8 KiB tensor 98 -> 16 us, 32
+// chunks 146 -> 25 us.  The waves that classify and build codes run at raised
+// priority: the others wait for them.
+template <int BB, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_analyze(
     const EncDesc* __restrict__ descs, int n_desc, const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
-    EncParams p, int phase, EncEntry* __restrict__ entries, CodeWord* __restrict__ codes, uint32_t* __restrict__ nwords)
+    EncParams p, int phase, EncEntry* __restrict__ entries, uint8_t* __restrict__ lens, uint32_t* __restrict__ nwords)
 {
-    __shared__ AnalyzeShared<BB> sh;
-    for (uint32_t gc = blockIdx.x; gc < total_chunks; gc += gridDim.x)
-        analyze_chunk<BB>(gc, descs, n_desc, chunk_prefix, p, phase, entries, codes, nwords, sh);
+    __shared__ AnalyzeShared<BB, NT> sh;
+    const uint32_t gc = chunk_of_block();
+    if (gc < total_chunks) analyze_chunk<BB, NT>(gc, descs, n_desc, chunk_prefix, p, phase, entries, lens, nwords, sh);
 }
 
 // One workgroup per tensor: offsets of its entries (128-byte aligned, in
@@ -1234,6 +1300,7 @@ struct PackLds {
     uint32_t bytes[4];
     uint32_t z[4];              // ZG fill value
     uint32_t wpre[4][65];       // lane-group word prefix per stream
+    alignas(16) uint32_t cnt[4][kMaxL + 1][kWaves];   // symbols of each code length, per wave
 };
 
 constexpr uint32_t kLenShift = 27;              // code length's place in a packer code entry
@@ -1564,13 +1631,18 @@ template <int BB, int GG>
 __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const EncDesc* __restrict__ descs, int n_desc,
                                                           const uint32_t* __restrict__ chunk_prefix, const EncParams& p,
                                                           const EncEntry* __restrict__ entries,
-                                                          const CodeWord* __restrict__ codes,
+                                                          const uint8_t* __restrict__ lens,
                                                           const uint64_t* __restrict__ offsets,
                                                           const uint64_t* __restrict__ totals,
                                                           uint32_t* __restrict__ nwords, PackLds& P)
 {
-    const int t = threadIdx.x, wv = t >> 6;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
     constexpr uint32_t B = BB;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint32_t len[B], rank[B];   // this thread's symbol: code length, place among its length in the wave
+#pragma unroll
+    for (uint32_t k = 0; k < B; k++) len[k] = rank[k] = 0;
     // staged: the payloads go to the staging slots (their places in the
     // container are not known yet) and the word counts come out
     const bool staged = p.stage != nullptr;
@@ -1585,6 +1657,7 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
     const uint32_t NG = (W + 63) / 64;
     const uint32_t head = huf_head(W);
     const uint64_t payload_base = payload_base_of(d.n_chunks, B);
+#pragma unroll
     for (uint32_t k = 0; k < B; k++) {
         const uint64_t ei = uint64_t(gc) * B + k;
         const EncEntry en = entries[ei];
@@ -1606,9 +1679,13 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
         }
         if (t == 0) P.z[k] = en.rle;
         if (en.mode == kModeHuf || en.mode == kModeZg) {
-            const uint32_t cw = codes[ei * 256 + t];
-            const uint32_t l = cw >> 16;
-            P.rcode[k][t] = l ? ((__brev(cw & 0xFFFFu) >> (32 - l)) | (l << kLenShift)) : 0u;
+            len[k] = lens[ei * 256 + t];
+            // symbols of each length in this wave; rank: equal lengths below
+            for (uint32_t l = 1; l <= p.L; l++) {
+                const uint64_t msk = __ballot(len[k] == l);
+                if (len[k] == l) rank[k] = __popcll(msk & lt_mask);
+                if (lane == 0) P.cnt[k][l][wv] = uint32_t(__popcll(msk));
+            }
             if (t < 64 && !staged) {
                 const uint32_t nw = uint32_t(t) < NG ? nwords[ei * 64 + t] : 0u;
                 uint32_t inc = nw;
@@ -1621,6 +1698,23 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
                 if (t == 0) P.wpre[k][0] = 0;
             }
         }
+    }
+    __syncthreads();
+    // canonical codes (RFC 1951 §3.2.2): the first code of each length follows
+    // from the counts of the shorter ones; within a length the codes follow
+    // the symbol order
+#pragma unroll
+    for (uint32_t k = 0; k < B; k++) {
+        if (P.mode[k] != kModeHuf && P.mode[k] != kModeZg) continue;
+        uint32_t first = 0, prev = 0, code = 0;
+        for (uint32_t l = 1; l <= p.L; l++) {
+            const uint4 c4 = *reinterpret_cast<const uint4*>(P.cnt[k][l]);
+            first = (first + prev) << 1;
+            prev = c4.x + c4.y + c4.z + c4.w;
+            if (len[k] == l)
+                code = first + rank[k] + (wv > 0 ? c4.x : 0u) + (wv > 1 ? c4.y : 0u) + (wv > 2 ? c4.z : 0u);
+        }
+        P.rcode[k][t] = len[k] ? ((__brev(code) >> (32 - len[k])) | (len[k] << kLenShift)) : 0u;
     }
     __syncthreads();
     const uint8_t* src = d.src + e0 * B;
@@ -1677,14 +1771,15 @@ template <int BB, int GG, bool XB>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BB == 2 ? (XB ? 6 : 5) : 4, 8))) void k_pack(const EncDesc* __restrict__ descs, int n_desc,
                                                  const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
                                                  EncParams p, const EncEntry* __restrict__ entries,
-                                                 const CodeWord* __restrict__ codes,
+                                                 const uint8_t* __restrict__ lens,
                                                  const uint64_t* __restrict__ offsets,
                                                  const uint64_t* __restrict__ totals,
                                                  uint32_t* __restrict__ nwords)
 {
     __shared__ PackLds P;
-    for (uint32_t gc = blockIdx.x; gc < total_chunks; gc += gridDim.x)
-        pack_chunk<BB, GG>(gc, descs, n_desc, chunk_prefix, p, entries, codes, offsets, totals, nwords, P);
+    const uint32_t gc = chunk_of_block();
+    if (gc < total_chunks)
+        pack_chunk<BB, GG>(gc, descs, n_desc, chunk_prefix, p, entries, lens, offsets, totals, nwords, P);
 }
 
 // Staged packing, last step: for each chunk, its map entries, and for each
@@ -1696,7 +1791,7 @@ template <int BB, int GG>
 __global__ __launch_bounds__(kBlock) void k_compact(const EncDesc* __restrict__ descs, int n_desc,
                                                     const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
                                                     EncParams p, const EncEntry* __restrict__ entries,
-                                                    const CodeWord* __restrict__ codes,
+                                                    const uint8_t* __restrict__ lens,
                                                     const uint64_t* __restrict__ offsets,
                                                     const uint64_t* __restrict__ totals,
                                                     const uint32_t* __restrict__ nwords)
@@ -1704,10 +1799,12 @@ __global__ __launch_bounds__(kBlock) void k_compact(const EncDesc* __restrict__ 
     __shared__ uint32_t wpre[65];
     const int t = threadIdx.x;
     constexpr uint32_t B = BB;
-    for (uint32_t gc = blockIdx.x; gc < total_chunks; gc += gridDim.x) {
+    {
+        const uint32_t gc = chunk_of_block();
+        if (gc >= total_chunks) return;
         const int di = find_desc(chunk_prefix, n_desc, gc);
         const EncDesc d = descs[di];
-        if (totals[di] > d.dst_cap) continue;   // too small: the host reports it
+        if (totals[di] > d.dst_cap) return;   // too small: the host reports it
         const uint32_t c = gc - chunk_prefix[di];
         const uint32_t E = p.chunk / B;
         const uint32_t m = uint32_t(min(uint64_t(E), d.n - uint64_t(c) * E));
@@ -1737,7 +1834,7 @@ __global__ __launch_bounds__(kBlock) void k_compact(const EncDesc* __restrict__ 
                 const bool zg = en.mode == kModeZg;
                 const uint32_t bm = zg ? zg_bitmap(m, GG) : 0u;
                 if (t < 128)
-                    pay[t] = uint8_t((codes[ei * 256 + 2 * t] >> 16) | ((codes[ei * 256 + 2 * t + 1] >> 16) << 4));
+                    pay[t] = uint8_t(lens[ei * 256 + 2 * t] | (lens[ei * 256 + 2 * t + 1] << 4));
                 if (t < 64) {
                     const uint32_t nw = uint32_t(t) < NG ? nwords[ei * 64 + t] : 0u;
                     if (uint32_t(t) < NG) reinterpret_cast<uint32_t*>(pay + 128)[t] = nw;
@@ -1788,23 +1885,37 @@ hipError_t launch_fill_desc(const EncDesc& one, uint32_t total_chunks, EncDesc* 
 }
 
 hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_prefix, uint32_t total_chunks,
-                         const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, CodeWord* codes,
+                         const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, uint8_t* lens,
                          uint32_t* nwords, uint64_t* offsets, uint64_t* totals, uint64_t* arena_off, hipStream_t s)
 {
-    const uint32_t grid = min(max(total_chunks, 1u), 1u << 16);
+    const dim3 grid = chunk_grid(total_chunks);
     const bool xb = (p.flags & kFlagDelta) != 0;   // some tensor has an XOR base
     const bool staged = p.stage != nullptr;
     if (total_chunks) {
         // with probing, the probe chunks first: the others read their entries
         for (int phase = p.skip ? 0 : -1; phase <= (p.skip ? 1 : -1); phase++) {
             bool launched = true;
-#define ZIPNN_ANALYZE(B_)                                                                                         \
-    k_analyze<B_><<<grid, kAnThreads, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries, codes, \
-                                              nwords)
-            if (p.B == 1) ZIPNN_ANALYZE(1);
-            else if (p.B == 2) ZIPNN_ANALYZE(2);
-            else if (p.B == 4) ZIPNN_ANALYZE(4);
-            else launched = false;
+            // one chunk's latency counts until two workgroups of 1024 threads
+            // per CU are full; then 512 threads a chunk, four workgroups per
+            // CU, overlap more phases (5 GB of BF16: 3.27 against 3.39 ms a
+            // pass; 32 chunks: equal within 1%)
+            const bool many = total_chunks > 512;
+#define ZIPNN_ANALYZE(B_)                                                                                            \
+    if (many)                                                                                                        \
+        k_analyze<B_, 512><<<grid, 512, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries,    \
+                                                lens, nwords);                                                       \
+    else                                                                                                             \
+        k_analyze<B_, 1024><<<grid, 1024, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries,  \
+                                                  lens, nwords)
+            if (p.B == 1) {
+                ZIPNN_ANALYZE(1);
+            } else if (p.B == 2) {
+                ZIPNN_ANALYZE(2);
+            } else if (p.B == 4) {
+                // its counters leave LDS for two workgroups per CU
+                k_analyze<4, 1024><<<grid, 1024, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries,
+                                                         lens, nwords);
+            } else launched = false;
 #undef ZIPNN_ANALYZE
             if (!launched) return hipErrorInvalidValue;
             if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
@@ -1820,13 +1931,13 @@ hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_p
     if (!launched && p.B == B_ && p.g == G_) {                                                                      \
         if (compact)                                                                                                \
             k_compact<B_, G_><<<grid, kBlock, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, entries,   \
-                                                      codes, offsets, totals, nwords);                             \
+                                                      lens, offsets, totals, nwords);                             \
         else if (xb)   /* the XB instance exists for 2-byte words only */                                        \
             k_pack<B_, G_, B_ == 2><<<grid, kBlock, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p,       \
-                                                            entries, codes, offsets, totals, nwords);              \
+                                                            entries, lens, offsets, totals, nwords);              \
         else                                                                                                        \
             k_pack<B_, G_, false><<<grid, kBlock, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, entries,\
-                                                          codes, offsets, totals, nwords);                         \
+                                                          lens, offsets, totals, nwords);                         \
         launched = true;                                                                                            \
     }
         ZIPNN_PACK(1, 2) ZIPNN_PACK(1, 4) ZIPNN_PACK(1, 8)

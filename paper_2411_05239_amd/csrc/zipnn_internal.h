@@ -180,9 +180,6 @@ struct EncEntry {
     uint16_t pad;
 };
 
-// Encode-side code table entry: canonical code | length << 16.
-using CodeWord = uint32_t;
-
 struct EncParams {
     uint32_t dtype, B, chunk, S, g, L;
     uint32_t flags;        // kFlagExp; kFlagDelta when some tensor of the launch has an XOR base
@@ -290,7 +287,7 @@ __host__ __device__ inline int dec_class_index(const DecClass& k)
 // into `arena`: analyze -> place -> arena layout (dst of every descriptor,
 // headers, arena_off[n_desc+1]) -> pack (maps and payloads).
 hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_prefix, uint32_t total_chunks,
-                         const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, CodeWord* codes,
+                         const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, uint8_t* lens,
                          uint32_t* nwords, uint64_t* offsets, uint64_t* totals, uint64_t* arena_off, hipStream_t s);
 
 hipError_t launch_fill_desc(const EncDesc& one, uint32_t total_chunks, EncDesc* d_desc, uint32_t* d_prefix,
@@ -308,7 +305,7 @@ inline EncScratch enc_scratch_layout(size_t ne, size_t n, size_t stage_bytes = 0
     EncScratch L;
     L.entries = 0;
     L.codes = a256(L.entries + ne * sizeof(EncEntry));
-    L.offsets = a256(L.codes + ne * 256 * sizeof(CodeWord));
+    L.offsets = a256(L.codes + ne * 1024);
     L.nwords = a256(L.offsets + ne * sizeof(uint64_t));
     L.totals = a256(L.nwords + ne * 64 * sizeof(uint32_t));
     L.aoff = a256(L.totals + n * sizeof(uint64_t));
