@@ -379,8 +379,9 @@ __device__ inline void loadNB(const uint8_t* p, uint32_t* w)
 }
 
 // A chunk's bytes as a buffer resource: a load's address is a lane offset
-// and a scalar offset (no 64-bit address per load in vector registers), and
-// reads past the end give zero.
+// and a scalar offset (no 64-bit address per load in vector registers).
+// Reads whose lane offset is past the end give zero; the scalar offset is
+// not part of that check, so it is used only where every lane is in range.
 __device__ inline __amdgpu_buffer_rsrc_t in_rsrc(const uint8_t* p, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p), (short)0, int(bytes), 0x00020000);
@@ -812,10 +813,6 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
         // vectors in flight per lane (loading the next batch ahead of this
         // one's atomics took registers and measured 5% slower)
         constexpr uint32_t HB = decltype(dl_const)::value ? 2 : 4;
-        auto load = [&](uint32_t v0, uint32_t (*xs)[4]) __attribute__((always_inline)) {
-#pragma unroll
-            for (uint32_t i = 0; i < HB; i++) chunk_in<B, 16>(cin, uint32_t(t) * 16, (v0 + i * NT) * 16, xs[i]);
-        };
         auto one = [&](const uint32_t* x) __attribute__((always_inline)) {
 #pragma unroll
             for (int jb = 0; jb < 16; jb++) {
@@ -848,20 +845,13 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
                 }
             }
         };
-        auto batch = [&](uint32_t v0, const uint32_t (*xs)[4]) __attribute__((always_inline)) {
-            if (v0 + HB * NT <= v_end) {
-#pragma unroll
-                for (uint32_t i = 0; i < HB; i++) one(xs[i]);
-            } else {
-#pragma unroll
-                for (uint32_t i = 0; i < HB; i++)
-                    if (v0 + i * NT + t < v_end) one(xs[i]);
-            }
-        };
-        uint32_t xs[1][HB][4];
         for (uint32_t v0 = v_begin; v0 < v_end; v0 += HB * NT) {
-            load(v0, xs[0]);
-            batch(v0, xs[0]);
+            uint32_t xs[HB][4];
+#pragma unroll
+            for (uint32_t i = 0; i < HB; i++) chunk_in<B, 16>(cin, (v0 + i * NT + t) * 16, 0, xs[i]);
+#pragma unroll
+            for (uint32_t i = 0; i < HB; i++)
+                if (v0 + i * NT + t < v_end) one(xs[i]);
         }
     };
     for (uint32_t part = 0;; part += kPartVec) {
