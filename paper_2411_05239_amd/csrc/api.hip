@@ -71,6 +71,7 @@ EncParams make_params(int dtype, const zipnn_params& p, bool delta)
     for (int k = 0; k < 4; k++) e.policy[k] = uint32_t(k) < e.B ? p.policy[k] : 0;
     e.stage = nullptr;
     e.stage_chunk = e.stage_lg = e.stage_bm = 0;
+    e.segs = nullptr;
     return e;
 }
 
@@ -78,12 +79,14 @@ EncParams make_params(int dtype, const zipnn_params& p, bool delta)
 // packer writes into staging slots and a compaction places the payloads) for
 // launches with an XOR base, whose containers are small next to the bytes
 // each pass reads; its slots take about L/8 of the input.  Up to this many
-// bytes; beyond, or when the slots cannot be allocated, the exact path.
+// bytes; beyond, or when the slots cannot be allocated, the exact path, and
+// also for few chunks, where the size pass's sums let the packer put more
+// waves on each of them.
 constexpr size_t kStageMax = size_t(64) << 30;
 
 static size_t stage_bytes_of(bool any_base, uint64_t total_chunks, int dtype, const zipnn_params& p)
 {
-    if (!any_base) return 0;
+    if (!any_base || total_chunks <= kFewChunks) return 0;
     const uint32_t B = uint32_t(dtype_bytes(dtype));
     const StageLayout sl = stage_layout(p.chunk_bytes, B, p.substream_syms, p.group, p.max_code_len);
     const size_t bytes = size_t(total_chunks) * B * sl.chunk;
@@ -271,11 +274,11 @@ static int encode_tensors(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, in
     bool any_base = false;
     for (int i = 0; i < n; i++) any_base |= t[i].base != nullptr;
     size_t stage = stage_bytes_of(any_base, total_chunks, dtype, *p);
-    EncScratch lay = enc_scratch_layout(size_t(total_chunks) * B, size_t(n), stage);
+    EncScratch lay = enc_scratch_layout(size_t(total_chunks), B, size_t(n), stage);
     int rc = grow_scratch(ctx, lay.need);
     if (rc && stage) {   // no room for the staging slots: the exact path
         stage = 0;
-        lay = enc_scratch_layout(size_t(total_chunks) * B, size_t(n));
+        lay = enc_scratch_layout(size_t(total_chunks), B, size_t(n));
         rc = grow_scratch(ctx, lay.need);
     }
     if (rc) return rc;
@@ -309,6 +312,7 @@ static int encode_tensors(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, in
     uint64_t* d_aoff = (uint64_t*)(sc + lay.aoff);
     EncParams ep = make_params(dtype, *p, any_base);
     if (stage) set_stage(ep, sc + lay.stage, dtype, *p);
+    else if (total_chunks <= kFewChunks) ep.segs = (uint32_t*)(sc + lay.segs);
     if (hipMemcpyAsync(d_descs, hd, size_t(n) * sizeof(EncDesc), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(d_prefix, hp, size_t(n + 1) * sizeof(uint32_t), hipMemcpyHostToDevice, s) != hipSuccess ||
         launch_encode(d_descs, n, d_prefix, uint32_t(total_chunks), ep, (uint8_t*)arena, cap,
@@ -346,7 +350,7 @@ int zipnn_compress_noalloc(zipnn_ctx ctx, const void* src, int dtype, uint64_t n
     const uint64_t E = p->chunk_bytes / B;
     const uint64_t nc = (n + E - 1) / E;
     if (payload_base_of(nc, B) > dst_cap) return ZIPNN_E_NOSPACE;
-    const EncScratch lay = enc_scratch_layout(size_t(nc) * B, 1);
+    const EncScratch lay = enc_scratch_layout(size_t(nc), B, 1);
     if (lay.need > kFixedScratch) return ZIPNN_E_TOOBIG;
     if (!ctx->fixed_scratch) return ZIPNN_E_HIP;
     std::lock_guard<std::mutex> lk(g_fixed_mu);
@@ -367,7 +371,8 @@ int zipnn_compress_noalloc(zipnn_ctx ctx, const void* src, int dtype, uint64_t n
     uint32_t* d_prefix = (uint32_t*)(sc + lay.prefix);
     uint64_t* d_aoff = (uint64_t*)(sc + lay.aoff);
     uint64_t ho[2] = {0, 0};   // the arena offsets come back to the stack
-    const EncParams ep = make_params(dtype, *p, one.base != nullptr);
+    EncParams ep = make_params(dtype, *p, one.base != nullptr);
+    if (nc <= kFewChunks) ep.segs = (uint32_t*)(sc + lay.segs);
     if (launch_fill_desc(one, uint32_t(nc), d_descs, d_prefix, s) != hipSuccess ||
         launch_encode(d_descs, 1, d_prefix, uint32_t(nc), ep, (uint8_t*)dst, dst_cap, (EncEntry*)(sc + lay.entries),
                       sc + lay.codes, (uint32_t*)(sc + lay.nwords), (uint64_t*)(sc + lay.offsets),
@@ -426,7 +431,7 @@ int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, int
     bool any_base = false;
     for (int i = 0; i < n; i++) any_base |= t[i].base != nullptr;
     size_t stage = stage_bytes_of(any_base, total_chunks, dtype, *p);
-    EncScratch lay = enc_scratch_layout(size_t(total_chunks) * B, size_t(n), stage);
+    EncScratch lay = enc_scratch_layout(size_t(total_chunks), B, size_t(n), stage);
     std::vector<EncDesc> hd(static_cast<size_t>(n));
     std::vector<uint32_t> hp(static_cast<size_t>(n) + 1);
     uint32_t run = 0;
@@ -441,7 +446,7 @@ int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, int
     if (dev_malloc((void**)&e->d_mem, lay.need) != hipSuccess && stage) {   // no room for the staging slots
         e->d_mem = nullptr;
         stage = 0;
-        lay = enc_scratch_layout(size_t(total_chunks) * B, size_t(n));
+        lay = enc_scratch_layout(size_t(total_chunks), B, size_t(n));
         if (dev_malloc((void**)&e->d_mem, lay.need) != hipSuccess) e->d_mem = nullptr;
     }
     if (!e->d_mem ||
@@ -461,6 +466,7 @@ int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, int
     // capture the launches and the copy of the offsets once; every run replays them
     EncParams ep = make_params(dtype, *p, any_base);
     if (stage) set_stage(ep, sc + lay.stage, dtype, *p);
+    else if (total_chunks <= kFewChunks) ep.segs = (uint32_t*)(sc + lay.segs);
     if (hipStreamCreateWithFlags(&e->capst, hipStreamNonBlocking) != hipSuccess ||
         hipStreamBeginCapture(e->capst, hipStreamCaptureModeThreadLocal) != hipSuccess) {
         zipnn_encoder_destroy(e);

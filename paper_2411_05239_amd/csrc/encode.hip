@@ -1135,6 +1135,13 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
             reinterpret_cast<const uint32_t*>(v ? A.lens2[wv] : A.lens[wv])[lane];
         if (!staged && uint32_t(lane) < NG) nwords[ei * 64 + lane] = sh.lgw[v][wv][lane];
     }
+    // the ranges' sums of the chosen codes, for the packer (its ranges are these)
+    if (p.segs && NT == kSegWords && NG < uint32_t(kWavesA)) {
+#pragma unroll
+        for (uint32_t k = 0; k < B; k++)
+            if ((A.coded >> k) & 1)
+                p.segs[(uint64_t(gc) * B + k) * kSegWords + t] = S.seg[(A.fin >> k) & 1][k][t];
+    }
     __syncthreads();
 }
 
@@ -1328,12 +1335,20 @@ constexpr uint32_t kNoStore = 0x80000000u;      // buffer offset past every reso
 // P.pay[k], lane group j's words start at stage_bm + j * stage_lg, a ZG
 // bitmap at the slot's start; the lane group's word count goes to
 // nw_out[k * 64 + j].
-template <int B, int G>
+// A range [s0, s1) of the lane group's steps can be packed on its own: with c
+// a lane's code bits and l those of its last pair before the range (summed
+// here from the ranges' sums in `seg`, this being range sg), it has taken
+// ceil((c - l + 2L) / 32) words, c mod 32 bits lie in its first unfinished
+// one, and the lanes' words add up to the cursor.  A word belongs to the range
+// that takes it: the words taken before are completed but not stored here,
+// and after s1 the lanes go on, taking none, until theirs are complete.
+template <int B, int G, bool XB>
 __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* src, const uint8_t* base, uint32_t cm,
                                                                uint32_t zm, const PackLds& P, uint32_t L, uint32_t j,
                                                                uint32_t W, uint32_t m, bool xf, bool fuse_bitmap,
                                                                uint32_t rawmask, uint8_t* dst, uint32_t stage_lg,
-                                                               uint32_t stage_bm, uint32_t* nw_out)
+                                                               uint32_t stage_bm, uint32_t* nw_out, uint32_t s0,
+                                                               uint32_t s1, uint32_t sg, const uint32_t* seg)
 {
     constexpr int NB = B * G;
     constexpr int NW = NB >= 4 ? NB / 4 : 1;
@@ -1353,8 +1368,16 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
     // full groups of the lane group's last lane: every lane has at least these
     const uint32_t w_last = min(W, 64 * j + 64) - 1;
     const uint32_t nfull_all = w_last < Gfull ? (Gfull - 1 - w_last) / W + 1 : 0;
-    const uint32_t n_fast = (64 * j + 64 <= W) ? nfull_all / kPf * kPf : 0;
+    s0 = __builtin_amdgcn_readfirstlane(s0);
+    s1 = min(uint32_t(__builtin_amdgcn_readfirstlane(s1)), ng_max);
+    const uint32_t n_fast = min(s1, nfull_all) > s0 ? s0 + (min(s1, nfull_all) - s0) / kPf * kPf : s0;
     const uint32_t head = huf_head(W), bm = zg_bitmap(m, G);
+    // lanes past the last sub-stream: their loads and stores are out of range
+    // and they never need a word
+    const bool act = w < W;
+    const uint32_t w_in = act ? w * NB : kNoStore, w_raw = act ? w * G : kNoStore;
+    const __amdgpu_buffer_rsrc_t rsrc = in_rsrc(src, m * B);
+    const __amdgpu_buffer_rsrc_t rbase = in_rsrc(base ? base : src, base ? m * B : 0u);   // no base: zeros
     auto uni64 = [](uint64_t v) {
         return uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v)))) |
                (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(v >> 32)))) << 32);
@@ -1388,8 +1411,23 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
         x.out = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(wa), (short)0,
                                                   int(((cm >> k) & 1) ? 4 * nw : 0u), 0x00020000);
         x.bmw = (zb && fuse_bitmap) ? reinterpret_cast<uint64_t*>(dst + pk + (staged ? 0u : head)) : nullptr;
-        x.cur = x.alo = x.ahi = x.nacc = x.s0 = x.s1 = 0;
+        x.cur = x.alo = x.ahi = x.nacc = 0;
+        x.s0 = x.s1 = kNoStore;
         x.held = 0;
+        if (sg && ((cm >> k) & 1)) {
+            const uint32_t NG = (W + 63) / 64;
+            uint32_t c = 0, last = 0;
+            for (uint32_t g = 0; g < sg; g++) {
+                const uint32_t y = seg[k * kSegWords + 64 * (g * NG + j) + lane];
+                c += y >> 5;
+                last = y ? y & 31 : last;
+            }
+            const uint32_t taken = c ? (c - last + 2 * L + 31) / 32 : 0u;
+            x.cur = wave_sum(taken);
+            x.nacc = c & 31;
+            x.held = int(32 * taken - c);
+        }
+        if (!act) x.held = 1 << 30;
     });
     // raw byte groups copied here (groups of at most 4 bytes: b16 / b32
     // stores through one resource over the chunk's payloads, which are
@@ -1401,19 +1439,21 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
         int(__builtin_amdgcn_readfirstlane(rawmask ? uint32_t(P.pay[B - 1] - P.pay[0]) + m : 0u)), 0x00020000);
     // one pair of stream k: entries c0, c1 (zero for a symbol that is not
     // coded), p0 whether the lane takes part
-    auto pair = [&](auto kc, uint32_t c0, uint32_t c1, bool p0) __attribute__((always_inline)) {
+    auto pair = [&](auto kc, uint32_t c0, uint32_t c1, bool p0, auto take_c) __attribute__((always_inline)) {
+        constexpr bool TAKE = decltype(take_c)::value;
         Stream& x = S(kc);
-        const bool need = p0 && x.held < twoL;
-        const uint64_t msk = __ballot(need);
-        const uint32_t rank =
-            __builtin_amdgcn_mbcnt_hi(uint32_t(msk >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(msk), 0u));
-        const uint32_t place = (x.cur + rank) * 4u;
-        // nothing pending: held + nacc = 0, i.e. held = 0 (nacc < 32)
-        const bool empty = x.held == 0;
-        x.s0 = (need && empty) ? place : x.s0;
-        x.s1 = need ? place : x.s1;
-        x.held += need ? 32 : 0;
-        x.cur += uint32_t(__popcll(msk));
+        if constexpr (TAKE) {
+            const bool need = p0 && x.held < twoL;
+            const uint64_t msk = __ballot(need);
+            const uint32_t place = 4u * __builtin_amdgcn_mbcnt_hi(uint32_t(msk >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo(uint32_t(msk), x.cur));
+            // nothing pending: held + nacc = 0, i.e. held = 0 (nacc < 32)
+            const bool empty = x.held == 0;
+            x.s0 = (need && empty) ? place : x.s0;
+            x.s1 = need ? place : x.s1;
+            x.held += need ? 32 : 0;
+            x.cur += uint32_t(__popcll(msk));
+        }
         // the two codes side by side (the lengths sit in bits 27..31 of an
         // entry, so the entries' sum carries the sum of the lengths, <= 2L)
         const uint32_t l0 = c0 >> kLenShift, l = (c0 + c1) >> kLenShift;
@@ -1430,15 +1470,17 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
         x.ahi = 0;   // fewer than 32 bits left: none above the low word
         x.nacc &= 31u;
         x.s0 = full ? x.s1 : x.s0;
+        if constexpr (!TAKE) x.s1 = full ? kNoStore : x.s1;
     };
     // one step (group e of every lane); FAST: every lane has a full group
-    auto step = [&](uint32_t e, const uint32_t* wd, auto fast_c) __attribute__((always_inline)) {
+    auto step = [&](uint32_t e, const uint32_t* wd, auto fast_c, auto take_c) __attribute__((always_inline)) {
         constexpr bool FAST = decltype(fast_c)::value;
+        constexpr bool TAKE = decltype(take_c)::value;   // else only words already taken are completed
         const bool has = FAST || e < ng;
         const uint32_t ecnt = FAST ? uint32_t(G) : (has ? (w + e * W < Gfull ? G : rem) : 0u);
-        if constexpr (kFuseRaw) {
+        if constexpr (kFuseRaw && TAKE) {
             if (rawmask && has) {
-                const uint32_t q0 = (w + e * W) * G;
+                const uint32_t q0 = w_raw + e * W * G;
                 for_streams<B>([&](auto rc) __attribute__((always_inline)) {
                     constexpr int r = decltype(rc)::value;
                     if (!((rawmask >> r) & 1)) return;
@@ -1465,15 +1507,15 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
                     const bool p0 = 2u * pr < gcnt, p1 = 2u * pr + 1 < gcnt;
                     const uint32_t c0 = P.rcode[k][sym_of<B>(wd, k, 2 * pr)];
                     const uint32_t c1 = P.rcode[k][sym_of<B>(wd, k, 2 * pr + 1)];
-                    pair(kc, p0 ? c0 : 0u, p1 ? c1 : 0u, p0);
+                    pair(kc, p0 ? c0 : 0u, p1 ? c1 : 0u, p0, take_c);
                 }
             };
             if ((zm >> k) & 1) {
-                const bool mk = has && marked<B, G>(wd, k, ecnt, P.z[k]);
+                const bool mk = act && has && marked<B, G>(wd, k, ecnt, P.z[k]);
                 const uint64_t bits = __ballot(mk);
                 // ZG with W a multiple of 64: the 64 bits of this lane
                 // group's step e are one aligned word of the bitmap
-                if (fuse_bitmap && lane == 0) S(kc).bmw[j + e * (W / 64)] = bits;
+                if (TAKE && fuse_bitmap && lane == 0) S(kc).bmw[j + e * (W / 64)] = bits;
                 // where no lane of the wave holds a marked group, the pairs
                 // would take no word and add no bits: they are skipped
                 if (bits) pairs(mk ? ecnt : 0u);
@@ -1482,33 +1524,74 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
             }
         });
     };
-    auto load = [&](uint32_t e, uint32_t* wd) {
-        if (e < ng) group_words<B, G>(src, base, w + e * W, m, wd, xf);
+    // step e's bytes of every lane (zeros past the end), fetched kPf steps
+    // ahead; taken into words when the step comes, so that nothing waits for
+    // them before.  The tensor's partial last group is read element by element.
+    struct Fetch {
+        uint32_t x[NW], y[XB ? NW : 1];
     };
-    uint32_t pf[kPf][NW];
+    Fetch pf[kPf];
+    auto load = [&](uint32_t e, Fetch& f) __attribute__((always_inline)) {
+        buf_in<NB>(rsrc, w_in + e * W * NB, 0, f.x);
+        if constexpr (XB) buf_in<NB>(rbase, w_in + e * W * NB, 0, f.y);
+    };
+    auto words = [&](const Fetch& f, uint32_t* wd) __attribute__((always_inline)) {
 #pragma unroll
-    for (uint32_t u = 0; u < kPf; u++) load(u, pf[u]);
-    for (uint32_t j0 = 0; j0 < n_fast; j0 += kPf) {
+        for (int x = 0; x < NW; x++) {
+            wd[x] = f.x[x];
+            if constexpr (XB) wd[x] ^= f.y[x];
+            if (xf) wd[x] = exp_fwd<B>(wd[x]);
+        }
+    };
+    auto last_words = [&](uint32_t e, uint32_t* wd) __attribute__((always_inline)) {
+        if (rem && act && w + e * W == Gfull) group_words<B, G>(src, base, Gfull, m, wd, xf);
+    };
+    using T = std::integral_constant<bool, true>;
+    using F = std::integral_constant<bool, false>;
+#pragma unroll
+    for (uint32_t u = 0; u < kPf; u++) load(s0 + u, pf[u]);
+    for (uint32_t j0 = s0; j0 < n_fast; j0 += kPf) {
 #pragma unroll
         for (uint32_t u = 0; u < kPf; u++) {
             uint32_t cw[NW];
-#pragma unroll
-            for (int x = 0; x < NW; x++) cw[x] = pf[u][x];
+            words(pf[u], cw);
             load(j0 + u + kPf, pf[u]);
-            step(j0 + u, cw, std::integral_constant<bool, true>{});
+            step(j0 + u, cw, T{}, T{});
         }
     }
-    for (uint32_t j0 = n_fast; j0 < ng_max; j0 += kPf) {
+    // the steps without a full group in every lane, then (after s1) those that
+    // complete the words taken in this range
+    bool ended = false;
+    for (uint32_t j0 = n_fast; j0 < ng_max && !ended; j0 += kPf) {
 #pragma unroll
         for (uint32_t u = 0; u < kPf; u++) {
             const uint32_t jj = j0 + u;
-            if (jj < ng_max) {
-                uint32_t cw[NW];
-#pragma unroll
-                for (int x = 0; x < NW; x++) cw[x] = pf[u][x];
-                load(jj + kPf, pf[u]);
-                step(jj, cw, std::integral_constant<bool, false>{});
+            if (jj >= ng_max || ended) continue;
+            if (jj == s1)
+                for_streams<B>([&](auto kc) __attribute__((always_inline)) {
+                    Stream& x = S(kc);
+                    const int pend = act ? (x.held + int(x.nacc)) >> 5 : 0;
+                    x.s0 = pend > 0 ? x.s0 : kNoStore;
+                    x.s1 = pend > 1 ? x.s1 : kNoStore;
+                });
+            if (jj >= s1) {
+                bool open = false;
+                for_streams<B>([&](auto kc) __attribute__((always_inline)) {
+                    constexpr int k = decltype(kc)::value;
+                    const Stream& x = S(kc);
+                    if ((cm >> k) & 1) open |= act && (x.held + int(x.nacc)) >> 5 > 0;
+                });
+                if (__ballot(open) == 0) {
+                    ended = true;
+                    continue;
+                }
             }
+            uint32_t cw[NW];
+            words(pf[u], cw);
+            last_words(jj, cw);
+            load(jj + kPf, pf[u]);
+            if (jj < s1) step(jj, cw, F{}, T{});
+            else step(jj, cw, F{}, F{});
         }
     }
     // the lane's unfinished words: the partial one (zero bits if none), then zero
@@ -1527,7 +1610,7 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
 // The group bitmap of a ZG stream: wave v writes 64-bit words x = v, v+4, ...
 // of the bm bytes (lane l tests group 64x + l); bits past the last group and
 // the padding are zero.
-template <int B, int G>
+template <int B, int G, int NT>
 __device__ void pack_bitmap(const uint8_t* src, const uint8_t* base, int k, uint32_t z, uint32_t m, uint32_t bm,
                             uint8_t* dst, bool xf)
 {
@@ -1535,7 +1618,7 @@ __device__ void pack_bitmap(const uint8_t* src, const uint8_t* base, int k, uint
     constexpr int NW = NB >= 4 ? NB / 4 : 1;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t Gtot = (m + G - 1) / G;
-    for (uint32_t x = threadIdx.x >> 6; x < bm / 8; x += kWaves) {
+    for (uint32_t x = threadIdx.x >> 6; x < bm / 8; x += NT / 64) {
         const uint32_t q = 64 * x + lane;
         bool mk = false;
         if (q < Gtot) {
@@ -1552,7 +1635,7 @@ __device__ void pack_bitmap(const uint8_t* src, const uint8_t* base, int k, uint
 // RAW stream with one 16-byte store each, then the zero padding.  With
 // pad_only the packer of a coded group copies the elements, and only the
 // padding is written here.
-template <int B>
+template <int B, int NT>
 __device__ void pack_raw(const uint8_t* src, const uint8_t* base, uint8_t* dst, const PackLds& P, uint32_t m, bool xf,
                          bool pad_only)
 {
@@ -1561,7 +1644,7 @@ __device__ void pack_raw(const uint8_t* src, const uint8_t* base, uint8_t* dst, 
         if (P.mode[k] == kModeRaw) rawmask |= 1u << k;
     if (!rawmask) return;
     if (pad_only) {
-        for (uint32_t e = m + threadIdx.x; e < uint32_t(align_pay(m)); e += kBlock)
+        for (uint32_t e = m + threadIdx.x; e < uint32_t(align_pay(m)); e += NT)
 #pragma unroll
             for (int k = 0; k < B; k++)
                 if ((rawmask >> k) & 1) dst[P.pay[k] + e] = 0;
@@ -1569,11 +1652,11 @@ __device__ void pack_raw(const uint8_t* src, const uint8_t* base, uint8_t* dst, 
     }
     const uint32_t units = m / 16;
     constexpr uint32_t RB = B == 4 ? 2 : (B == 2 ? 4 : 8);   // units in flight per thread
-    for (uint32_t u0 = threadIdx.x; u0 < units; u0 += RB * kBlock) {
+    for (uint32_t u0 = threadIdx.x; u0 < units; u0 += RB * NT) {
         uint32_t wds[RB][4 * B];
 #pragma unroll
         for (uint32_t r = 0; r < RB; r++) {
-            const uint32_t u = u0 + r * kBlock;
+            const uint32_t u = u0 + r * NT;
             if (u < units) {
                 loadNB<16 * B>(src + uint64_t(u) * 16 * B, wds[r]);
                 if (base) {
@@ -1589,7 +1672,7 @@ __device__ void pack_raw(const uint8_t* src, const uint8_t* base, uint8_t* dst, 
         }
 #pragma unroll
         for (uint32_t r = 0; r < RB; r++) {
-            const uint32_t u = u0 + r * kBlock;
+            const uint32_t u = u0 + r * NT;
 #pragma unroll
             for (int k = 0; k < B; k++) {
                 if (!((rawmask >> k) & 1) || u >= units) continue;
@@ -1601,7 +1684,7 @@ __device__ void pack_raw(const uint8_t* src, const uint8_t* base, uint8_t* dst, 
         }
     }
     // tail elements, then zero padding to the payload alignment
-    for (uint32_t e = units * 16 + threadIdx.x; e < uint32_t(align_pay(m)); e += kBlock) {
+    for (uint32_t e = units * 16 + threadIdx.x; e < uint32_t(align_pay(m)); e += NT) {
         const uint32_t v = e < m ? element_word<B>(src, base, e, xf) : 0u;
 #pragma unroll
         for (int k = 0; k < B; k++)
@@ -1609,15 +1692,9 @@ __device__ void pack_raw(const uint8_t* src, const uint8_t* base, uint8_t* dst, 
     }
 }
 
-// Five waves per SIMD for 2-byte words (at most 96 VGPRs, a few spills
-// outside the pair loop: the BF16 deltas' encode 6% faster, the checkpoint's
-// unchanged), four for the others (at most 128; the FP32 g = 4 instance
-// spills).  XB: the instance for launches with an XOR base, six waves for
-// 2-byte words (80 VGPRs): the deltas 4% faster again, where the plain
-// checkpoint would lose 2%.
 // The packing of chunk gc by one workgroup (into its container, or staged
 // into its staging slots with the word counts).
-template <int BB, int GG>
+template <int BB, int GG, bool XB, int NT>
 __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const EncDesc* __restrict__ descs, int n_desc,
                                                           const uint32_t* __restrict__ chunk_prefix, const EncParams& p,
                                                           const EncEntry* __restrict__ entries,
@@ -1669,12 +1746,12 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
         }
         if (t == 0) P.z[k] = en.rle;
         if (en.mode == kModeHuf || en.mode == kModeZg) {
-            len[k] = lens[ei * 256 + t];
+            len[k] = t < 256 ? lens[ei * 256 + t] : 0u;
             // symbols of each length in this wave; rank: equal lengths below
             for (uint32_t l = 1; l <= p.L; l++) {
                 const uint64_t msk = __ballot(len[k] == l);
                 if (len[k] == l) rank[k] = __popcll(msk & lt_mask);
-                if (lane == 0) P.cnt[k][l][wv] = uint32_t(__popcll(msk));
+                if (lane == 0 && wv < 4) P.cnt[k][l][wv] = uint32_t(__popcll(msk));
             }
             if (t < 64 && !staged) {
                 const uint32_t nw = uint32_t(t) < NG ? nwords[ei * 64 + t] : 0u;
@@ -1704,7 +1781,7 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
             if (len[k] == l)
                 code = first + rank[k] + (wv > 0 ? c4.x : 0u) + (wv > 1 ? c4.y : 0u) + (wv > 2 ? c4.z : 0u);
         }
-        P.rcode[k][t] = len[k] ? ((__brev(code) >> (32 - len[k])) | (len[k] << kLenShift)) : 0u;
+        if (t < 256) P.rcode[k][t] = len[k] ? ((__brev(code) >> (32 - len[k])) | (len[k] << kLenShift)) : 0u;
     }
     __syncthreads();
     const uint8_t* src = d.src + e0 * B;
@@ -1720,7 +1797,7 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
         if (P.mode[k] == kModeZg) zm |= 1u << k;
     }
     const bool fuse_raw = GG <= 4 && BB * GG <= 16 && cm != 0;
-    pack_raw<BB>(src, base, dst, P, m, xf, fuse_raw);
+    pack_raw<BB, NT>(src, base, dst, P, m, xf, fuse_raw);
     // with W a multiple of 64 the packer writes a ZG bitmap's words as it
     // marks the groups
     const bool fuse_bitmap = W % 64 == 0;
@@ -1734,8 +1811,8 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
             if (t < 128)
                 pay[t] = uint8_t((P.rcode[k][2 * t] >> kLenShift) | ((P.rcode[k][2 * t + 1] >> kLenShift) << 4));
             if (uint32_t(t) < NG) ((uint32_t*)(pay + 128))[t] = P.wpre[k][t + 1] - P.wpre[k][t];
-            for (uint32_t i = 128 + 4 * NG + t; i < head; i += kBlock) pay[i] = 0;
-            for (uint32_t i = P.bytes[k] + t; i < uint32_t(align_pay(P.bytes[k])); i += kBlock) pay[i] = 0;
+            for (uint32_t i = 128 + 4 * NG + t; i < head; i += NT) pay[i] = 0;
+            for (uint32_t i = P.bytes[k] + t; i < uint32_t(align_pay(P.bytes[k])); i += NT) pay[i] = 0;
         }
         const uint32_t lead = staged ? 0u : head;   // where the bitmap starts
         if (zg) {
@@ -1743,33 +1820,44 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
             if (fuse_bitmap) {   // only the words past the last group are zeroed here
                 uint64_t* words = reinterpret_cast<uint64_t*>(pay + lead);
                 const uint32_t Gtot = (m + GG - 1) / GG;
-                for (uint32_t x = (Gtot + 63) / 64 + t; x < bm / 8; x += kBlock) words[x] = 0;
+                for (uint32_t x = (Gtot + 63) / 64 + t; x < bm / 8; x += NT) words[x] = 0;
             } else {
-                pack_bitmap<BB, GG>(src, base, int(k), P.z[k], m, bm, pay + lead, xf);
+                pack_bitmap<BB, GG, NT>(src, base, int(k), P.z[k], m, bm, pay + lead, xf);
             }
         }
     }
+    // one wave per lane group, or (ranges of steps summed by the analysis,
+    // fewer lane groups than waves) per range of one
+    const uint32_t nseg = p.segs && NG < uint32_t(NT / 64) ? uint32_t(NT / 64) / NG : 1u;
+    const uint32_t steps = ((m + GG - 1) / GG - 1) / W + 1, per = (steps + nseg - 1) / nseg;
     if (cm)
-        for (uint32_t j = wv; j < NG; j += kWaves)
-            pack_lane_group<BB, GG>(src, base, cm, zm, P, p.L, j, W, m, xf, fuse_bitmap, fuse_raw ? rawmask : 0u,
+        for (uint32_t x = wv; x < NG * nseg; x += NT / 64) {
+            const uint32_t j = x % NG, sg = x / NG;
+            if (sg * per >= steps) continue;
+            pack_lane_group<BB, GG, XB>(src, base, cm, zm, P, p.L, j, W, m, xf, fuse_bitmap, fuse_raw ? rawmask : 0u,
                                     dst, staged ? p.stage_lg : 0u, p.stage_bm,
-                                    staged ? nwords + uint64_t(gc) * B * 64 : nullptr);
-    __syncthreads();
+                                    staged ? nwords + uint64_t(gc) * B * 64 : nullptr, sg * per,
+                                    min(steps, (sg + 1) * per), sg, p.segs + uint64_t(gc) * B * kSegWords);
+        }
 }
 
-template <int BB, int GG, bool XB>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BB == 2 ? (XB ? 6 : 5) : 4, 8))) void k_pack(const EncDesc* __restrict__ descs, int n_desc,
-                                                 const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
-                                                 EncParams p, const EncEntry* __restrict__ entries,
-                                                 const uint8_t* __restrict__ lens,
-                                                 const uint64_t* __restrict__ offsets,
-                                                 const uint64_t* __restrict__ totals,
-                                                 uint32_t* __restrict__ nwords)
+// NT = 256 for full launches, which the bytes read and written bound: 5 GB of
+// an 8B checkpoint 1.77 ms, 4.7 TB/s, a copy's rate.  NT = 1024 for few
+// chunks, where a lane group's serial steps bound: with its steps cut into 16
+// / (lane groups) ranges, an 8 KiB tensor 58 -> 16 us, 32 chunks of 256 KiB 61
+// -> 30 us.  XB: some tensor has an XOR base, whose bytes are fetched ahead
+// with the tensor's (a 1.7 GB delta's pass 1880 -> 1750 us against the XOR at
+// the fetch, which waited for both).
+template <int BB, int GG, bool XB, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 256 && BB == 2 ? (XB ? 6 : 5) : 4, 8))) void k_pack(
+    const EncDesc* __restrict__ descs, int n_desc, const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
+    EncParams p, const EncEntry* __restrict__ entries, const uint8_t* __restrict__ lens,
+    const uint64_t* __restrict__ offsets, const uint64_t* __restrict__ totals, uint32_t* __restrict__ nwords)
 {
     __shared__ PackLds P;
     const uint32_t gc = chunk_of_block();
     if (gc < total_chunks)
-        pack_chunk<BB, GG>(gc, descs, n_desc, chunk_prefix, p, entries, lens, offsets, totals, nwords, P);
+        pack_chunk<BB, GG, XB, NT>(gc, descs, n_desc, chunk_prefix, p, entries, lens, offsets, totals, nwords, P);
 }
 
 // Staged packing, last step: for each chunk, its map entries, and for each
@@ -1889,7 +1977,7 @@ hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_p
             // per CU are full; then 512 threads a chunk, four workgroups per
             // CU, overlap more phases (5 GB of BF16: 3.27 against 3.39 ms a
             // pass; 32 chunks: equal within 1%)
-            const bool many = total_chunks > 512;
+            const bool many = p.segs == nullptr;
 #define ZIPNN_ANALYZE(B_)                                                                                            \
     if (many)                                                                                                        \
         k_analyze<B_, 512><<<grid, 512, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries,    \
@@ -1922,12 +2010,12 @@ hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_p
         if (compact)                                                                                                \
             k_compact<B_, G_><<<grid, kBlock, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, entries,   \
                                                       lens, offsets, totals, nwords);                             \
-        else if (xb)   /* the XB instance exists for 2-byte words only */                                        \
-            k_pack<B_, G_, B_ == 2><<<grid, kBlock, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p,       \
-                                                            entries, lens, offsets, totals, nwords);              \
+        else if (p.segs)                                                                                            \
+            (xb ? k_pack<B_, G_, true, 1024> : k_pack<B_, G_, false, 1024>)<<<grid, 1024, 0, s>>>(                  \
+                d_descs, n_desc, d_chunk_prefix, total_chunks, p, entries, lens, offsets, totals, nwords);          \
         else                                                                                                        \
-            k_pack<B_, G_, false><<<grid, kBlock, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, entries,\
-                                                          lens, offsets, totals, nwords);                         \
+            (xb ? k_pack<B_, G_, true, 256> : k_pack<B_, G_, false, 256>)<<<grid, 256, 0, s>>>(                     \
+                d_descs, n_desc, d_chunk_prefix, total_chunks, p, entries, lens, offsets, totals, nwords);          \
         launched = true;                                                                                            \
     }
         ZIPNN_PACK(1, 2) ZIPNN_PACK(1, 4) ZIPNN_PACK(1, 8)

@@ -191,7 +191,17 @@ struct EncParams {
     // words at stage_bm + j * stage_lg (StageLayout).
     uint8_t* stage;
     uint32_t stage_chunk, stage_lg, stage_bm;
+    // Launches of few chunks (else nullptr): kSegWords words per (chunk,
+    // stream), the code bits of each lane over ranges of its steps, from
+    // which the packer starts several waves on one lane group.
+    uint32_t* segs;
 };
+
+// At most this many chunks (two analysis workgroups per CU) count as few: the
+// launch's time is one chunk's latency, which more waves per chunk shorten,
+// and not the memory's rate.
+constexpr uint32_t kFewChunks = 512;
+constexpr uint32_t kSegWords = 1024;
 
 // Staging slots of one launch: a lane of S symbols holds at most S * L code
 // bits and takes at most ceil((S L + 2L + 31) / 32) words (the refill rule),
@@ -296,11 +306,12 @@ hipError_t launch_fill_desc(const EncDesc& one, uint32_t total_chunks, EncDesc* 
 // Offsets of the encoder's device scratch for ne = chunks * B entries of n
 // tensors (every array 256-byte aligned); `need` is the total.
 struct EncScratch {
-    size_t entries, codes, offsets, nwords, totals, aoff, descs, prefix, stage, need;
+    size_t entries, codes, offsets, nwords, totals, aoff, descs, prefix, segs, stage, need;
 };
 // stage_bytes: the staging slots of a staged launch (0: none)
-inline EncScratch enc_scratch_layout(size_t ne, size_t n, size_t stage_bytes = 0)
+inline EncScratch enc_scratch_layout(size_t chunks, size_t B, size_t n, size_t stage_bytes = 0)
 {
+    const size_t ne = chunks * B;
     auto a256 = [](size_t v) { return (v + 255) & ~size_t(255); };
     EncScratch L;
     L.entries = 0;
@@ -311,7 +322,8 @@ inline EncScratch enc_scratch_layout(size_t ne, size_t n, size_t stage_bytes = 0
     L.aoff = a256(L.totals + n * sizeof(uint64_t));
     L.descs = a256(L.aoff + (n + 1) * sizeof(uint64_t));
     L.prefix = a256(L.descs + n * sizeof(EncDesc));
-    L.stage = a256(L.prefix + (n + 1) * sizeof(uint32_t));
+    L.segs = a256(L.prefix + (n + 1) * sizeof(uint32_t));
+    L.stage = a256(L.segs + (chunks <= kFewChunks ? ne * kSegWords * sizeof(uint32_t) : 0));
     L.need = L.stage + stage_bytes + 256;
     return L;
 }

@@ -1,0 +1,107 @@
+"""GPU parity of the encoder's choices by launch size: up to 512 chunks the
+analysis runs 1024 threads a chunk and the packer starts several waves on one
+lane group from the analysis' sums; beyond, 512 and 256 threads (and staging
+slots for launches with an XOR base).  The counting pass reduces its counters
+every 2 MiB of a chunk.  Containers equal the oracle's byte for byte."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2411_05239_amd import zipnn as Z
+
+pytestmark = pytest.mark.gpu
+
+TORCH = {Z.ZIPNN_BF16: torch.bfloat16, Z.ZIPNN_FP32: torch.float32, Z.ZIPNN_U8: torch.uint8}
+
+
+@pytest.fixture(scope="module")
+def codec():
+    c = Z.Codec(0)
+    yield c
+    c.close()
+
+
+def _check(codec, dt, raw, p, base=None):
+    """raw, base: uint8 arrays of whole words"""
+    x = torch.from_numpy(raw.copy()).view(TORCH[dt]).cuda()
+    b = torch.from_numpy(base.copy()).view(TORCH[dt]).cuda() if base is not None else None
+    c = codec.compress(x, p, base=b)
+    ref = oracle.compress(raw, dt, base=base, chunk_bytes=p.chunk_bytes, S=p.substream_syms, g=p.group,
+                          L=p.max_code_len, policy=list(p.policy), skip=p.probe_skip, exp=bool(p.exponent))
+    assert np.array_equal(c.cpu().numpy(), ref)
+    out = torch.empty_like(x)
+    codec.decompress(c, out, base=b)
+    assert torch.equal(out.view(torch.uint8), x.view(torch.uint8))
+
+
+def _words(rng, n, B):
+    """an exponent-like, a delta-like and spread byte groups"""
+    raw = rng.integers(0, 256, (n, B), dtype=np.uint8)
+    raw[:, B - 1] = rng.choice(np.array([60, 61, 62, 63, 188, 189, 190, 64], np.uint8), n,
+                               p=[.3, .2, .15, .1, .1, .08, .05, .02])
+    if B > 1:
+        raw[:, 0] = np.where(rng.random(n) < 0.85, 0, raw[:, 0])
+    return raw.reshape(-1)
+
+
+@pytest.mark.parametrize("delta", [False, True])
+@pytest.mark.parametrize("dt,S,g", [(Z.ZIPNN_BF16, 32, 4), (Z.ZIPNN_BF16, 128, 2), (Z.ZIPNN_FP32, 16, 8),
+                                    (Z.ZIPNN_U8, 64, 8)])
+@pytest.mark.parametrize("extra", [0, 1])
+def test_few_and_many_chunks(codec, dt, S, g, extra, delta):
+    """512 chunks are few, 513 (the last of one element) are many."""
+    B = Z.WIDTH[dt]
+    n = 512 * 4096 // B + extra
+    rng = np.random.default_rng(31 * dt + S + extra)
+    raw = _words(rng, n, B)
+    base = None
+    if delta:
+        base = rng.integers(0, 256, raw.size, dtype=np.uint8)
+        raw = raw ^ base
+    _check(codec, dt, raw, Z.make_params(dt, chunk_bytes=4096, S=S, g=g), base)
+
+
+@pytest.mark.parametrize("W,tail", [(1, 0), (8, 3), (63, 1), (64, 0), (65, 2), (192, 5), (320, 0), (960, 7), (1024, 1)])
+@pytest.mark.parametrize("zg", [False, True])
+def test_ranges_of_a_lane_group(codec, W, tail, zg):
+    """Lane groups cut into 16 / (lane groups) ranges of steps, with partial
+    lane groups, a partial last group and, for ZG, lanes whose words stay
+    unfinished over several ranges."""
+    S, g = 64, 4
+    n = W * S - tail
+    rng = np.random.default_rng(W + tail)
+    raw = np.zeros((n, 2), np.uint8)
+    raw[:, 1] = rng.choice(np.array([1, 2, 3, 4, 5], np.uint8), n, p=[.9, .05, .03, .01, .01])
+    raw[:, 0] = np.where(rng.random(n) < 0.03, rng.integers(0, 256, n), 0)
+    p = Z.make_params(Z.ZIPNN_BF16, chunk_bytes=262144, S=S, g=g,
+                      policy=[Z.ZIPNN_HUF, Z.ZIPNN_ZG if zg else Z.ZIPNN_HUF])
+    _check(codec, Z.ZIPNN_BF16, raw.reshape(-1), p)
+
+
+@pytest.mark.parametrize("dt", [Z.ZIPNN_BF16, Z.ZIPNN_FP32, Z.ZIPNN_U8])
+@pytest.mark.parametrize("value", [0, 0x5A])
+def test_largest_chunk_of_almost_one_value(codec, dt, value):
+    """4 MiB chunks whose bytes are all but one the same: the largest counts
+    that the shared counters and the code construction meet."""
+    B = Z.WIDTH[dt]
+    raw = np.full((4 << 20) + 16 * B, value, np.uint8)
+    raw[12345 * B:12345 * B + B] = value ^ 1
+    p = Z.make_params(dt, chunk_bytes=4 << 20, S=4096, g=4, policy=[Z.ZIPNN_HUF] * B)
+    _check(codec, dt, raw, p)
+
+
+@pytest.mark.parametrize("n_sym", [2, 63, 64, 65, 128, 255, 256])
+@pytest.mark.parametrize("L", [8, 11])
+def test_alphabet_sizes(codec, n_sym, L):
+    """Code construction with one and four leaves a lane, ties and steep
+    counts."""
+    rng = np.random.default_rng(n_sym + L)
+    syms = rng.permutation(256)[:n_sym].astype(np.uint8)
+    for counts in (np.full(n_sym, 7), np.minimum(np.cumsum(np.arange(n_sym)) + 1, 3000),
+                   np.minimum(2 ** np.minimum(np.arange(n_sym), 14), 6000), rng.integers(1, 5, n_sym)):
+        raw = np.repeat(syms, counts)
+        rng.shuffle(raw)
+        raw = np.resize(raw, (raw.size + 15) // 16 * 16)
+        _check(codec, Z.ZIPNN_U8, raw, Z.make_params(Z.ZIPNN_U8, chunk_bytes=1 << 20, S=256, L=L,
+                                                     policy=[Z.ZIPNN_HUF]))
