@@ -252,8 +252,8 @@ typedef struct zipnn_encoder_s* zipnn_encoder;
 /* Prepare the batched compression of tensors[0..n) (as zipnn_compress_batch,
  * same bytes) for repeated runs, e.g. saving a checkpoint again and again:
  * the descriptors are uploaded once, and the encode launches (histogram and
- * code build, placement, container layout, packing) plus the copy of the
- * n+1 arena offsets to pinned host memory are captured in a hipGraph.  The
+ * code build, placement and container layout, which also writes the n+1 arena
+ * offsets to pinned host memory, packing) are captured in a hipGraph.  The
  * encoder owns its scratch.  The tensors (and bases) are read, and the arena
  * written, at every run: they must stay valid while the encoder lives. */
 int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* tensors, int n, const zipnn_params* p,

@@ -202,9 +202,7 @@ int zipnn_ctx_status(zipnn_ctx ctx, void* stream, int clear)
     if (!ctx) return ZIPNN_E_INVAL;
     DeviceGuard g(ctx->device);
     hipStream_t s = (hipStream_t)stream;
-    if (hipMemcpyAsync(ctx->h_status, ctx->d_status, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess)
-        return ZIPNN_E_HIP;
-    if (clear && launch_clear_status(ctx->d_status, s) != hipSuccess) return ZIPNN_E_HIP;
+    if (launch_take_status(ctx->d_status, ctx->h_status, clear != 0, s) != hipSuccess) return ZIPNN_E_HIP;
     if (hipStreamSynchronize(s) != hipSuccess) return ZIPNN_E_HIP;
     return *ctx->h_status;
 }
@@ -282,14 +280,15 @@ static int encode_tensors(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, in
         rc = grow_scratch(ctx, lay.need);
     }
     if (rc) return rc;
-    // host staging (pinned): descriptors, chunk prefix, then the arena offsets
-    const size_t stage_bytes = size_t(n) * sizeof(EncDesc) + size_t(n + 1) * sizeof(uint32_t) +
-                               size_t(n + 1) * sizeof(uint64_t) + 64;
-    rc = grow_pinned(ctx, stage_bytes / sizeof(uint64_t) + 1);
+    // host staging (pinned): descriptors and chunk prefix as they lie in the
+    // scratch (one copy), then the arena offsets, which the placement writes
+    const size_t prefix_at = lay.prefix - lay.descs;
+    const size_t up_bytes = prefix_at + size_t(n + 1) * sizeof(uint32_t);
+    rc = grow_pinned(ctx, (align256(up_bytes) + size_t(n + 1) * sizeof(uint64_t)) / sizeof(uint64_t) + 1);
     if (rc) return rc;
     EncDesc* hd = (EncDesc*)ctx->h_total;
-    uint32_t* hp = (uint32_t*)(hd + n);
-    uint64_t* ho = (uint64_t*)align16(uint64_t(hp + n + 1));
+    uint32_t* hp = (uint32_t*)((uint8_t*)hd + prefix_at);
+    uint64_t* ho = (uint64_t*)((uint8_t*)hd + align256(up_bytes));
     uint32_t run = 0;
     for (int i = 0; i < n; i++) {
         const uint64_t nc = (t[i].n_elems + E - 1) / E;
@@ -313,12 +312,13 @@ static int encode_tensors(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, in
     EncParams ep = make_params(dtype, *p, any_base);
     if (stage) set_stage(ep, sc + lay.stage, dtype, *p);
     else if (total_chunks <= kFewChunks) ep.segs = (uint32_t*)(sc + lay.segs);
-    if (hipMemcpyAsync(d_descs, hd, size_t(n) * sizeof(EncDesc), hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(d_prefix, hp, size_t(n + 1) * sizeof(uint32_t), hipMemcpyHostToDevice, s) != hipSuccess ||
+    // a single tensor's descriptor travels in kernel arguments
+    const hipError_t up = n == 1 ? launch_fill_desc(hd[0], hp[1], d_descs, d_prefix, s)
+                                 : hipMemcpyAsync(d_descs, hd, up_bytes, hipMemcpyHostToDevice, s);
+    if (up != hipSuccess ||
         launch_encode(d_descs, n, d_prefix, uint32_t(total_chunks), ep, (uint8_t*)arena, cap,
                       (EncEntry*)(sc + lay.entries), sc + lay.codes, (uint32_t*)(sc + lay.nwords),
-                      (uint64_t*)(sc + lay.offsets), (uint64_t*)(sc + lay.totals), d_aoff, s) != hipSuccess ||
-        hipMemcpyAsync(ho, d_aoff, size_t(n + 1) * sizeof(uint64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+                      (uint64_t*)(sc + lay.offsets), (uint64_t*)(sc + lay.totals), d_aoff, ho, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return ZIPNN_E_HIP;
     if (ho[n] > cap) return ZIPNN_E_NOSPACE;
@@ -376,7 +376,7 @@ int zipnn_compress_noalloc(zipnn_ctx ctx, const void* src, int dtype, uint64_t n
     if (launch_fill_desc(one, uint32_t(nc), d_descs, d_prefix, s) != hipSuccess ||
         launch_encode(d_descs, 1, d_prefix, uint32_t(nc), ep, (uint8_t*)dst, dst_cap, (EncEntry*)(sc + lay.entries),
                       sc + lay.codes, (uint32_t*)(sc + lay.nwords), (uint64_t*)(sc + lay.offsets),
-                      (uint64_t*)(sc + lay.totals), d_aoff, s) != hipSuccess ||
+                      (uint64_t*)(sc + lay.totals), d_aoff, nullptr, s) != hipSuccess ||
         hipMemcpyAsync(ho, d_aoff, sizeof(ho), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return ZIPNN_E_HIP;
@@ -463,7 +463,8 @@ int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, int
         zipnn_encoder_destroy(e);
         return ZIPNN_E_HIP;
     }
-    // capture the launches and the copy of the offsets once; every run replays them
+    // capture the launches once (the placement writes the offsets to pinned
+    // memory); every run replays them
     EncParams ep = make_params(dtype, *p, any_base);
     if (stage) set_stage(ep, sc + lay.stage, dtype, *p);
     else if (total_chunks <= kFewChunks) ep.segs = (uint32_t*)(sc + lay.segs);
@@ -475,9 +476,7 @@ int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, int
     hipError_t le = launch_encode(d_descs, n, d_prefix, uint32_t(total_chunks), ep, (uint8_t*)arena, cap,
                                   (EncEntry*)(sc + lay.entries), sc + lay.codes,
                                   (uint32_t*)(sc + lay.nwords), (uint64_t*)(sc + lay.offsets),
-                                  (uint64_t*)(sc + lay.totals), d_aoff, e->capst);
-    if (le == hipSuccess)
-        le = hipMemcpyAsync(e->h_offs, d_aoff, size_t(n + 1) * sizeof(uint64_t), hipMemcpyDeviceToHost, e->capst);
+                                  (uint64_t*)(sc + lay.totals), d_aoff, e->h_offs, e->capst);
     const hipError_t ce = hipStreamEndCapture(e->capst, &e->graph);
     if (le != hipSuccess || ce != hipSuccess || hipGraphInstantiate(&e->exec, e->graph, nullptr, nullptr, 0) != hipSuccess) {
         zipnn_encoder_destroy(e);
@@ -550,8 +549,7 @@ int zipnn_decompress(zipnn_ctx ctx, const void* src, uint64_t src_len, const voi
     DeviceGuard g(ctx->device);
     hipStream_t s = (hipStream_t)stream;
     // the kernel is chosen from the header: read its 64 bytes (stream-ordered)
-    if (hipMemcpyAsync(ctx->h_total, src, 64, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
+    if (launch_fetch_header(src, ctx->h_total, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return ZIPNN_E_HIP;
     uint32_t w[16];
     memcpy(w, ctx->h_total, 64);

@@ -1180,7 +1180,14 @@ __global__ __launch_bounds__(kBlock) void k_plan(const DecDesc* __restrict__ des
     }
 }
 
-__global__ void k_clear(int* p) { *p = 0; }
+// Small results go to pinned host memory from a kernel: a copy engine's or a
+// copy kernel's turn-around is several microseconds longer.
+__global__ void k_take_status(int* p, int* host, int clear)
+{
+    *host = *p;
+    if (clear) *p = 0;
+}
+__global__ void k_fetch_header(const uint4* __restrict__ src, uint4* host) { host[threadIdx.x] = src[threadIdx.x]; }
 
 // Copy the 64-byte header of every container of an arena to `out`.
 __global__ void k_gather_headers(const uint8_t* __restrict__ arena, const uint64_t* __restrict__ offs, int n,
@@ -1280,9 +1287,15 @@ hipError_t launch_gather_headers(const uint8_t* arena, const uint64_t* d_offs, i
     return hipGetLastError();
 }
 
-hipError_t launch_clear_status(int* d_status, hipStream_t s)
+hipError_t launch_take_status(int* d_status, int* host, bool clear, hipStream_t s)
 {
-    k_clear<<<1, 1, 0, s>>>(d_status);
+    k_take_status<<<1, 1, 0, s>>>(d_status, host, clear ? 1 : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_fetch_header(const void* src, void* host, hipStream_t s)
+{
+    k_fetch_header<<<1, 4, 0, s>>>((const uint4*)src, (uint4*)host);
     return hipGetLastError();
 }
 

@@ -16,9 +16,10 @@
 //              With a probe interval the probe chunks run first
 //              (compressibility probing, §III-B).
 //   k_place    one workgroup per tensor: exclusive scan of the 128-byte aligned
-//              payload sizes in chunk-major order -> map entries and header
-//              (the map that enables parallel decode, paper §V-A), and whether
-//              the map holds ZG entries (a header flag).
+//              payload sizes in chunk-major order (the map that enables
+//              parallel decode, paper §V-A), and whether the map holds ZG
+//              entries (a header flag); the last workgroup places the
+//              containers in the arena and writes their headers.
 //   k_pack     one workgroup per chunk: raw groups are copied with 16-byte
 //              stores; for a Huffman or ZG group, wave v writes lane groups v,
 //              v+4, ...: its lanes replay the same steps, and in every round
@@ -386,20 +387,29 @@ __device__ inline __amdgpu_buffer_rsrc_t in_rsrc(const uint8_t* p, uint32_t byte
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p), (short)0, int(bytes), 0x00020000);
 }
-template <int NB>
+// Non-temporal (the cache policy bits of the buffer builtins): bytes touched
+// once and not again soon.  The packer's input and raw stores so: 256 MiB of
+// FP32 243 -> 227 us a pass, a 5 GB checkpoint 3306 -> 3216, a 1.7 GB delta
+// 1733 -> 1665; its words complete in scattered order, and their partly
+// written lines must stay (non-temporal: 4530 us).  The analysis' size pass
+// too (checkpoint 3216 -> 3101), but not its counting pass, which the size
+// pass follows (3320) -- unless there is an XOR base, where large launches
+// need no size pass (delta 1663 -> 1612).
+constexpr int kNt = 2;
+template <int NB, int AUX = 0>
 __device__ __attribute__((always_inline)) inline void buf_in(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
                                                              uint32_t* w)
 {
-    if constexpr (NB == 2) w[0] = __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
-    else if constexpr (NB == 4) w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0);
+    if constexpr (NB == 2) w[0] = __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, AUX);
+    else if constexpr (NB == 4) w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, AUX);
     else if constexpr (NB == 8) {
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, AUX);
         w[0] = v.x;
         w[1] = v.y;
     } else {
 #pragma unroll
         for (int i = 0; i < NB / 16; i++) {
-            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff + 16 * i, soff, 0);
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff + 16 * i, soff, AUX);
             w[4 * i] = v.x;
             w[4 * i + 1] = v.y;
             w[4 * i + 2] = v.z;
@@ -412,15 +422,15 @@ struct ChunkIn {
     __amdgpu_buffer_rsrc_t src, base;
     bool delta, xf;
 };
-template <int B, int NB>
+template <int B, int NB, int AUX = 0>
 __device__ __attribute__((always_inline)) inline void chunk_in(const ChunkIn& in, uint32_t voff, uint32_t soff,
                                                                uint32_t* w)
 {
     constexpr int NW = NB >= 4 ? NB / 4 : 1;
-    buf_in<NB>(in.src, voff, soff, w);
+    buf_in<NB, AUX>(in.src, voff, soff, w);
     if (in.delta) {
         uint32_t y[NW];
-        buf_in<NB>(in.base, voff, soff, y);
+        buf_in<NB, AUX>(in.base, voff, soff, y);
 #pragma unroll
         for (int x = 0; x < NW; x++) w[x] ^= y[x];
     }
@@ -589,7 +599,7 @@ __device__ __attribute__((always_inline)) void count_steps(const ChunkIn& in, co
                 constexpr uint32_t N = decltype(n_const)::value;
                 uint32_t wds[N][NW];
 #pragma unroll
-                for (uint32_t u = 0; u < N; u++) chunk_in<B, NB>(in, w * NB, (jj + u) * W * NB, wds[u]);
+                for (uint32_t u = 0; u < N; u++) chunk_in<B, NB, kNt>(in, w * NB, (jj + u) * W * NB, wds[u]);
 #pragma unroll
                 for (int k = 0; k < B; k++) {
                     if (!((hc >> k) & 1)) continue;
@@ -848,7 +858,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
         for (uint32_t v0 = v_begin; v0 < v_end; v0 += HB * NT) {
             uint32_t xs[HB][4];
 #pragma unroll
-            for (uint32_t i = 0; i < HB; i++) chunk_in<B, 16>(cin, (v0 + i * NT + t) * 16, 0, xs[i]);
+            for (uint32_t i = 0; i < HB; i++) chunk_in<B, 16, decltype(dl_const)::value ? kNt : 0>(cin, (v0 + i * NT + t) * 16, 0, xs[i]);
 #pragma unroll
             for (uint32_t i = 0; i < HB; i++)
                 if (v0 + i * NT + t < v_end) one(xs[i]);
@@ -1163,130 +1173,162 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     if (gc < total_chunks) analyze_chunk<BB, NT>(gc, descs, n_desc, chunk_prefix, p, phase, entries, lens, nwords, sh);
 }
 
-// One workgroup per tensor: offsets of its entries (128-byte aligned, in
-// chunk-major order) and the tensor's container size.
-__global__ __launch_bounds__(kBlock) void k_place(EncDesc* __restrict__ descs, EncParams p,
-                                                  EncEntry* __restrict__ entries, uint64_t* __restrict__ offsets,
-                                                  uint64_t* __restrict__ totals, const uint32_t* __restrict__ nwords)
+constexpr int kPlaceThreads = 1024;
+constexpr int kPlaceVec = 4;   // neighbouring entries per thread
+
+// Exclusive scan over the workgroup: this thread's start, `carry` advanced by
+// the total (both in every thread).
+__device__ inline uint64_t block_scan(uint64_t v, uint64_t& carry, uint64_t* red)
 {
-    __shared__ uint64_t red[kWaves];
-    __shared__ uint64_t carry;
-    __shared__ uint32_t zg;
-    const EncDesc d = descs[blockIdx.x];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    uint64_t inc = v;
+#pragma unroll
+    for (int dd = 1; dd < 64; dd <<= 1) {
+        const uint64_t o = __shfl_up(inc, dd, 64);
+        if (lane >= dd) inc += o;
+    }
+    if (lane == 63) red[wv] = inc;
+    __syncthreads();
+    uint64_t pre = carry, tot = carry;
+    for (int i = 0; i < kPlaceThreads / 64; i++) {
+        pre += i < wv ? red[i] : 0;
+        tot += red[i];
+    }
+    __syncthreads();
+    carry = tot;
+    return pre + inc - v;
+}
+
+// One workgroup per tensor: offsets of its entries (128-byte aligned, in
+// chunk-major order) and the tensor's container size.  The last workgroup to
+// finish then lays the tensors' containers out back to back in the arena
+// (each at a kPayAlign-aligned offset, in tensor order): it sets each
+// descriptor's dst, writes every header, and records the arena offsets (n+1
+// of them, in host_off too unless null: host memory).  If the arena is too
+// small nothing is written and the recorded end says so.  descs[0].pad
+// counts the workgroups; it is zero before and after.  4096 entries a round:
+// the 8016 of a checkpoint's embedding, 256 a round, took 33 us and the
+// arena 5 us in a launch of its own; now 13 us together.
+__global__ __launch_bounds__(kPlaceThreads) void k_place(EncDesc* descs, int n_desc, EncParams p, EncEntry* entries,
+                                                         uint64_t* offsets, uint64_t* totals, const uint32_t* nwords,
+                                                         uint8_t* arena, uint64_t cap, uint64_t* arena_off,
+                                                         uint64_t* host_off)
+{
+    __shared__ uint64_t red[kPlaceThreads / 64];
+    __shared__ uint32_t zg, last;
+    const EncDesc d = descs[blockIdx.x];
+    const int t = threadIdx.x;
     const uint32_t B = p.B;
     const uint64_t ne = uint64_t(d.n_chunks) * B;
     const uint64_t e_first = uint64_t(d.chunk0) * B;
-    if (t == 0) carry = 0, zg = 0;
+    uint64_t carry = 0;
+    if (t == 0) zg = 0;
     __syncthreads();
-    for (uint64_t b0 = 0; b0 < ne; b0 += kBlock) {
-        const uint64_t e = b0 + t;
-        uint64_t sz = 0;
-        if (e < ne) {
-            EncEntry en = entries[e_first + e];
-            if (p.stage && (en.mode == kModeHuf || en.mode == kModeZg)) {
-                // staged: the payload's size from the packer's word counts
-                const uint32_t E = p.chunk / B;
-                const uint32_t m = uint32_t(min(uint64_t(E), d.n - uint64_t(e / B) * E));
-                const uint32_t W = (m + p.S - 1) / p.S, NG = (W + 63) / 64;
-                uint32_t words = 0;
-                for (uint32_t j = 0; j < NG; j++) words += nwords[(e_first + e) * 64 + j];
-                en.bytes = huf_head(W) + (en.mode == kModeZg ? zg_bitmap(m, p.g) : 0u) + 4 * words;
-                entries[e_first + e].bytes = en.bytes;
+    for (uint64_t b0 = 0; b0 < ne; b0 += kPlaceThreads * kPlaceVec) {
+        const uint64_t e0 = b0 + uint64_t(t) * kPlaceVec;
+        uint64_t sz[kPlaceVec], sum = 0;
+#pragma unroll
+        for (int v = 0; v < kPlaceVec; v++) {
+            const uint64_t e = e0 + v;
+            sz[v] = 0;
+            if (e < ne) {
+                EncEntry en = entries[e_first + e];
+                if (p.stage && (en.mode == kModeHuf || en.mode == kModeZg)) {
+                    // staged: the payload's size from the packer's word counts
+                    const uint32_t E = p.chunk / B;
+                    const uint32_t m = uint32_t(min(uint64_t(E), d.n - uint64_t(e / B) * E));
+                    const uint32_t W = (m + p.S - 1) / p.S, NG = (W + 63) / 64;
+                    uint32_t words = 0;
+                    for (uint32_t j = 0; j < NG; j++) words += nwords[(e_first + e) * 64 + j];
+                    en.bytes = huf_head(W) + (en.mode == kModeZg ? zg_bitmap(m, p.g) : 0u) + 4 * words;
+                    entries[e_first + e].bytes = en.bytes;
+                }
+                sz[v] = align_pay(en.bytes);
+                if (en.mode == kModeZg) zg = 1;
             }
-            sz = align_pay(en.bytes);
-            if (en.mode == kModeZg) zg = 1;
+            sum += sz[v];
         }
-        uint64_t inc = sz;
+        uint64_t at = block_scan(sum, carry, red);
 #pragma unroll
-        for (int dd = 1; dd < 64; dd <<= 1) {
-            uint64_t o = __shfl_up(inc, dd, 64);
-            if (lane >= dd) inc += o;
+        for (int v = 0; v < kPlaceVec; v++) {
+            if (e0 + v < ne) offsets[e_first + e0 + v] = at;
+            at += sz[v];
         }
-        if (lane == 63) red[wv] = inc;
-        __syncthreads();
-        uint64_t pre = carry;
-        for (int i = 0; i < wv; i++) pre += red[i];
-        if (e < ne) offsets[e_first + e] = pre + inc - sz;
-        __syncthreads();
-        if (t == kBlock - 1) carry = pre + inc;
-        __syncthreads();
-    }
-    if (t == 0) {
-        totals[blockIdx.x] = payload_base_of(d.n_chunks, B) + carry;
-        descs[blockIdx.x].has_zg = zg;
-    }
-}
-
-// One workgroup: the tensors' containers are laid out back to back in the
-// arena (each at a kPayAlign-aligned offset, in tensor order); sets each descriptor's dst,
-// writes every header, and records the arena offsets (n+1 of them).  If the
-// arena is too small nothing is written and the recorded end says so.
-__global__ __launch_bounds__(kBlock) void k_arena(EncDesc* __restrict__ descs, int n_desc, EncParams p,
-                                                  uint8_t* __restrict__ arena, uint64_t cap,
-                                                  const uint64_t* __restrict__ totals,
-                                                  uint64_t* __restrict__ arena_off)
-{
-    __shared__ uint64_t red[kWaves];
-    __shared__ uint64_t carry;
-    __shared__ uint64_t end_sh;
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const uint32_t B = p.B;
-    // pass 1: offsets
-    if (t == 0) carry = 0;
-    __syncthreads();
-    for (int b0 = 0; b0 < n_desc; b0 += kBlock) {
-        const int i = b0 + t;
-        const uint64_t sz = i < n_desc ? align_pay(totals[i]) : 0;
-        uint64_t inc = sz;
-#pragma unroll
-        for (int dd = 1; dd < 64; dd <<= 1) {
-            uint64_t o = __shfl_up(inc, dd, 64);
-            if (lane >= dd) inc += o;
-        }
-        if (lane == 63) red[wv] = inc;
-        __syncthreads();
-        uint64_t pre = carry;
-        for (int w = 0; w < wv; w++) pre += red[w];
-        if (i < n_desc) arena_off[i] = pre + inc - sz;
-        __syncthreads();
-        if (t == kBlock - 1) carry = pre + inc;
-        __syncthreads();
-    }
-    if (t == 0) {
-        // the last container needs only its own bytes, not the alignment
-        end_sh = n_desc ? arena_off[n_desc - 1] + totals[n_desc - 1] : 0;
-        arena_off[n_desc] = end_sh;
     }
     __syncthreads();
-    const bool fits = end_sh <= cap;
-    for (int i = t; i < n_desc; i += kBlock) {
-        EncDesc d = descs[i];
-        d.dst = arena + arena_off[i];
-        d.dst_cap = fits ? totals[i] : 0;   // pack skips tensors whose dst_cap is short
-        descs[i] = d;
-        if (!fits) continue;
-        const uint64_t total = totals[i];
+    const uint64_t total1 = payload_base_of(d.n_chunks, B) + carry;
+    if (t == 0) {
+        totals[blockIdx.x] = total1;
+        if (n_desc > 1) {
+            descs[blockIdx.x].has_zg = zg;
+            __threadfence();
+            last = atomicAdd(&descs[0].pad, 1u) == uint32_t(n_desc) - 1;
+        }
+    }
+    // a tensor's container: descriptor and header
+    auto write_header = [&](int i, EncDesc x, uint64_t total, uint64_t at, bool fits) {
+        x.dst = arena + at;
+        x.dst_cap = fits ? total : 0;   // pack skips tensors whose dst_cap is short
+        x.pad = 0;
+        descs[i] = x;
+        if (!fits) return;
         uint32_t h[16];
         h[0] = 0x314E4E5Au;
         h[1] = 1u | (p.dtype << 16) | (B << 24);
-        h[2] = uint32_t(d.n);
-        h[3] = uint32_t(d.n >> 32);
+        h[2] = uint32_t(x.n);
+        h[3] = uint32_t(x.n >> 32);
         h[4] = p.chunk;
         h[5] = p.S | (p.g << 16) | (p.L << 24);
-        h[6] = (d.base ? kFlagDelta : 0u) | (d.has_zg ? kFlagZg : 0u) | (p.flags & kFlagExp);
-        h[7] = d.n_chunks;
+        h[6] = (x.base ? kFlagDelta : 0u) | (x.has_zg ? kFlagZg : 0u) | (p.flags & kFlagExp);
+        h[7] = x.n_chunks;
         h[8] = uint32_t(total);
         h[9] = uint32_t(total >> 32);
         h[10] = 0;
         for (uint32_t k = 0; k < B; k++) h[10] |= uint32_t(p.policy[k]) << (8 * k);
         h[11] = p.skip;   // byte 44: the probe interval
-        for (int x = 12; x < 16; x++) h[x] = 0;
-        uint4* o = (uint4*)d.dst;
-        for (int x = 0; x < 4; x++) o[x] = make_uint4(h[4 * x], h[4 * x + 1], h[4 * x + 2], h[4 * x + 3]);
+        for (int y = 12; y < 16; y++) h[y] = 0;
+        uint4* o = (uint4*)x.dst;
+        for (int y = 0; y < 4; y++) o[y] = make_uint4(h[4 * y], h[4 * y + 1], h[4 * y + 2], h[4 * y + 3]);
         // zero padding between the map and the aligned payload area
-        const uint64_t map_end = 64 + 16ull * d.n_chunks * B, pb = payload_base_of(d.n_chunks, B);
-        for (uint64_t x = map_end / 16; x < pb / 16; x++) o[x] = make_uint4(0, 0, 0, 0);
+        const uint64_t map_end = 64 + 16ull * x.n_chunks * B, pb = payload_base_of(x.n_chunks, B);
+        for (uint64_t y = map_end / 16; y < pb / 16; y++) o[y] = make_uint4(0, 0, 0, 0);
+    };
+    if (n_desc == 1) {   // nothing to wait for or read back
+        if (t == 0) {
+            arena_off[0] = 0;
+            arena_off[1] = total1;
+            if (host_off) host_off[0] = 0, host_off[1] = total1;
+            EncDesc x = d;
+            x.has_zg = zg;
+            write_header(0, x, total1, 0, total1 <= cap);
+        }
+        return;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    carry = 0;
+    uint64_t end = 0;   // the last container needs only its own bytes, not the alignment
+    for (int b0 = 0; b0 < n_desc; b0 += kPlaceThreads) {
+        const int i = b0 + t;
+        const uint64_t total = i < n_desc ? totals[i] : 0;
+        const uint64_t at = block_scan(align_pay(total), carry, red);
+        if (i < n_desc) {
+            arena_off[i] = at;
+            if (host_off) host_off[i] = at;
+        }
+        if (i == n_desc - 1) red[0] = at + total;
+        __syncthreads();
+        if (b0 + kPlaceThreads >= n_desc) end = red[0];
+        __syncthreads();
+    }
+    if (t == 0) {
+        arena_off[n_desc] = end;
+        if (host_off) host_off[n_desc] = end;
+    }
+    const bool fits = end <= cap;
+    for (int i = t; i < n_desc; i += kPlaceThreads) {
+        write_header(i, descs[i], totals[i], arena_off[i], fits);
     }
 }
 
@@ -1487,8 +1529,8 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
                     const uint32_t roff = __builtin_amdgcn_readfirstlane(uint32_t(P.pay[r] - P.pay[0]));
                     if (FAST || ecnt == G) {
                         const uint32_t v = gather_stream<B, G>(wd, r);
-                        if constexpr (G == 2) __builtin_amdgcn_raw_buffer_store_b16(uint16_t(v), rr, q0, roff, 0);
-                        else __builtin_amdgcn_raw_buffer_store_b32(v, rr, q0, roff, 0);
+                        if constexpr (G == 2) __builtin_amdgcn_raw_buffer_store_b16(uint16_t(v), rr, q0, roff, kNt);
+                        else __builtin_amdgcn_raw_buffer_store_b32(v, rr, q0, roff, kNt);
                     } else {
                         for (uint32_t i = 0; i < ecnt; i++)
                             __builtin_amdgcn_raw_buffer_store_b8(uint8_t(sym_of<B>(wd, r, int(i))), rr, q0 + i, roff,
@@ -1532,8 +1574,8 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
     };
     Fetch pf[kPf];
     auto load = [&](uint32_t e, Fetch& f) __attribute__((always_inline)) {
-        buf_in<NB>(rsrc, w_in + e * W * NB, 0, f.x);
-        if constexpr (XB) buf_in<NB>(rbase, w_in + e * W * NB, 0, f.y);
+        buf_in<NB, kNt>(rsrc, w_in + e * W * NB, 0, f.x);
+        if constexpr (XB) buf_in<NB, kNt>(rbase, w_in + e * W * NB, 0, f.y);
     };
     auto words = [&](const Fetch& f, uint32_t* wd) __attribute__((always_inline)) {
 #pragma unroll
@@ -1964,7 +2006,8 @@ hipError_t launch_fill_desc(const EncDesc& one, uint32_t total_chunks, EncDesc* 
 
 hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_prefix, uint32_t total_chunks,
                          const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, uint8_t* lens,
-                         uint32_t* nwords, uint64_t* offsets, uint64_t* totals, uint64_t* arena_off, hipStream_t s)
+                         uint32_t* nwords, uint64_t* offsets, uint64_t* totals, uint64_t* arena_off,
+                         uint64_t* host_off, hipStream_t s)
 {
     const dim3 grid = chunk_grid(total_chunks);
     const bool xb = (p.flags & kFlagDelta) != 0;   // some tensor has an XOR base
@@ -2029,9 +2072,8 @@ hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_p
         const hipError_t e = pack_or_compact(false);
         if (e != hipSuccess) return e;
     }
-    k_place<<<n_desc, kBlock, 0, s>>>(d_descs, p, entries, offsets, totals, nwords);
-    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    k_arena<<<1, kBlock, 0, s>>>(d_descs, n_desc, p, arena, cap, totals, arena_off);
+    k_place<<<n_desc, kPlaceThreads, 0, s>>>(d_descs, n_desc, p, entries, offsets, totals, nwords, arena, cap,
+                                             arena_off, host_off);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     return pack_or_compact(staged);
 }

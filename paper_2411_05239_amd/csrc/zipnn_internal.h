@@ -169,7 +169,7 @@ struct EncDesc {
     uint32_t chunk0;       // index of this tensor's first chunk in the scratch arrays
     uint32_t n_chunks;
     uint32_t has_zg;       // set by the placement kernel: some entry is ZG
-    uint32_t pad;
+    uint32_t pad;          // descriptor 0: the placement kernel's count of finished tensors, zero between launches
 };
 
 // Per-(chunk, stream) result of the analysis kernel.
@@ -281,7 +281,10 @@ hipError_t launch_decode_batch(const DecClass& k, const DecDesc* d_descs, int n_
 // counter, zero at launch (n_desc + 2 entries).
 hipError_t launch_decode_planned(const DecClass& k, const DecDesc* d_descs, int n_desc, uint64_t* d_item_prefix,
                                  int* d_status, int grid, hipStream_t s);
-hipError_t launch_clear_status(int* d_status, hipStream_t s);
+// Write the status to *host (pinned host memory) and clear it if asked to.
+hipError_t launch_take_status(int* d_status, int* host, bool clear, hipStream_t s);
+// Copy a 64-byte header (16-byte aligned) to pinned host memory.
+hipError_t launch_fetch_header(const void* src, void* host, hipStream_t s);
 hipError_t launch_gather_headers(const uint8_t* arena, const uint64_t* d_offs, int n, void* d_out, hipStream_t s);
 int decode_grid_size(int device, const DecClass& k);
 // Index of a kernel class in per-class tables (B in {1,2,4}, G in {2,4,8}).
@@ -294,11 +297,13 @@ __host__ __device__ inline int dec_class_index(const DecClass& k)
 }
 
 // Compress n_desc tensors (descriptors and chunk prefix in device memory)
-// into `arena`: analyze -> place -> arena layout (dst of every descriptor,
-// headers, arena_off[n_desc+1]) -> pack (maps and payloads).
+// into `arena`: analyze -> place and arena layout (dst of every descriptor,
+// headers, arena_off[n_desc+1], written to host_off too unless null: pinned
+// host memory) -> pack (maps and payloads).
 hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_prefix, uint32_t total_chunks,
                          const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, uint8_t* lens,
-                         uint32_t* nwords, uint64_t* offsets, uint64_t* totals, uint64_t* arena_off, hipStream_t s);
+                         uint32_t* nwords, uint64_t* offsets, uint64_t* totals, uint64_t* arena_off, uint64_t* host_off,
+                         hipStream_t s);
 
 hipError_t launch_fill_desc(const EncDesc& one, uint32_t total_chunks, EncDesc* d_desc, uint32_t* d_prefix,
                             hipStream_t s);
