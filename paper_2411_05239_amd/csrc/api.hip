@@ -530,6 +530,8 @@ static int decompress_common(zipnn_ctx ctx, const uint32_t* hdr_words, const voi
     one.c_begin = 0;
     one.c_end = kAllChunks;
     one.status = nullptr;
+    one.zg = (h.flags & kFlagZg) ? 1 : 0;
+    one.pad = 0;
     // no more workgroups than items: a small tensor does not dispatch the
     // whole persistent grid
     const uint64_t items = plan_items(h, 0, kAllChunks).items;
@@ -641,7 +643,29 @@ int zipnn_batch_create(zipnn_ctx ctx, const void* arena, const uint64_t* offsets
         d.c_begin = 0;
         d.c_end = kAllChunks;
         d.status = nullptr;
-        groups[std::make_tuple(h.B, h.g, delta, (h.flags & kFlagZg) != 0)].push_back(d);
+        d.zg = (h.flags & kFlagZg) ? 1 : 0;
+        d.pad = 0;
+        groups[std::make_tuple(h.B, h.g, delta, d.zg != 0)].push_back(d);
+    }
+    // A few plain containers beside many with ZG entries (the norm vectors of
+    // a delta checkpoint) join their launch: alone they are a launch that
+    // lasts one item's latency (65 us of a 1.7 GB delta's 920).  The ZG
+    // kernels run plain containers with fewer registers to spare, so only up
+    // to an eighth of the bytes.
+    for (auto it = groups.begin(); it != groups.end();) {
+        const auto& k = it->first;
+        auto zgs = groups.find(std::make_tuple(std::get<0>(k), std::get<1>(k), std::get<2>(k), true));
+        auto bytes = [](const std::vector<DecDesc>& v) {
+            uint64_t b = 0;
+            for (const auto& d : v) b += d.dst_cap;
+            return b;
+        };
+        if (std::get<3>(k) || zgs == groups.end() || bytes(it->second) > bytes(zgs->second) / 8) {
+            ++it;
+            continue;
+        }
+        zgs->second.insert(zgs->second.begin(), it->second.begin(), it->second.end());
+        it = groups.erase(it);
     }
     zipnn_batch b = new (std::nothrow) zipnn_batch_s;
     if (!b) return ZIPNN_E_NOMEM;

@@ -1045,9 +1045,9 @@ __device__ __attribute__((always_inline)) void decode_item(const DecDesc& d, con
 
 // `descs` == nullptr: decode the single tensor `one`; otherwise the batch
 // descs[0..n_desc) whose per-tensor item counts k_plan prefixed.  Every tensor
-// of a launch has B-byte words, groups of G, (for DELTA) an XOR base and (for
-// ZGK) the header's ZG flag; a header that disagrees is reported as
-// ZIPNN_E_FORMAT.  With `work` (batched launches) a workgroup takes its next
+// of a launch has B-byte words, groups of G, (for DELTA) an XOR base and the
+// ZG flag that its descriptor says (none without ZGK); a header that
+// disagrees is reported as ZIPNN_E_FORMAT.  With `work` (batched launches) a workgroup takes its next
 // item from that counter, zero at launch, as it finishes one: against items
 // handed out grid-stride, the checkpoint decoded 4-9% faster and its deltas
 // 7-8%, since workgroups do not run at one speed.  A single-tensor launch
@@ -1078,15 +1078,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(B * G >=
         n_desc = 1;
         item_prefix = nullptr;
     }
-    auto matches = [&](const TensorState& x) {
+    auto matches = [&](const TensorState& x, const DecDesc& d) {
+        const bool zg = (x.h.flags & kFlagZg) != 0;
         return x.h.B == uint32_t(B) && x.h.g == uint32_t(G) && ((x.h.flags & kFlagDelta) != 0) == DELTA &&
-               ((x.h.flags & kFlagZg) != 0) == ZGK;
+               zg == (d.zg != 0) && (ZGK || !zg);
     };
     if (threadIdx.x == 0) {
         ts.desc = -1;
         if (item_prefix == nullptr) {
             const bool ok = load_tensor(descs[0], 0, ts, status, blockIdx.x == 0);
-            if (ok && !matches(ts)) {
+            if (ok && !matches(ts, descs[0])) {
                 ts.valid = 0;
                 if (blockIdx.x == 0) set_status(status, ZIPNN_E_FORMAT);
             }
@@ -1122,7 +1123,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(B * G >=
                     // when planned; a container changed since then is
                     // reported and its items are skipped
                     const DecDesc& dl = descs[lo];
-                    if (load_tensor(dl, lo, ts, status, false) && !matches(ts)) ts.valid = 0;
+                    if (load_tensor(dl, lo, ts, status, false) && !matches(ts, dl)) ts.valid = 0;
                     if (!ts.valid) set_status(dl.status ? dl.status : status, ZIPNN_E_FORMAT);
                 }
             }
@@ -1161,7 +1162,7 @@ __global__ __launch_bounds__(kBlock) void k_plan(const DecDesc* __restrict__ des
         if (i < n_desc && load_tensor(descs[i], i, tsv[threadIdx.x], status, true)) {
             const Header& h = tsv[threadIdx.x].h;
             const DecClass x = dec_class(h);
-            if (x.B != k.B || x.G != k.G || x.delta != k.delta || x.zg != k.zg) {
+            if (x.B != k.B || x.G != k.G || x.delta != k.delta || x.zg != (descs[i].zg != 0) || (x.zg && !k.zg)) {
                 tsv[threadIdx.x].valid = 0;
                 set_status(status, ZIPNN_E_FORMAT);
             }

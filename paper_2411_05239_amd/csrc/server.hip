@@ -254,6 +254,8 @@ bool launch_iteration(zipnn_server s)
         d.c_begin = r.next;
         d.c_end = r.next + tk.second;
         d.status = nullptr;   // set once the buffer layout is known
+        d.zg = (e.h.flags & kFlagZg) ? 1 : 0;
+        d.pad = 0;
         const DecClass k = dec_class(e.h);
         Class& c = classes[std::make_tuple(k.B, k.G, k.delta, k.zg)];
         const uint64_t items = plan_items(e.h, d.c_begin, d.c_end).items;

@@ -156,6 +156,8 @@ struct DecDesc {
     uint32_t c_begin;      // chunks [c_begin, min(c_end, n_chunks)) are decoded
     uint32_t c_end;
     int* status;           // where corruption found in its chunks is reported (nullptr: the launch's)
+    uint32_t zg;           // the ZG flag its header had when the launch was prepared
+    uint32_t pad;
 };
 constexpr uint32_t kAllChunks = 0xFFFFFFFFu;
 
@@ -261,7 +263,8 @@ __host__ __device__ inline ItemPlan plan_items(const Header& h, uint32_t c_begin
 // Launchers (decode.hip / encode.hip).  A null descriptor array means "the
 // single tensor passed by value".
 // Decode kernels are specialised on (B, g, delta, zg) taken from the header
-// (zg: the header's ZG flag; only those kernels carry the ZG decoder).
+// (zg: the header's ZG flag; only those kernels carry the ZG decoder, and
+// they decode containers without the flag too).
 struct DecClass {
     uint32_t B, G;
     bool delta, zg;
