@@ -345,7 +345,7 @@ int zipnn_autotune(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* tensors, int
  * outputs are placed in a device pool of fixed size owned by the server.
  * Requests are admitted in arrival order while the pool has room for the
  * output (and fewer than max_inflight are admitted).  A scheduler thread
- * runs decode iterations on a private stream, keeping two in flight: in
+ * runs decode iterations on private streams, keeping two in flight: in
  * ZIPNN_SERVE_CONTINUOUS mode, when more requests are admitted than can
  * each have an iteration in flight, an iteration takes them whole: the
  * oldest, then the others with the fewest chunks first while they fit under
