@@ -309,8 +309,53 @@ __device__ __attribute__((always_inline)) uint32_t build_lengths(const uint32_t*
 // 2^-18 of the truth, so the terms err by under 10^-5 bits per symbol in all,
 // and rounding the products and the sum errs by under 10^-6 of the sum; the
 // margins below (10^-4 relative, 10^-4 bits per symbol) keep the bound a lower
-// bound.  Near the boundary the code is built and sized exactly.
-__device__ inline bool entropy_says_raw(const uint32_t* fv, uint32_t tot, uint32_t head, uint32_t raw)
+// bound.
+//
+// Near the boundary (within 1/32 of the raw bytes) whole code lengths give a
+// closer bound, by weak duality: for any price mu of code space, lengths l in
+// 1..L with sum 2^-l <= 1 cost sum f l >= sum min_l (f l + mu 2^-l) - mu.  The
+// best mu lies between tot and 2 tot (each term's best l has mu 2^-(l+1) <= f <
+// mu 2^-l) and is bisected on the sum of 2^-l; every mu tried gives a valid
+// bound, in whole numbers (mu a multiple of 2^L).  The fraction byte of BF16
+// weights, whose best code is 46 bytes under 128 KiB, is settled here in about
+// 3000 cycles instead of a construction of 20000.  What is still open is
+// built and sized exactly.
+__device__ __attribute__((always_inline)) inline bool lengths_say_raw(const uint32_t* fv, uint32_t tot, uint32_t head,
+                                                                      uint32_t raw, uint32_t L)
+{
+    float lf[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) lf[r] = __log2f(float(fv[r]));
+    uint32_t lo = tot, hi = 2 * tot;
+    for (int it = 0; it < 10 && hi - lo > 2 << kMaxL; it++) {
+        const uint32_t mu = ((lo + hi) / 2) & ~((1u << kMaxL) - 1);
+        const float lm = __log2f(float(mu));
+        uint32_t v = 0, space = 0;   // space: sum of 2^(kMaxL - l)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            if (!fv[r]) continue;
+            // the best length is the quotient's logarithm rounded down, or
+            // one off where the logarithms round
+            const int l0 = int(lm - lf[r]);
+            uint32_t best = ~0u, bl = 1;
+#pragma unroll
+            for (int d = -1; d <= 1; d++) {
+                const uint32_t l = uint32_t(min(max(l0 + d, 1), int(L)));
+                const uint32_t c = fv[r] * l + (mu >> l);
+                if (c < best) best = c, bl = l;
+            }
+            v += best;
+            space += (1u << kMaxL) >> bl;
+        }
+        v = wave_sum(v);
+        space = wave_sum(space);
+        if (v > mu && uint64_t(head) + (v - mu + 7) / 8 >= raw) return true;
+        if (space > 1u << kMaxL) lo = mu;
+        else hi = mu;
+    }
+    return false;
+}
+__device__ inline bool entropy_says_raw(const uint32_t* fv, uint32_t tot, uint32_t head, uint32_t raw, uint32_t L)
 {
     const float lt = __log2f(float(tot));
     float h = 0.0f;
@@ -320,7 +365,9 @@ __device__ inline bool entropy_says_raw(const uint32_t* fv, uint32_t tot, uint32
     h = wave_fsum(h);
     const float lb = h * (1.0f - 1e-4f) - 1e-4f * float(tot) - 1.0f;
     const uint64_t words_lb = lb > 0.0f ? uint64_t(lb / 32.0f) : 0u;   // floor: a lower bound too
-    return uint64_t(head) + 4 * words_lb >= raw;
+    const uint64_t bound = uint64_t(head) + 4 * words_lb;
+    if (bound >= raw) return true;
+    return bound + raw / 32 >= raw && lengths_say_raw(fv, tot, head, raw, L);
 }
 
 // One workgroup per chunk over a two-dimensional grid (chunk_grid).  A loop
@@ -722,7 +769,7 @@ struct AnalyzeShared {
 
 // The analysis of chunk gc by one workgroup (steps 1-5 above); a chunk that
 // the probing phase leaves to the other launch is passed over.
-template <int BB, int NT>
+template <int BB, int NT, int HOLD>
 __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const EncDesc* __restrict__ descs,
                                                              int n_desc, const uint32_t* __restrict__ chunk_prefix,
                                                              const EncParams& p, int phase,
@@ -783,8 +830,10 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
     // this lane's copy of the counters: B = 1 counts in 32 bits, else byte
     // groups 2a and 2a+1 in the halves of array a
     const uint32_t copy = uint32_t(lane) % kCopies;
-    auto add = [&](uint32_t k, uint32_t v) __attribute__((always_inline)) {
-        atomicAdd(&S.copies[k / 2][v][copy], (B > 1 && (k & 1)) ? 0x10000u : 1u);
+    // counts byte jb (of a run of whole little-endian words starting at x)
+    auto add = [&](const uint32_t* x, int jb) __attribute__((always_inline)) {
+        const uint32_t k = B - 1 - uint32_t(jb) % B;   // byte jb%B of a word -> stream B-1-jb%B
+        atomicAdd(&S.copies[k / 2][(x[jb >> 2] >> (8 * (jb & 3))) & 0xFFu][copy], (B > 1 && (k & 1)) ? 0x10000u : 1u);
     };
     // Delta-like groups (zero bytes in at least half of the first 64 vectors;
     // the same vectors in every wave, so the choice is uniform) also count, in
@@ -826,10 +875,8 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
         auto one = [&](const uint32_t* x) __attribute__((always_inline)) {
 #pragma unroll
             for (int jb = 0; jb < 16; jb++) {
-                const uint32_t byte = (x[jb >> 2] >> (8 * (jb & 3))) & 0xFFu;
-                const int k = int(B) - 1 - (jb % int(B));   // byte jb%B of a word -> stream B-1-jb%B
-                if (!LV && !((live >> k) & 1)) continue;
-                add(uint32_t(k), byte);
+                if (!LV && !((live >> (int(B) - 1 - (jb % int(B)))) & 1)) continue;
+                add(x, jb);
             }
             if constexpr (SP) {
 #pragma unroll
@@ -864,11 +911,49 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
                 if (v0 + i * NT + t < v_end) one(xs[i]);
         }
     };
+    // HOLD > 0: a full chunk of HOLD groups of 4 per thread, which its size
+    // pass would give to the same threads (wave wv: range wv / NG of the steps
+    // of lane group wv % NG), is read in that order, and the bytes of its
+    // first streams stay in registers for the size pass.
+    constexpr int kHeld = HOLD ? (BB == 4 ? 2 : 1) : 1;
+    constexpr int kHoldN = HOLD ? HOLD : 1;
+    uint32_t hold[kHeld][kHoldN];
+    bool held = false;
+    if constexpr (HOLD > 0) {
+        held = m == uint32_t(HOLD) * 4 * NT && W % 64 == 0 && NG <= uint32_t(kWavesA) && kWavesA % NG == 0 &&
+               live == (1u << B) - 1 && spec == 0 && !in.delta && !xf;
+        if (held) {
+            constexpr int NB = BB * 4, NW = NB / 4;
+            constexpr int FB = 16 / NW;   // groups in flight
+            const uint32_t q0 = 64 * (uint32_t(wv) % NG) + (uint32_t(wv) / NG) * HOLD * W;
+            uint32_t wd[2][FB][NW];
+            auto fetch = [&](int i0, uint32_t (*x)[NW]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < FB; u++) buf_in<NB, kNt>(in.src, lane * NB, (q0 + (i0 + u) * W) * NB, x[u]);
+            };
+            fetch(0, wd[0]);
+#pragma unroll
+            for (int i0 = 0; i0 < HOLD; i0 += FB) {
+                uint32_t(*x)[NW] = wd[(i0 / FB) & 1];
+                if (i0 + FB < HOLD) fetch(i0 + FB, wd[(i0 / FB + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);   // the next batch is on its way, and no more than that
+#pragma unroll
+                for (int u = 0; u < FB; u++) {
+#pragma unroll
+                    for (int jb = 0; jb < NB; jb++) add(x[u], jb);
+#pragma unroll
+                    for (int k = 0; k < kHeld; k++) hold[k][i0 + u] = gather_stream<BB, 4>(x[u], k);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
     for (uint32_t part = 0;; part += kPartVec) {
         const uint32_t v_end = min(nvec, part + kPartVec);
         using T = std::integral_constant<bool, true>;
         using F = std::integral_constant<bool, false>;
-        if (live != (1u << B) - 1) in.delta ? count(F{}, T{}, T{}, part, v_end) : count(F{}, T{}, F{}, part, v_end);
+        if (held) ;
+        else if (live != (1u << B) - 1) in.delta ? count(F{}, T{}, T{}, part, v_end) : count(F{}, T{}, F{}, part, v_end);
         else if (spec) in.delta ? count(T{}, T{}, T{}, part, v_end) : count(T{}, T{}, F{}, part, v_end);
         else in.delta ? count(T{}, F{}, T{}, part, v_end) : count(T{}, F{}, F{}, part, v_end);
         const bool done = v_end == nvec;
@@ -876,7 +961,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
             for (uint32_t e = nvec * 16 / B + t; e < m; e += NT) {
                 const uint32_t v = element_word<B>(src, base, e, xf);
                 for (uint32_t b = 0; b < B; b++)
-                    if ((live >> (B - 1 - b)) & 1) add(B - 1 - b, (v >> (8 * b)) & 0xFFu);
+                    if ((live >> (B - 1 - b)) & 1) add(&v, int(b));
             }
         __syncthreads();
         // the copies of a bin: kPer neighbouring threads sum kEach counters each
@@ -940,7 +1025,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
                 entries[uint64_t(gc) * B + k] = e;
             }
         } else {
-            const bool huf = policy == ZIPNN_HUF || (policy == ZIPNN_AUTO && !entropy_says_raw(fv, m, head, m));
+            const bool huf = policy == ZIPNN_HUF || (policy == ZIPNN_AUTO && !entropy_says_raw(fv, m, head, m, p.L));
             const bool zc = policy == ZIPNN_ZG || (policy == ZIPNN_AUTO && 2 * (best >> 8) >= m);
             if (lane == 0) {
                 atomicOr(&A.open, 1u << k);
@@ -982,7 +1067,7 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
                 nd += __popcll(__ballot(fv[r] > 0));
             }
             tot = wave_sum(tot);
-            const bool zg = nd >= 2 && !(A.pol[k] == ZIPNN_AUTO && entropy_says_raw(fv, tot, head_z, m));
+            const bool zg = nd >= 2 && !(A.pol[k] == ZIPNN_AUTO && entropy_says_raw(fv, tot, head_z, m, p.L));
             if (lane == 0) {
                 A.zn[k] = zn;
                 if (zg) atomicOr(&A.build[1], 1u << k);
@@ -1059,13 +1144,44 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
             default: count_steps<BB, 8>(in, src, base, hc, zgc, A.lens, A.lens2, A.z, j, s0, s1, W, m, out, xf); break;
             }
         };
+        // the sums of the streams held in registers, if they are all there is
+        bool from_held = false;
+        uint32_t hsum[kHeld];
+#pragma unroll
+        for (int k = 0; k < kHeld; k++) hsum[k] = 0;
+        if constexpr (HOLD > 0) {
+            from_held = held && zgc == 0 && (hc >> kHeld) == 0;
+            if (from_held) {
+#pragma unroll
+                for (int k = 0; k < kHeld; k++) {
+                    if (!((hc >> k) & 1)) continue;
+                    uint32_t bits = 0, last = 0;
+#pragma unroll
+                    for (int i0 = 0; i0 < HOLD; i0 += 4) {
+                        uint32_t e[16];
+#pragma unroll
+                        for (int i = 0; i < 16; i++)
+                            e[i] = A.lens[k][(hold[k][i0 + i / 4] >> (8 * (i % 4))) & 0xFFu];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int i = 0; i < 16; i++) bits += e[i];
+                        last = e[14] + e[15];
+                    }
+                    hsum[k] = (bits << 5) | last;
+                }
+            }
+        }
         // wave wv: range wv / NG of lane group wv % NG, or (nseg = 1) all of
         // lane groups wv, wv + kWavesA, ...
         for (uint32_t j0 = 0; j0 < NG; j0 += kWavesA) {
             const uint32_t sg = nseg > 1 ? uint32_t(wv) / NG : 0u, j = nseg > 1 ? uint32_t(wv) % NG : j0 + wv;
             uint32_t out[2][BB];
             const bool mine = nseg > 1 ? sg < nseg : j < NG;
-            if (mine) steps_of(j, sg * per, min(steps, (sg + 1) * per), out);
+            if (from_held) {
+#pragma unroll
+                for (int k = 0; k < BB; k++) out[0][k] = k < kHeld ? hsum[k < kHeld ? k : 0] : 0u, out[1][k] = 0;
+            }
+            if (mine && !from_held) steps_of(j, sg * per, min(steps, (sg + 1) * per), out);
             if (nseg > 1) {
                 if (mine) {
 #pragma unroll
@@ -1155,22 +1271,25 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
     __syncthreads();
 }
 
-// What bounds it: on full launches the two reads of every chunk (the counting
-// and the size pass; the second one misses L2, and the last-level cache serves
-// it at 7.5 TB/s against HBM's 6.2).  5 GB of an 8B checkpoint (BF16, 256 KiB
-// chunks) take 1.43 ms, 7.0 TB/s of both reads; four waves per chunk with
-// one wave building each code in LDS took 3.45 ms.  On small launches, the
-// chain count - code - sizes of one chunk: an 8 KiB tensor 98 -> 16 us, 32
-// chunks 146 -> 25 us.  The waves that classify and build codes run at raised
-// priority: the others wait for them.
-template <int BB, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_analyze(
+// What bounds it: on full launches without HOLD the two reads of every chunk
+// (the counting and the size pass; the second one misses L2, and the
+// last-level cache serves it at 7.5 TB/s against HBM's 6.2): 5 GB of an 8B
+// checkpoint (BF16, 256 KiB chunks) 1.37 ms, 7.3 TB/s of both reads.  With
+// HOLD one read, 1.13 ms, and the waves of a CU halved by the registers: the
+// chain of a chunk's phases shows.  (Four waves per chunk, one wave building
+// each code in LDS, took 3.45 ms.)  256 MiB of FP32: 240, 108 and 72 us.  On
+// small launches the chain count - code - sizes of one chunk: an 8 KiB tensor
+// 98 -> 14 us, 32 chunks 146 -> 26 us.  The waves that classify and build
+// codes run at raised priority: the others wait for them.
+template <int BB, int NT, int HOLD>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(HOLD ? 4 : 8, 8))) void k_analyze(
     const EncDesc* __restrict__ descs, int n_desc, const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
     EncParams p, int phase, EncEntry* __restrict__ entries, uint8_t* __restrict__ lens, uint32_t* __restrict__ nwords)
 {
     __shared__ AnalyzeShared<BB, NT> sh;
     const uint32_t gc = chunk_of_block();
-    if (gc < total_chunks) analyze_chunk<BB, NT>(gc, descs, n_desc, chunk_prefix, p, phase, entries, lens, nwords, sh);
+    if (gc < total_chunks)
+        analyze_chunk<BB, NT, HOLD>(gc, descs, n_desc, chunk_prefix, p, phase, entries, lens, nwords, sh);
 }
 
 constexpr int kPlaceThreads = 1024;
@@ -2021,22 +2140,25 @@ hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_p
             // CU, overlap more phases (5 GB of BF16: 3.27 against 3.39 ms a
             // pass; 32 chunks: equal within 1%)
             const bool many = p.segs == nullptr;
-#define ZIPNN_ANALYZE(B_)                                                                                            \
-    if (many)                                                                                                        \
-        k_analyze<B_, 512><<<grid, 512, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries,    \
-                                                lens, nwords);                                                       \
-    else                                                                                                             \
-        k_analyze<B_, 1024><<<grid, 1024, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries,  \
-                                                  lens, nwords)
-            if (p.B == 1) {
-                ZIPNN_ANALYZE(1);
-            } else if (p.B == 2) {
-                ZIPNN_ANALYZE(2);
-            } else if (p.B == 4) {
-                // its counters leave LDS for two workgroups per CU
-                k_analyze<4, 1024><<<grid, 1024, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries,
-                                                         lens, nwords);
-            } else launched = false;
+            // plain launches at the default group: chunks of 64 (4-byte words:
+            // 32) groups a thread, 256 KiB, keep their coded streams in
+            // registers (a pass over 5 GB of BF16 2.88 against 3.09 ms, 256
+            // MiB of FP32 202 against 218 us).  At 512 KiB it would take 1024
+            // threads, one workgroup per CU, whose phases nothing overlaps:
+            // 3.08 against 3.11 ms, so no instance.
+            const bool hold = many && !staged && p.g == 4 && p.skip == 0 && p.chunk == 512 * 512;
+#define ZIPNN_ANALYZE(B_, NT_, H_)                                                                                  \
+    k_analyze<B_, NT_, H_><<<grid, NT_, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries,   \
+                                                lens, nwords)
+            if (p.B == 1 && many) ZIPNN_ANALYZE(1, 512, 0);
+            else if (p.B == 1) ZIPNN_ANALYZE(1, 1024, 0);
+            else if (p.B == 2 && hold) ZIPNN_ANALYZE(2, 512, 64);
+            else if (p.B == 2 && many) ZIPNN_ANALYZE(2, 512, 0);
+            else if (p.B == 2) ZIPNN_ANALYZE(2, 1024, 0);
+            else if (p.B == 4 && hold) ZIPNN_ANALYZE(4, 512, 32);
+            // (its counters leave LDS for two workgroups per CU)
+            else if (p.B == 4) ZIPNN_ANALYZE(4, 1024, 0);
+            else launched = false;
 #undef ZIPNN_ANALYZE
             if (!launched) return hipErrorInvalidValue;
             if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;

@@ -105,3 +105,57 @@ def test_alphabet_sizes(codec, n_sym, L):
         raw = np.resize(raw, (raw.size + 15) // 16 * 16)
         _check(codec, Z.ZIPNN_U8, raw, Z.make_params(Z.ZIPNN_U8, chunk_bytes=1 << 20, S=256, L=L,
                                                      policy=[Z.ZIPNN_HUF]))
+
+
+@pytest.mark.parametrize("spread", [0.0, 0.2, 0.35, 0.45, 0.6, 0.9])
+@pytest.mark.parametrize("chunk,S", [(262144, 512), (65536, 128), (4096, 16)])
+def test_nearly_uniform_groups(codec, spread, chunk, S):
+    """AUTO where the best code lies just above or below the raw size: counts
+    spread evenly, in a ramp, and in two levels."""
+    rng = np.random.default_rng(int(100 * spread) + chunk)
+    E = chunk // 2
+    cols = []
+    for w in (1 + spread * np.linspace(-1, 1, 256), np.where(np.arange(256) < 32, 1 + 4 * spread, 1.0)):
+        cols.append(rng.choice(256, 2 * E + 33, p=w / w.sum()).astype(np.uint8))
+    raw = np.stack([cols[0], cols[1]], axis=1).reshape(-1)
+    _check(codec, Z.ZIPNN_BF16, raw, Z.make_params(Z.ZIPNN_BF16, chunk_bytes=chunk, S=S))
+
+
+@pytest.mark.parametrize("dt", [Z.ZIPNN_BF16, Z.ZIPNN_FP32])
+@pytest.mark.parametrize("chunk", [262144, 524288])
+@pytest.mark.parametrize("S_div", [64, 128, 256, 512])
+def test_streams_held_in_registers(codec, dt, chunk, S_div):
+    """More than 512 chunks of the sizes whose coded streams stay in registers
+    between the counting and the size pass, full and partial last chunk, with
+    streams beyond the held ones coded in some chunks."""
+    B = Z.WIDTH[dt]
+    E = chunk // B
+    if E // S_div > 4096:
+        pytest.skip("S out of range")
+    n = 513 * E + 1000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(S_div + B)
+    x = (torch.randn(n, generator=g, device="cuda") * 0.02).to(TORCH[dt])
+    x.view(torch.uint8).view(-1, B)[5 * E:6 * E, 0] &= 3       # the lowest byte group of chunk 5 is compressible
+    x[7 * E:7 * E + E // 2] = 0                               # zeros: a ZG candidate in chunk 7
+    p = Z.make_params(dt, chunk_bytes=chunk, S=E // S_div)
+    c = codec.compress(x, p)
+    out = torch.empty_like(x)
+    codec.decompress(c, out)
+    assert torch.equal(out.view(torch.uint8), x.view(torch.uint8))
+    # the first and the last chunks against the oracle, as tensors of their own:
+    # a chunk's map entries do not depend on the others but for the offsets
+    for a, b in ((0, 9 * E), (512 * E, n)):
+        part = x[a:b].clone()
+        ref = oracle.compress(part.cpu().view(torch.uint8).numpy(), dt, chunk_bytes=chunk, S=p.substream_syms, g=p.group,
+                              L=p.max_code_len, policy=list(p.policy))
+        nc = (b - a + E - 1) // E
+        got = c[64 + 16 * B * (a // E):64 + 16 * B * (a // E + nc)].cpu().numpy().view(np.uint64).reshape(-1, 2)
+        want = np.frombuffer(ref[64:64 + 16 * B * nc].tobytes(), np.uint64).reshape(-1, 2)
+        assert np.array_equal(got[:, 1], want[:, 1])          # sizes and modes
+        pb = 64 + 16 * B * 514
+        pb = (pb + 127) // 128 * 128
+        rb = (64 + 16 * B * nc + 127) // 128 * 128
+        o = int(got[0, 0])
+        size = ref.size - rb
+        assert np.array_equal(c[pb + o:pb + o + size].cpu().numpy(), ref[rb:])
