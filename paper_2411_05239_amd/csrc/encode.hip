@@ -402,6 +402,18 @@ __device__ inline int find_desc(const uint32_t* prefix, int n_desc, uint32_t g)
 // (global loads: a generic pointer's flat loads would also wait for LDS).
 template <class T>
 using global_ptr = const T __attribute__((address_space(1)))*;
+// A flat access also leaves the compiler unsure which later wait covers it:
+// one pending before the packer's loop made every step wait for all memory
+// operations, stores included.
+__device__ inline uint32_t gld8(const uint8_t* p)
+{
+    return *(global_ptr<uint8_t>)reinterpret_cast<uint64_t>(p);
+}
+template <class T>
+__device__ inline void gst(uint8_t* p, T v)
+{
+    *(T __attribute__((address_space(1)))*)reinterpret_cast<uint64_t>(p) = v;
+}
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <int NB>
@@ -514,7 +526,7 @@ __device__ inline void group_words(const uint8_t* src, const uint8_t* base, uint
             for (int b = 0; b < 4; b++) {
                 const uint32_t jb = 4 * x + b;
                 if (jb < nb) {
-                    const uint32_t v = src[uint64_t(e) * B + jb] ^ (base ? base[uint64_t(e) * B + jb] : 0u);
+                    const uint32_t v = gld8(src + uint64_t(e) * B + jb) ^ (base ? gld8(base + uint64_t(e) * B + jb) : 0u);
                     wd[x] |= v << (8 * b);
                 }
             }
@@ -534,7 +546,7 @@ __device__ inline uint32_t element_word(const uint8_t* src, const uint8_t* base,
 #pragma unroll
     for (int b = 0; b < B; b++) {
         const uint64_t o = uint64_t(e) * B + b;
-        v |= uint32_t(src[o] ^ (base ? base[o] : 0u)) << (8 * b);
+        v |= (gld8(src + o) ^ (base ? gld8(base + o) : 0u)) << (8 * b);
     }
     return xf ? exp_fwd<B>(v) : v;
 }
@@ -545,6 +557,16 @@ __device__ inline uint32_t sym_of(const uint32_t* wd, int k, int i)
 {
     const int jb = i * B + (B - 1 - k);
     return (wd[jb >> 2] >> (8 * (jb & 3))) & 0xFFu;
+}
+
+// The bytes of stream k in a 32-bit word of B-byte elements (in its first
+// `nb` bytes).
+template <int B>
+__device__ inline constexpr uint32_t stream_bytes(int k, int nb)
+{
+    uint32_t m = 0;
+    for (int jb = B - 1 - k; jb < nb; jb += B) m |= 0xFFu << (8 * jb);
+    return m;
 }
 
 // Whether a group of gcnt symbols of stream k holds a value other than z.
@@ -1473,6 +1495,7 @@ __device__ __attribute__((always_inline)) inline void for_streams(F&& f)
         f(std::integral_constant<int, N - 1>{});
     }
 }
+constexpr int kNever = -0x7FFFFFFF;             // packer: no lane holds fewer bits
 constexpr uint32_t kNoStore = 0x80000000u;      // buffer offset past every resource: the store is dropped
 
 // Write the words of lane group j of every coded stream of one chunk (bit k
@@ -1503,7 +1526,7 @@ constexpr uint32_t kNoStore = 0x80000000u;      // buffer offset past every reso
 // one, and the lanes' words add up to the cursor.  A word belongs to the range
 // that takes it: the words taken before are completed but not stored here,
 // and after s1 the lanes go on, taking none, until theirs are complete.
-template <int B, int G, bool XB>
+template <int B, int G, bool XB, bool SPEC>
 __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* src, const uint8_t* base, uint32_t cm,
                                                                uint32_t zm, const PackLds& P, uint32_t L, uint32_t j,
                                                                uint32_t W, uint32_t m, bool xf, bool fuse_bitmap,
@@ -1536,6 +1559,9 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
     // lanes past the last sub-stream: their loads and stores are out of range
     // and they never need a word
     const bool act = w < W;
+    uint32_t zrep[B];   // a ZG stream's fill value in every byte
+#pragma unroll
+    for (int k = 0; k < B; k++) zrep[k] = __builtin_amdgcn_readfirstlane(P.z[k] * 0x01010101u);
     const uint32_t w_in = act ? w * NB : kNoStore, w_raw = act ? w * G : kNoStore;
     const __amdgpu_buffer_rsrc_t rsrc = in_rsrc(src, m * B);
     const __amdgpu_buffer_rsrc_t rbase = in_rsrc(base ? base : src, base ? m * B : 0u);   // no base: zeros
@@ -1547,7 +1573,7 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
     // fused bitmap, and the lock-step state
     struct Stream {
         __amdgpu_buffer_rsrc_t out;
-        uint64_t* bmw;
+        uint8_t* bmw;   // the fused bitmap
         uint32_t cur, alo, ahi, nacc, s0, s1;
         int held;
     };
@@ -1571,7 +1597,7 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
         const uint64_t wa = uni64(uint64_t(dst + pk + lead) + 4ull * w0);
         x.out = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(wa), (short)0,
                                                   int(((cm >> k) & 1) ? 4 * nw : 0u), 0x00020000);
-        x.bmw = (zb && fuse_bitmap) ? reinterpret_cast<uint64_t*>(dst + pk + (staged ? 0u : head)) : nullptr;
+        x.bmw = (zb && fuse_bitmap) ? dst + pk + (staged ? 0u : head) : nullptr;
         x.cur = x.alo = x.ahi = x.nacc = 0;
         x.s0 = x.s1 = kNoStore;
         x.held = 0;
@@ -1599,12 +1625,13 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
         reinterpret_cast<void*>(raw0), (short)0,
         int(__builtin_amdgcn_readfirstlane(rawmask ? uint32_t(P.pay[B - 1] - P.pay[0]) + m : 0u)), 0x00020000);
     // one pair of stream k: entries c0, c1 (zero for a symbol that is not
-    // coded), p0 whether the lane takes part
-    auto pair = [&](auto kc, uint32_t c0, uint32_t c1, bool p0, auto take_c) __attribute__((always_inline)) {
+    // coded); a lane takes a word if it holds fewer than thr bits (2L, or
+    // kNever where it takes no part)
+    auto pair = [&](auto kc, uint32_t c0, uint32_t c1, int thr, auto take_c) __attribute__((always_inline)) {
         constexpr bool TAKE = decltype(take_c)::value;
         Stream& x = S(kc);
         if constexpr (TAKE) {
-            const bool need = p0 && x.held < twoL;
+            const bool need = x.held < thr;
             const uint64_t msk = __ballot(need);
             const uint32_t place = 4u * __builtin_amdgcn_mbcnt_hi(uint32_t(msk >> 32),
                                                                   __builtin_amdgcn_mbcnt_lo(uint32_t(msk), x.cur));
@@ -1634,7 +1661,11 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
         if constexpr (!TAKE) x.s1 = full ? kNoStore : x.s1;
     };
     // one step (group e of every lane); FAST: every lane has a full group
-    auto step = [&](uint32_t e, const uint32_t* wd, auto fast_c, auto take_c) __attribute__((always_inline)) {
+    auto step = [&](uint32_t e, const uint32_t* wd, auto fast_c, auto take_c, auto cm_c, auto zm_c)
+                    __attribute__((always_inline)) {
+        // the coded and the ZG streams, known here or (-1) not
+        constexpr int CM = decltype(cm_c)::value, ZM = decltype(zm_c)::value;
+        const uint32_t cms = CM >= 0 ? uint32_t(CM) : cm, zms = ZM >= 0 ? uint32_t(ZM) : zm;
         constexpr bool FAST = decltype(fast_c)::value;
         constexpr bool TAKE = decltype(take_c)::value;   // else only words already taken are completed
         const bool has = FAST || e < ng;
@@ -1660,28 +1691,47 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
         }
         for_streams<B>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            if (!((cm >> k) & 1)) return;
-            // the pairs of a group of gcnt coded symbols
-            auto pairs = [&](uint32_t gcnt) __attribute__((always_inline)) {
+            if (!((cms >> k) & 1)) return;
+            // the pairs of a group of gcnt coded symbols; in a fast step, all
+            // G of them, or none where `on` (all ones or zero) is zero.  The
+            // table is read in either case and the entries are masked: no
+            // branch per pair, no flag turned into a number for the ballot.
+            auto pairs = [&](uint32_t gcnt, uint32_t on) __attribute__((always_inline)) {
+                const int thr_on = on ? twoL : kNever;
 #pragma unroll
                 for (int pr = 0; pr < G / 2; pr++) {
-                    const bool p0 = 2u * pr < gcnt, p1 = 2u * pr + 1 < gcnt;
                     const uint32_t c0 = P.rcode[k][sym_of<B>(wd, k, 2 * pr)];
                     const uint32_t c1 = P.rcode[k][sym_of<B>(wd, k, 2 * pr + 1)];
-                    pair(kc, p0 ? c0 : 0u, p1 ? c1 : 0u, p0, take_c);
+                    if constexpr (FAST) {
+                        pair(kc, c0 & on, c1 & on, thr_on, take_c);
+                    } else {
+                        const bool p0 = 2u * pr < gcnt, p1 = 2u * pr + 1 < gcnt;
+                        pair(kc, p0 ? c0 : 0u, p1 ? c1 : 0u, p0 ? twoL : kNever, take_c);
+                    }
                 }
             };
-            if ((zm >> k) & 1) {
-                const bool mk = act && has && marked<B, G>(wd, k, ecnt, P.z[k]);
+            if ((zms >> k) & 1) {
+                bool mk;
+                if constexpr (FAST) {
+                    // lanes past the last sub-stream may count as marked:
+                    // they take no word and their stores are out of range
+                    // (a fused bitmap has no such lanes)
+                    uint32_t diff = 0;
+#pragma unroll
+                    for (int x = 0; x < NW; x++) diff |= (wd[x] ^ zrep[k]) & stream_bytes<B>(k, NB < 4 ? NB : 4);
+                    mk = diff != 0;
+                } else {
+                    mk = has && marked<B, G>(wd, k, ecnt, P.z[k]);
+                }
                 const uint64_t bits = __ballot(mk);
                 // ZG with W a multiple of 64: the 64 bits of this lane
                 // group's step e are one aligned word of the bitmap
-                if (TAKE && fuse_bitmap && lane == 0) S(kc).bmw[j + e * (W / 64)] = bits;
+                if (TAKE && fuse_bitmap && lane == 0) gst(S(kc).bmw + 8 * (j + e * (W / 64)), bits);
                 // where no lane of the wave holds a marked group, the pairs
                 // would take no word and add no bits: they are skipped
-                if (bits) pairs(mk ? ecnt : 0u);
+                if (bits) pairs(mk ? ecnt : 0u, mk ? ~0u : 0u);
             } else {
-                pairs(ecnt);   // in a fast step, G: no per-lane conditions
+                pairs(ecnt, ~0u);   // in a fast step, G: no per-lane conditions
             }
         });
     };
@@ -1701,7 +1751,11 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
         for (int x = 0; x < NW; x++) {
             wd[x] = f.x[x];
             if constexpr (XB) wd[x] ^= f.y[x];
-            if (xf) wd[x] = exp_fwd<B>(wd[x]);
+        }
+        if (xf) {
+            asm volatile("");   // a branch: computed and selected, it is 12 instructions of every step
+#pragma unroll
+            for (int x = 0; x < NW; x++) wd[x] = exp_fwd<B>(wd[x]);
         }
     };
     auto last_words = [&](uint32_t e, uint32_t* wd) __attribute__((always_inline)) {
@@ -1711,15 +1765,41 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
     using F = std::integral_constant<bool, false>;
 #pragma unroll
     for (uint32_t u = 0; u < kPf; u++) load(s0 + u, pf[u]);
-    for (uint32_t j0 = s0; j0 < n_fast; j0 += kPf) {
+    // the first loads are waited for once, here: left pending, their order
+    // would set how far back the loop's waits reach
 #pragma unroll
-        for (uint32_t u = 0; u < kPf; u++) {
-            uint32_t cw[NW];
-            words(pf[u], cw);
-            load(j0 + u + kPf, pf[u]);
-            step(j0 + u, cw, T{}, T{});
+    for (uint32_t u = 0; u < kPf; u++) {
+#pragma unroll
+        for (int x = 0; x < NW; x++) {
+            asm volatile("" : "+v"(pf[u].x[x]));
+            if constexpr (XB) asm volatile("" : "+v"(pf[u].y[x]));
         }
     }
+    // A copy of the loop for a BF16 chunk's common set (exponent coded, the
+    // other byte group raw): with the set known only at run time every stream's
+    // state is moved at the ends of its branches (a 5 GB shard's encode, us:
+    // 2880 without, 2869 with). On a delta such a copy for both byte groups
+    // coded and unmarked spills: 1590 without, 1605 with.
+    auto fast = [&](auto cm_c, auto zm_c) __attribute__((always_inline)) {
+        for (uint32_t j0 = s0; j0 < n_fast; j0 += kPf) {
+#pragma unroll
+            for (uint32_t u = 0; u < kPf; u++) {
+                uint32_t cw[NW];
+                words(pf[u], cw);
+                load(j0 + u + kPf, pf[u]);
+                step(j0 + u, cw, T{}, T{}, cm_c, zm_c);
+            }
+        }
+    };
+    using Any = std::integral_constant<int, -1>;
+    bool done = false;
+    if constexpr (SPEC && B == 2 && !XB) {
+        if (cm == 1 && zm == 0) {
+            fast(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
+            done = true;
+        }
+    }
+    if (!done) fast(Any{}, Any{});
     // the steps without a full group in every lane, then (after s1) those that
     // complete the words taken in this range
     bool ended = false;
@@ -1751,8 +1831,8 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
             words(pf[u], cw);
             last_words(jj, cw);
             load(jj + kPf, pf[u]);
-            if (jj < s1) step(jj, cw, F{}, T{});
-            else step(jj, cw, F{}, F{});
+            if (jj < s1) step(jj, cw, F{}, T{}, Any{}, Any{});
+            else step(jj, cw, F{}, F{}, Any{}, Any{});
         }
     }
     // the lane's unfinished words: the partial one (zero bits if none), then zero
@@ -1764,7 +1844,7 @@ __device__ __attribute__((always_inline)) void pack_lane_group(const uint8_t* sr
         __builtin_amdgcn_raw_buffer_store_b32(x.alo, x.out, pend > 0 ? x.s0 : kNoStore, 0, 0);
         __builtin_amdgcn_raw_buffer_store_b32(0u, x.out, pend > 1 ? x.s1 : kNoStore, 0, 0);
         // staged: the words this lane group took (the cursor is uniform)
-        if (nw_out && lane == 0) nw_out[k * 64 + j] = x.cur;
+        if (nw_out && lane == 0) gst(reinterpret_cast<uint8_t*>(nw_out + k * 64 + j), x.cur);
     });
 }
 
@@ -1788,7 +1868,7 @@ __device__ void pack_bitmap(const uint8_t* src, const uint8_t* base, int k, uint
             mk = marked<B, G>(wd, k, min(uint32_t(G), m - q * G), z);
         }
         const uint64_t bits = __ballot(mk);
-        if (lane == 0) *reinterpret_cast<uint64_t*>(dst + 8 * x) = bits;
+        if (lane == 0) gst(dst + 8 * x, bits);
     }
 }
 
@@ -1808,7 +1888,7 @@ __device__ void pack_raw(const uint8_t* src, const uint8_t* base, uint8_t* dst, 
         for (uint32_t e = m + threadIdx.x; e < uint32_t(align_pay(m)); e += NT)
 #pragma unroll
             for (int k = 0; k < B; k++)
-                if ((rawmask >> k) & 1) dst[P.pay[k] + e] = 0;
+                if ((rawmask >> k) & 1) gst(dst + P.pay[k] + e, uint8_t(0));
         return;
     }
     const uint32_t units = m / 16;
@@ -1840,7 +1920,7 @@ __device__ void pack_raw(const uint8_t* src, const uint8_t* base, uint8_t* dst, 
                 uint32_t o[4] = {0, 0, 0, 0};
 #pragma unroll
                 for (int i = 0; i < 16; i++) o[i >> 2] |= sym_of<B>(wds[r], k, i) << (8 * (i & 3));
-                *(uint4*)(dst + P.pay[k] + 16 * u) = make_uint4(o[0], o[1], o[2], o[3]);
+                gst(dst + P.pay[k] + 16 * u, u32x4{o[0], o[1], o[2], o[3]});
             }
         }
     }
@@ -1849,7 +1929,7 @@ __device__ void pack_raw(const uint8_t* src, const uint8_t* base, uint8_t* dst, 
         const uint32_t v = e < m ? element_word<B>(src, base, e, xf) : 0u;
 #pragma unroll
         for (int k = 0; k < B; k++)
-            if ((rawmask >> k) & 1) dst[P.pay[k] + e] = uint8_t(v >> (8 * (B - 1 - k)));
+            if ((rawmask >> k) & 1) gst(dst + P.pay[k] + e, uint8_t(v >> (8 * (B - 1 - k))));
     }
 }
 
@@ -1898,12 +1978,9 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
             P.bytes[k] = en.bytes;
             P.pay[k] = payload_base + offsets[ei];
             // this chunk's map entry
-            uint4 ent;
-            ent.x = uint32_t(offsets[ei]);
-            ent.y = uint32_t(offsets[ei] >> 32);
-            ent.z = en.bytes;
-            ent.w = uint32_t(en.mode) | (uint32_t(en.rle) << 8);
-            *(uint4*)(d.dst + 64 + 16 * (uint64_t(c) * B + k)) = ent;
+            gst(d.dst + 64 + 16 * (uint64_t(c) * B + k),
+                u32x4{uint32_t(offsets[ei]), uint32_t(offsets[ei] >> 32), en.bytes,
+                      uint32_t(en.mode) | (uint32_t(en.rle) << 8)});
         }
         if (t == 0) P.z[k] = en.rle;
         if (en.mode == kModeHuf || en.mode == kModeZg) {
@@ -1970,18 +2047,17 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
         // after words (staged: the compaction writes all but the bitmap)
         if (!staged) {
             if (t < 128)
-                pay[t] = uint8_t((P.rcode[k][2 * t] >> kLenShift) | ((P.rcode[k][2 * t + 1] >> kLenShift) << 4));
-            if (uint32_t(t) < NG) ((uint32_t*)(pay + 128))[t] = P.wpre[k][t + 1] - P.wpre[k][t];
-            for (uint32_t i = 128 + 4 * NG + t; i < head; i += NT) pay[i] = 0;
-            for (uint32_t i = P.bytes[k] + t; i < uint32_t(align_pay(P.bytes[k])); i += NT) pay[i] = 0;
+                gst(pay + t, uint8_t((P.rcode[k][2 * t] >> kLenShift) | ((P.rcode[k][2 * t + 1] >> kLenShift) << 4)));
+            if (uint32_t(t) < NG) gst(pay + 128 + 4 * t, P.wpre[k][t + 1] - P.wpre[k][t]);
+            for (uint32_t i = 128 + 4 * NG + t; i < head; i += NT) gst(pay + i, uint8_t(0));
+            for (uint32_t i = P.bytes[k] + t; i < uint32_t(align_pay(P.bytes[k])); i += NT) gst(pay + i, uint8_t(0));
         }
         const uint32_t lead = staged ? 0u : head;   // where the bitmap starts
         if (zg) {
             const uint32_t bm = zg_bitmap(m, GG);
             if (fuse_bitmap) {   // only the words past the last group are zeroed here
-                uint64_t* words = reinterpret_cast<uint64_t*>(pay + lead);
                 const uint32_t Gtot = (m + GG - 1) / GG;
-                for (uint32_t x = (Gtot + 63) / 64 + t; x < bm / 8; x += NT) words[x] = 0;
+                for (uint32_t x = (Gtot + 63) / 64 + t; x < bm / 8; x += NT) gst(pay + lead + 8 * x, uint64_t(0));
             } else {
                 pack_bitmap<BB, GG, NT>(src, base, int(k), P.z[k], m, bm, pay + lead, xf);
             }
@@ -1995,20 +2071,21 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
         for (uint32_t x = wv; x < NG * nseg; x += NT / 64) {
             const uint32_t j = x % NG, sg = x / NG;
             if (sg * per >= steps) continue;
-            pack_lane_group<BB, GG, XB>(src, base, cm, zm, P, p.L, j, W, m, xf, fuse_bitmap, fuse_raw ? rawmask : 0u,
-                                    dst, staged ? p.stage_lg : 0u, p.stage_bm,
-                                    staged ? nwords + uint64_t(gc) * B * 64 : nullptr, sg * per,
-                                    min(steps, (sg + 1) * per), sg, p.segs + uint64_t(gc) * B * kSegWords);
+            pack_lane_group<BB, GG, XB, NT == 256>(src, base, cm, zm, P, p.L, j, W, m, xf, fuse_bitmap,
+                                                   fuse_raw ? rawmask : 0u, dst, staged ? p.stage_lg : 0u, p.stage_bm,
+                                                   staged ? nwords + uint64_t(gc) * B * 64 : nullptr, sg * per,
+                                                   min(steps, (sg + 1) * per), sg, p.segs + uint64_t(gc) * B * kSegWords);
         }
 }
 
 // NT = 256 for full launches, which the bytes read and written bound: 5 GB of
-// an 8B checkpoint 1.77 ms, 4.7 TB/s, a copy's rate.  NT = 1024 for few
+// an 8B checkpoint 1.72 ms, 4.9 TB/s, a copy's rate.  NT = 1024 for few
 // chunks, where a lane group's serial steps bound: with its steps cut into 16
 // / (lane groups) ranges, an 8 KiB tensor 58 -> 16 us, 32 chunks of 256 KiB 61
 // -> 30 us.  XB: some tensor has an XOR base, whose bytes are fetched ahead
-// with the tensor's (a 1.7 GB delta's pass 1880 -> 1750 us against the XOR at
-// the fetch, which waited for both).
+// with the tensor's (against the XOR at the fetch, which waited for both).
+// Vector instructions bound it (93% of its issue slots): with 128 a step of a
+// wave instead of 150, an 845 MB delta's pass 858 -> 826 us.
 template <int BB, int GG, bool XB, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 256 && BB == 2 ? (XB ? 6 : 5) : 4, 8))) void k_pack(
     const EncDesc* __restrict__ descs, int n_desc, const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
