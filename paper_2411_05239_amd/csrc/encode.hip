@@ -1,6 +1,6 @@
 // Encode kernels of the gfx950 ZipNN codec.
 //
-//   k_analyze  one workgroup of 16 waves per chunk: reads the chunk (16-byte
+//   k_analyze  one workgroup of 8 or 16 waves per chunk: reads the chunk (16-byte
 //              loads, XOR with the base for a delta, paper §IV-B, exponent
 //              extraction when asked, §III-A), splits every word into its B
 //              byte groups (paper §III-A/§III-B) and histograms each group in
@@ -20,13 +20,15 @@
 //              parallel decode, paper §V-A), and whether the map holds ZG
 //              entries (a header flag); the last workgroup places the
 //              containers in the arena and writes their headers.
-//   k_pack     one workgroup per chunk: raw groups are copied with 16-byte
-//              stores; for a Huffman or ZG group, wave v writes lane groups v,
-//              v+4, ...: its lanes replay the same steps, and in every round
-//              the lanes that the decoder will serve write their next word to
-//              consecutive slots (ballot + prefix popcount), encoding codes
-//              ahead of the decoder model.  Every byte of the payload extent,
-//              padding included, is written; no atomics.
+//   k_pack     one workgroup per chunk: a wave writes a lane group's words of
+//              every coded stream (few chunks: a range of its steps) in
+//              lock-step over the layout's steps and pairs; a word's place
+//              follows from the rank among the lanes that take one (ballot +
+//              prefix popcount).  Raw groups are copied on the same pass.
+//              Every byte of the payload extent, padding included, is
+//              written; no atomics.
+//   k_compact  large launches with an XOR base: their words were packed into
+//              staging slots and counted there, and move to their places.
 #include <type_traits>
 
 #include "zipnn_internal.h"
@@ -1349,7 +1351,7 @@ __device__ inline uint64_t block_scan(uint64_t v, uint64_t& carry, uint64_t* red
 // small nothing is written and the recorded end says so.  descs[0].pad
 // counts the workgroups; it is zero before and after.  4096 entries a round:
 // the 8016 of a checkpoint's embedding, 256 a round, took 33 us and the
-// arena 5 us in a launch of its own; now 13 us together.
+// arena 5 us in a launch of its own; now 21 us together.
 __global__ __launch_bounds__(kPlaceThreads) void k_place(EncDesc* descs, int n_desc, EncParams p, EncEntry* entries,
                                                          uint64_t* offsets, uint64_t* totals, const uint32_t* nwords,
                                                          uint8_t* arena, uint64_t cap, uint64_t* arena_off,
@@ -2085,7 +2087,7 @@ __device__ __attribute__((always_inline)) void pack_chunk(uint32_t gc, const Enc
 // -> 30 us.  XB: some tensor has an XOR base, whose bytes are fetched ahead
 // with the tensor's (against the XOR at the fetch, which waited for both).
 // Vector instructions bound it (93% of its issue slots): with 128 a step of a
-// wave instead of 150, an 845 MB delta's pass 858 -> 826 us.
+// wave instead of 150, a 1.7 GB delta's pass 858 -> 826 us.
 template <int BB, int GG, bool XB, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 256 && BB == 2 ? (XB ? 6 : 5) : 4, 8))) void k_pack(
     const EncDesc* __restrict__ descs, int n_desc, const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,

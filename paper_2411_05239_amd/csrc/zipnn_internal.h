@@ -313,6 +313,8 @@ hipError_t launch_fill_desc(const EncDesc& one, uint32_t total_chunks, EncDesc* 
 
 // Offsets of the encoder's device scratch for ne = chunks * B entries of n
 // tensors (every array 256-byte aligned); `need` is the total.
+// `codes` keeps 1 KiB an entry, of which the code lengths fill 256 bytes: a
+// caller's scratch that was too small for a call stays too small for it.
 struct EncScratch {
     size_t entries, codes, offsets, nwords, totals, aoff, descs, prefix, segs, stage, need;
 };
