@@ -159,13 +159,13 @@ int zipnn_ctx_create(int hip_device, zipnn_ctx* out)
     if (!ctx) return ZIPNN_E_NOMEM;
     ctx->device = hip_device;
     DeviceGuard g(hip_device);
-    if (dev_malloc((void**)&ctx->d_status, sizeof(int)) != hipSuccess ||
-        host_malloc((void**)&ctx->h_status, sizeof(int)) != hipSuccess ||
+    if (host_malloc((void**)&ctx->status, sizeof(int)) != hipSuccess ||
         grow_pinned(ctx, 64) != ZIPNN_OK) {
         zipnn_ctx_destroy(ctx);
         return ZIPNN_E_NOMEM;
     }
-    if (hipMemset(ctx->d_status, 0, sizeof(int)) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    __atomic_store_n(ctx->status, 0, __ATOMIC_SEQ_CST);
+    if (hipDeviceSynchronize() != hipSuccess) {
         zipnn_ctx_destroy(ctx);
         return ZIPNN_E_HIP;
     }
@@ -189,8 +189,7 @@ void zipnn_ctx_destroy(zipnn_ctx ctx)
     {
         DeviceGuard g(ctx->device);
         (void)hipDeviceSynchronize();
-        if (ctx->d_status) (void)hipFree(ctx->d_status);
-        if (ctx->h_status) (void)hipHostFree(ctx->h_status);
+        if (ctx->status) (void)hipHostFree(ctx->status);
         if (ctx->h_total) (void)hipHostFree(ctx->h_total);
         if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
     }
@@ -202,9 +201,9 @@ int zipnn_ctx_status(zipnn_ctx ctx, void* stream, int clear)
     if (!ctx) return ZIPNN_E_INVAL;
     DeviceGuard g(ctx->device);
     hipStream_t s = (hipStream_t)stream;
-    if (launch_take_status(ctx->d_status, ctx->h_status, clear != 0, s) != hipSuccess) return ZIPNN_E_HIP;
     if (hipStreamSynchronize(s) != hipSuccess) return ZIPNN_E_HIP;
-    return *ctx->h_status;
+    return clear ? __atomic_exchange_n(ctx->status, 0, __ATOMIC_SEQ_CST)
+                 : __atomic_load_n(ctx->status, __ATOMIC_SEQ_CST);
 }
 
 void zipnn_default_params(int dtype, zipnn_params* out)
@@ -313,10 +312,8 @@ static int encode_tensors(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, in
     if (stage) set_stage(ep, sc + lay.stage, dtype, *p);
     else if (total_chunks <= kFewChunks) ep.segs = (uint32_t*)(sc + lay.segs);
     // a single tensor's descriptor travels in kernel arguments
-    const hipError_t up = n == 1 ? launch_fill_desc(hd[0], hp[1], d_descs, d_prefix, s)
-                                 : hipMemcpyAsync(d_descs, hd, up_bytes, hipMemcpyHostToDevice, s);
-    if (up != hipSuccess ||
-        launch_encode(d_descs, n, d_prefix, uint32_t(total_chunks), ep, (uint8_t*)arena, cap,
+    if ((n > 1 && hipMemcpyAsync(d_descs, hd, up_bytes, hipMemcpyHostToDevice, s) != hipSuccess) ||
+        launch_encode(n == 1 ? hd : nullptr, d_descs, n, d_prefix, uint32_t(total_chunks), ep, (uint8_t*)arena, cap,
                       (EncEntry*)(sc + lay.entries), sc + lay.codes, (uint32_t*)(sc + lay.nwords),
                       (uint64_t*)(sc + lay.offsets), (uint64_t*)(sc + lay.totals), d_aoff, ho, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
@@ -373,8 +370,7 @@ int zipnn_compress_noalloc(zipnn_ctx ctx, const void* src, int dtype, uint64_t n
     uint64_t ho[2] = {0, 0};   // the arena offsets come back to the stack
     EncParams ep = make_params(dtype, *p, one.base != nullptr);
     if (nc <= kFewChunks) ep.segs = (uint32_t*)(sc + lay.segs);
-    if (launch_fill_desc(one, uint32_t(nc), d_descs, d_prefix, s) != hipSuccess ||
-        launch_encode(d_descs, 1, d_prefix, uint32_t(nc), ep, (uint8_t*)dst, dst_cap, (EncEntry*)(sc + lay.entries),
+    if (launch_encode(&one, d_descs, 1, d_prefix, uint32_t(nc), ep, (uint8_t*)dst, dst_cap, (EncEntry*)(sc + lay.entries),
                       sc + lay.codes, (uint32_t*)(sc + lay.nwords), (uint64_t*)(sc + lay.offsets),
                       (uint64_t*)(sc + lay.totals), d_aoff, nullptr, s) != hipSuccess ||
         hipMemcpyAsync(ho, d_aoff, sizeof(ho), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -473,7 +469,7 @@ int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, int
         zipnn_encoder_destroy(e);
         return ZIPNN_E_HIP;
     }
-    hipError_t le = launch_encode(d_descs, n, d_prefix, uint32_t(total_chunks), ep, (uint8_t*)arena, cap,
+    hipError_t le = launch_encode(nullptr, d_descs, n, d_prefix, uint32_t(total_chunks), ep, (uint8_t*)arena, cap,
                                   (EncEntry*)(sc + lay.entries), sc + lay.codes,
                                   (uint32_t*)(sc + lay.nwords), (uint64_t*)(sc + lay.offsets),
                                   (uint64_t*)(sc + lay.totals), d_aoff, e->h_offs, e->capst);
@@ -537,7 +533,7 @@ static int decompress_common(zipnn_ctx ctx, const uint32_t* hdr_words, const voi
     const uint64_t items = plan_items(h, 0, kAllChunks).items;
     const int grid = int(std::min<uint64_t>(uint64_t(ctx->dec_grid[dec_class_index(dec_class(h))]),
                                             std::max<uint64_t>(items, 1)));
-    if (launch_decode_one(h, one, ctx->d_status, grid, s) != hipSuccess) return ZIPNN_E_HIP;
+    if (launch_decode_one(h, one, ctx->status, grid, s) != hipSuccess) return ZIPNN_E_HIP;
     return ZIPNN_OK;
 }
 
@@ -590,7 +586,7 @@ struct zipnn_batch_s {
 static hipError_t batch_launch(zipnn_batch b, hipStream_t s)
 {
     for (auto& c : b->classes) {
-        hipError_t e = launch_decode_batch(c.k, c.d_descs, c.n, c.d_prefix, b->ctx->d_status,
+        hipError_t e = launch_decode_batch(c.k, c.d_descs, c.n, c.d_prefix, b->ctx->status,
                                            b->ctx->dec_grid[dec_class_index(c.k)], s);
         if (e != hipSuccess) return e;
     }

@@ -794,8 +794,7 @@ struct AnalyzeShared {
 // The analysis of chunk gc by one workgroup (steps 1-5 above); a chunk that
 // the probing phase leaves to the other launch is passed over.
 template <int BB, int NT, int HOLD>
-__device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const EncDesc* __restrict__ descs,
-                                                             int n_desc, const uint32_t* __restrict__ chunk_prefix,
+__device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const EncDesc& d, uint32_t c,
                                                              const EncParams& p, int phase,
                                                              EncEntry* __restrict__ entries, uint8_t* __restrict__ lens,
                                                              uint32_t* __restrict__ nwords, AnalyzeShared<BB, NT>& sh)
@@ -807,9 +806,6 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
     const int t = threadIdx.x, lane = t & 63;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
     constexpr uint32_t B = BB;
-    const int di = find_desc(chunk_prefix, n_desc, gc);
-    const EncDesc d = descs[di];
-    const uint32_t c = gc - chunk_prefix[di];
     const uint32_t run = p.skip + 1;
     const bool probe = c % run == 0;
     if ((phase == 0 && !probe) || (phase == 1 && probe)) return;
@@ -1305,15 +1301,32 @@ __device__ __attribute__((always_inline)) void analyze_chunk(uint32_t gc, const 
 // small launches the chain count - code - sizes of one chunk: an 8 KiB tensor
 // 98 -> 14 us, 32 chunks 146 -> 26 us.  The waves that classify and build
 // codes run at raised priority: the others wait for them.
+// A single tensor's descriptor comes in `one`, and the first workgroup writes
+// it and its prefix to own[0] and own_prefix[0, 2) for the kernels that
+// follow (own not null); by a kernel of its own before this one, an 8 KiB
+// tensor's compress took 57 us, so 54.5 (8 MiB of BF16: 76.5, 73.1).
 template <int BB, int NT, int HOLD>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(HOLD ? 4 : 8, 8))) void k_analyze(
     const EncDesc* __restrict__ descs, int n_desc, const uint32_t* __restrict__ chunk_prefix, uint32_t total_chunks,
-    EncParams p, int phase, EncEntry* __restrict__ entries, uint8_t* __restrict__ lens, uint32_t* __restrict__ nwords)
+    EncParams p, int phase, EncEntry* __restrict__ entries, uint8_t* __restrict__ lens, uint32_t* __restrict__ nwords,
+    EncDesc one, EncDesc* own, uint32_t* own_prefix)
 {
     __shared__ AnalyzeShared<BB, NT> sh;
     const uint32_t gc = chunk_of_block();
-    if (gc < total_chunks)
-        analyze_chunk<BB, NT, HOLD>(gc, descs, n_desc, chunk_prefix, p, phase, entries, lens, nwords, sh);
+    if (gc >= total_chunks) return;
+    uint32_t c = gc;
+    if (own) {
+        if (gc == 0 && threadIdx.x == 0) {
+            *own = one;
+            own_prefix[0] = 0;
+            own_prefix[1] = total_chunks;
+        }
+    } else {
+        const int di = find_desc(chunk_prefix, n_desc, gc);
+        one = descs[di];
+        c = gc - chunk_prefix[di];
+    }
+    analyze_chunk<BB, NT, HOLD>(gc, one, c, p, phase, entries, lens, nwords, sh);
 }
 
 constexpr int kPlaceThreads = 1024;
@@ -2182,8 +2195,8 @@ __global__ __launch_bounds__(kBlock) void k_compact(const EncDesc* __restrict__ 
     }
 }
 
-// One tensor's descriptor and chunk prefix, written from kernel arguments (the
-// allocation-free entry point has no host staging to copy them from).
+// An empty tensor's descriptor and chunk prefix, written from kernel arguments
+// (no analysis runs that would).
 __global__ void k_fill_desc(EncDesc one, uint32_t total_chunks, EncDesc* __restrict__ d, uint32_t* __restrict__ prefix)
 {
     if (threadIdx.x == 0) {
@@ -2195,21 +2208,19 @@ __global__ void k_fill_desc(EncDesc one, uint32_t total_chunks, EncDesc* __restr
 
 }  // namespace
 
-hipError_t launch_fill_desc(const EncDesc& one, uint32_t total_chunks, EncDesc* d_desc, uint32_t* d_prefix,
-                            hipStream_t s)
-{
-    k_fill_desc<<<1, 64, 0, s>>>(one, total_chunks, d_desc, d_prefix);
-    return hipGetLastError();
-}
-
-hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_prefix, uint32_t total_chunks,
-                         const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, uint8_t* lens,
+hipError_t launch_encode(const EncDesc* single, EncDesc* d_descs, int n_desc, uint32_t* d_chunk_prefix,
+                         uint32_t total_chunks, const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, uint8_t* lens,
                          uint32_t* nwords, uint64_t* offsets, uint64_t* totals, uint64_t* arena_off,
                          uint64_t* host_off, hipStream_t s)
 {
     const dim3 grid = chunk_grid(total_chunks);
     const bool xb = (p.flags & kFlagDelta) != 0;   // some tensor has an XOR base
     const bool staged = p.stage != nullptr;
+    const EncDesc one = single ? *single : EncDesc{};
+    if (single && !total_chunks) {
+        k_fill_desc<<<1, 64, 0, s>>>(one, total_chunks, d_descs, d_chunk_prefix);
+        if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    }
     if (total_chunks) {
         // with probing, the probe chunks first: the others read their entries
         for (int phase = p.skip ? 0 : -1; phase <= (p.skip ? 1 : -1); phase++) {
@@ -2228,7 +2239,7 @@ hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_p
             const bool hold = many && !staged && p.g == 4 && p.skip == 0 && p.chunk == 512 * 512;
 #define ZIPNN_ANALYZE(B_, NT_, H_)                                                                                  \
     k_analyze<B_, NT_, H_><<<grid, NT_, 0, s>>>(d_descs, n_desc, d_chunk_prefix, total_chunks, p, phase, entries,   \
-                                                lens, nwords)
+                                                lens, nwords, one, single ? d_descs : nullptr, d_chunk_prefix)
             if (p.B == 1 && many) ZIPNN_ANALYZE(1, 512, 0);
             else if (p.B == 1) ZIPNN_ANALYZE(1, 1024, 0);
             else if (p.B == 2 && hold) ZIPNN_ANALYZE(2, 512, 64);

@@ -273,19 +273,17 @@ __host__ __device__ inline DecClass dec_class(const Header& h)
 {
     return DecClass{h.B, h.g, (h.flags & kFlagDelta) != 0, (h.flags & kFlagZg) != 0};
 }
-hipError_t launch_decode_one(const Header& h, const DecDesc& one, int* d_status, int grid, hipStream_t s);
+hipError_t launch_decode_one(const Header& h, const DecDesc& one, int* status, int grid, hipStream_t s);
 // Batched decode: k_plan writes the item prefix (n_desc + 1 entries) and
 // zeroes the item counter after it, from which the workgroups take their
 // items; d_item_prefix has room for n_desc + 2 entries.
 hipError_t launch_decode_batch(const DecClass& k, const DecDesc* d_descs, int n_desc, uint64_t* d_item_prefix,
-                               int* d_status, int grid, hipStream_t s);
+                               int* status, int grid, hipStream_t s);
 // Batched decode whose item prefix (plan_items per descriptor) was computed
 // on the host and copied beside the descriptors, followed by the item
 // counter, zero at launch (n_desc + 2 entries).
 hipError_t launch_decode_planned(const DecClass& k, const DecDesc* d_descs, int n_desc, uint64_t* d_item_prefix,
-                                 int* d_status, int grid, hipStream_t s);
-// Write the status to *host (pinned host memory) and clear it if asked to.
-hipError_t launch_take_status(int* d_status, int* host, bool clear, hipStream_t s);
+                                 int* status, int grid, hipStream_t s);
 // Copy a 64-byte header (16-byte aligned) to pinned host memory.
 hipError_t launch_fetch_header(const void* src, void* host, hipStream_t s);
 hipError_t launch_gather_headers(const uint8_t* arena, const uint64_t* d_offs, int n, void* d_out, hipStream_t s);
@@ -299,17 +297,16 @@ __host__ __device__ inline int dec_class_index(const DecClass& k)
     return ((bi * 3 + gi) * 2 + (k.delta ? 1 : 0)) * 2 + (k.zg ? 1 : 0);
 }
 
-// Compress n_desc tensors (descriptors and chunk prefix in device memory)
+// Compress n_desc tensors (descriptors and chunk prefix in device memory, or,
+// with `single`, one tensor whose descriptor is that and whose places there
+// the launches fill)
 // into `arena`: analyze -> place and arena layout (dst of every descriptor,
 // headers, arena_off[n_desc+1], written to host_off too unless null: pinned
 // host memory) -> pack (maps and payloads).
-hipError_t launch_encode(EncDesc* d_descs, int n_desc, const uint32_t* d_chunk_prefix, uint32_t total_chunks,
-                         const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, uint8_t* lens,
+hipError_t launch_encode(const EncDesc* single, EncDesc* d_descs, int n_desc, uint32_t* d_chunk_prefix,
+                         uint32_t total_chunks, const EncParams& p, uint8_t* arena, uint64_t cap, EncEntry* entries, uint8_t* lens,
                          uint32_t* nwords, uint64_t* offsets, uint64_t* totals, uint64_t* arena_off, uint64_t* host_off,
                          hipStream_t s);
-
-hipError_t launch_fill_desc(const EncDesc& one, uint32_t total_chunks, EncDesc* d_desc, uint32_t* d_prefix,
-                            hipStream_t s);
 
 // Offsets of the encoder's device scratch for ne = chunks * B entries of n
 // tensors (every array 256-byte aligned); `need` is the total.
@@ -345,8 +342,7 @@ inline EncScratch enc_scratch_layout(size_t chunks, size_t B, size_t n, size_t s
 struct zipnn_ctx_s {
     int device = 0;
     int dec_grid[zipnn::kDecClasses] = {};   // persistent decode grid of each kernel class
-    int* d_status = nullptr;      // sticky device-side status
-    int* h_status = nullptr;      // pinned
+    int* status = nullptr;        // sticky device-side status (pinned host memory: kernels write it, the host reads it)
     uint64_t* h_total = nullptr;  // pinned, encode sizes
     size_t h_total_cap = 0;
     void* d_scratch = nullptr;    // encode scratch (grown on demand)
