@@ -159,3 +159,41 @@ def test_streams_held_in_registers(codec, dt, chunk, S_div):
         o = int(got[0, 0])
         size = ref.size - rb
         assert np.array_equal(c[pb + o:pb + o + size].cpu().numpy(), ref[rb:])
+
+
+@pytest.mark.parametrize("skip", [0, 3])
+@pytest.mark.parametrize("n", [0, 1, 5000])
+def test_single_tensor_descriptor(codec, n, skip):
+    """A single tensor's descriptor comes with the analysis' launch (an empty
+    one's, which is not analysed, by a launch of its own); it leaves nothing
+    of the descriptors of a larger batch before it, nor the other way."""
+    p = Z.zipnn_default_params(Z.ZIPNN_BF16)
+    p.chunk_bytes, p.substream_syms, p.probe_skip = 1024, 16, skip
+    rng = np.random.default_rng(7 + n)
+    raws = [_words(rng, m, 2) for m in (3000, n, 700)]
+    xs = [torch.from_numpy(r).view(torch.bfloat16).cuda() for r in raws]
+    for _ in range(2):
+        arena, offs = codec.compress_batch(xs, p)
+        for i, r in enumerate(raws):
+            ref = oracle.compress(r, Z.ZIPNN_BF16, chunk_bytes=p.chunk_bytes, S=p.substream_syms, g=p.group,
+                                  L=p.max_code_len, policy=list(p.policy), skip=skip, exp=False)
+            assert np.array_equal(arena[offs[i]:offs[i] + ref.size].cpu().numpy(), ref)
+            assert np.array_equal(codec.compress(xs[i], p).cpu().numpy(), ref)
+
+
+def test_status_keeps_the_first_error(codec):
+    """An error stays until it is cleared, whatever is decoded after it."""
+    p = Z.zipnn_default_params(Z.ZIPNN_BF16)
+    x = torch.from_numpy(_words(np.random.default_rng(3), 4096, 2)).view(torch.bfloat16).cuda()
+    c = codec.compress(x, p)
+    out = torch.empty_like(x)
+    head = c[:64].cpu().numpy().tobytes()
+    bad = c.clone()
+    bad[64:] = 0xFF   # map entries of no known mode
+    codec.decompress(bad, out, header=head, check=False)
+    codec.decompress(c, out, header=head, check=False)
+    assert codec.status(clear=False) == Z.ZIPNN_E_CORRUPT
+    assert codec.status(clear=True) == Z.ZIPNN_E_CORRUPT
+    assert codec.status(clear=True) == Z.ZIPNN_OK
+    codec.decompress(c, out)
+    assert torch.equal(out.view(torch.uint8), x.view(torch.uint8))
