@@ -319,8 +319,11 @@ __device__ inline void huf_take(uint32_t* r, WordCursor& c, bool part, uint32_t 
     c.ptr += uint32_t(__popcll(m));
 }
 
-// Called at least every Ring<B>::CHECK rounds: a round takes at most 64
-// words, so between checks the reads stay inside the ring's RW words.
+// A round takes at most 64 words.  The general path calls this every
+// Ring<B>::CHECK rounds and at a step's end, so that at most RW/2 words are
+// taken between two calls: with ptr - rb <= RW/2 where it starts, its reads
+// stay inside the ring's RW words.  The fast loop calls it at its refill
+// points and huf_dry after every other round.
 template <int B>
 __device__ inline void huf_refill(uint32_t* r, WordCursor& c, uint32_t lane)
 {
@@ -819,7 +822,15 @@ __device__ __attribute__((always_inline)) void decode_lane_group(const uint8_t* 
         }
         if (!done) fast(integral_constant<I, -1>{}, integral_constant<I, -1>{});
     }
-    // general path: the remaining groups, with per-lane conditions
+    // general path: the remaining groups, with per-lane conditions.  A ZG step
+    // without a marked group passes a refill point of the fast loop by, so up
+    // to RW - 64 words of the ring may be used up here: one more makes it at
+    // most RW/2, as the general path needs.
+    if (n_fast < ng_max) {
+#pragma unroll
+        for (int k = 0; k < B; k++)
+            if (mode[k] == kModeHuf || (ZGK && mode[k] == kModeZg)) huf_refill<B>(slot[k], cur[k], lane);
+    }
     for (uint32_t j0 = n_fast; j0 < ng_max; j0 += kDepth) {
 #pragma unroll
         for (int u = 0; u < kDepth; u++) {
