@@ -825,11 +825,11 @@ __device__ __attribute__((always_inline)) void decode_lane_group(const uint8_t* 
     // general path: the remaining groups, with per-lane conditions.  A ZG step
     // without a marked group passes a refill point of the fast loop by, so up
     // to RW - 64 words of the ring may be used up here: one more makes it at
-    // most RW/2, as the general path needs.
-    if (n_fast < ng_max) {
+    // most RW/2, as the general path needs.  (Huffman streams pass none by.)
+    if (ZGK && n_fast < ng_max) {
 #pragma unroll
         for (int k = 0; k < B; k++)
-            if (mode[k] == kModeHuf || (ZGK && mode[k] == kModeZg)) huf_refill<B>(slot[k], cur[k], lane);
+            if (mode[k] == kModeZg) huf_refill<B>(slot[k], cur[k], lane);
     }
     for (uint32_t j0 = n_fast; j0 < ng_max; j0 += kDepth) {
 #pragma unroll
