@@ -215,8 +215,13 @@ __device__ inline void buf_store(__amdgpu_buffer_rsrc_t r, uint32_t off, const u
     else if constexpr (NBYTES == 8) __builtin_amdgcn_raw_buffer_store_b64(u32x2{w[0], w[1]}, r, off, 0, 2);
     else if constexpr (NBYTES == 16) __builtin_amdgcn_raw_buffer_store_b128(u32x4{w[0], w[1], w[2], w[3]}, r, off, 0, 2);
     else {
+        // back to back, so that the halves of a lane's 32 bytes meet on their
+        // way to memory: left alone, the next step's first pair came between
+        // them, and 256 MiB of FP32 at g = 8 took 148 us, so 120 (a few MiB,
+        // where a lane's chain counts, 31.5 and 32.4)
         __builtin_amdgcn_raw_buffer_store_b128(u32x4{w[0], w[1], w[2], w[3]}, r, off, 0, 2);
         __builtin_amdgcn_raw_buffer_store_b128(u32x4{w[4], w[5], w[6], w[7]}, r, off + 16, 0, 2);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -824,8 +829,8 @@ __device__ __attribute__((always_inline)) void decode_lane_group(const uint8_t* 
     }
     // general path: the remaining groups, with per-lane conditions.  A ZG step
     // without a marked group passes a refill point of the fast loop by, so up
-    // to RW - 64 words of the ring may be used up here: one more makes it at
-    // most RW/2, as the general path needs.  (Huffman streams pass none by.)
+    // to RW - 64 words of the ring may be used up here; a refill leaves at most
+    // RW/2, as the general path needs.  (Huffman streams pass none by.)
     if (ZGK && n_fast < ng_max) {
 #pragma unroll
         for (int k = 0; k < B; k++)
