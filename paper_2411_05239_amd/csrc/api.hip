@@ -159,13 +159,16 @@ int zipnn_ctx_create(int hip_device, zipnn_ctx* out)
     if (!ctx) return ZIPNN_E_NOMEM;
     ctx->device = hip_device;
     DeviceGuard g(hip_device);
-    if (host_malloc((void**)&ctx->status, sizeof(int)) != hipSuccess ||
+    if (dev_malloc((void**)&ctx->status, sizeof(StatusWord)) != hipSuccess ||
+        host_malloc((void**)&ctx->h_status, sizeof(int)) != hipSuccess ||
         grow_pinned(ctx, 64) != ZIPNN_OK) {
         zipnn_ctx_destroy(ctx);
         return ZIPNN_E_NOMEM;
     }
-    __atomic_store_n(ctx->status, 0, __ATOMIC_SEQ_CST);
-    if (hipDeviceSynchronize() != hipSuccess) {
+    __atomic_store_n(ctx->h_status, 0, __ATOMIC_SEQ_CST);
+    const StatusWord clear = {0, 0, ctx->h_status};
+    if (hipMemcpy(ctx->status, &clear, sizeof(clear), hipMemcpyHostToDevice) != hipSuccess ||
+        hipDeviceSynchronize() != hipSuccess) {
         zipnn_ctx_destroy(ctx);
         return ZIPNN_E_HIP;
     }
@@ -189,7 +192,8 @@ void zipnn_ctx_destroy(zipnn_ctx ctx)
     {
         DeviceGuard g(ctx->device);
         (void)hipDeviceSynchronize();
-        if (ctx->status) (void)hipHostFree(ctx->status);
+        if (ctx->status) (void)hipFree(ctx->status);
+        if (ctx->h_status) (void)hipHostFree(ctx->h_status);
         if (ctx->h_total) (void)hipHostFree(ctx->h_total);
         if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
     }
@@ -202,8 +206,16 @@ int zipnn_ctx_status(zipnn_ctx ctx, void* stream, int clear)
     DeviceGuard g(ctx->device);
     hipStream_t s = (hipStream_t)stream;
     if (hipStreamSynchronize(s) != hipSuccess) return ZIPNN_E_HIP;
-    return clear ? __atomic_exchange_n(ctx->status, 0, __ATOMIC_SEQ_CST)
-                 : __atomic_load_n(ctx->status, __ATOMIC_SEQ_CST);
+    if (!clear) return __atomic_load_n(ctx->h_status, __ATOMIC_SEQ_CST);
+    // the copy before the word: an error of another stream in between counts
+    // as one before the clear, and none recorded after it is lost
+    const int code = __atomic_exchange_n(ctx->h_status, 0, __ATOMIC_SEQ_CST);
+    if (code == ZIPNN_OK) return code;
+    if (launch_clear_status(ctx->status, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
+        __atomic_store_n(ctx->h_status, code, __ATOMIC_SEQ_CST);   // still recorded
+        return ZIPNN_E_HIP;
+    }
+    return code;
 }
 
 void zipnn_default_params(int dtype, zipnn_params* out)

@@ -63,14 +63,31 @@ struct TensorState {
     ItemPlan p;
 };
 
-// The first error found stays.  The word may be host memory (a context's
-// status, which the host reads once the stream is done): stores only, as
-// read-modify-write over the bus may not be supported.  Reading it by a
-// kernel of its own made an 8 KiB tensor's decode 72.8 us, so it is 69.7.
-__device__ inline void set_status(int* st, int code)
+// Values the same in every lane of the wave, made scalar.
+__device__ inline uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline uint64_t uni64(uint64_t v)
 {
-    if (__hip_atomic_load(st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == 0)
-        __hip_atomic_store(st, code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return uint64_t(uni(uint32_t(v))) | (uint64_t(uni(uint32_t(v >> 32))) << 32);
+}
+template <class T>
+__device__ inline T* uniptr(T* p)
+{
+    return reinterpret_cast<T*>(uni64(reinterpret_cast<uint64_t>(p)));
+}
+
+// The first error recorded stays; one that comes at the same time loses the
+// exchange.  (The host reads a context's copy: copied from the device word by
+// each status call, an 8 KiB tensor's decode took 72.8 us, so 69.7.)
+__device__ inline void set_status(StatusWord* st, int code)
+{
+    using G = StatusWord __attribute__((address_space(1)));
+    using H = int __attribute__((address_space(1)));
+    G* g = (G*)uniptr(st);
+    int seen = 0;
+    if (__hip_atomic_compare_exchange_strong(&g->code, &seen, code, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT) &&
+        g->host)
+        __hip_atomic_store((H*)uniptr(g->host), code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __device__ inline uint32_t wave_incl_scan(uint32_t v)
@@ -162,17 +179,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // set to kOff, far past any valid range.
 constexpr uint32_t kOff = 0x80000000u;
 
-// Values the same in every lane of the wave, made scalar.
-__device__ inline uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ inline uint64_t uni64(uint64_t v)
-{
-    return uint64_t(uni(uint32_t(v))) | (uint64_t(uni(uint32_t(v >> 32))) << 32);
-}
-template <class T>
-__device__ inline T* uniptr(T* p)
-{
-    return reinterpret_cast<T*>(uni64(reinterpret_cast<uint64_t>(p)));
-}
 __device__ inline __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
@@ -508,7 +514,7 @@ template <int B, int G, bool DELTA, bool ZGK>
 __device__ __attribute__((always_inline)) void decode_lane_group(const uint8_t* __restrict__ src, const ItemState& st, uint32_t* wring,
                                   const uint16_t (*lut)[kLutSize], const uint32_t (*wprefix)[65], uint32_t L,
                                   uint32_t j, uint32_t W, uint32_t m, uint8_t* __restrict__ out,
-                                  const uint8_t* __restrict__ base, int* status, bool xf)
+                                  const uint8_t* __restrict__ base, StatusWord* status, bool xf)
 {
     constexpr int NB = B * G;
     constexpr int NW = NB >= 4 ? NB / 4 : 1;
@@ -652,6 +658,9 @@ __device__ __attribute__((always_inline)) void decode_lane_group(const uint8_t* 
 #pragma unroll
                 for (int x = 0; x < NW; x++) asm volatile("" : "+v"(bring[u][x]));
         }
+        // where the loop lies within 32 bytes shows: a BF16 chunk's chain took
+        // 47.7 to 48.8 us for 8 MiB as code before it came and went
+        asm volatile(".p2align 5");
         for (uint32_t j0 = 0; j0 < n_fast; j0 += kDepth) {
 #pragma unroll
             for (int u = 0; u < kDepth; u++) {
@@ -933,7 +942,7 @@ __device__ __attribute__((always_inline)) void decode_lane_group(const uint8_t* 
 }
 
 // Parse one tensor's header on the device and size its work.
-__device__ bool load_tensor(const DecDesc& d, int di, TensorState& ts, int* status, bool report)
+__device__ bool load_tensor(const DecDesc& d, int di, TensorState& ts, StatusWord* status, bool report)
 {
     const uint4* hp = (const uint4*)d.src;
     uint32_t w[16];
@@ -972,7 +981,7 @@ __device__ bool load_tensor(const DecDesc& d, int di, TensorState& ts, int* stat
 template <int B, int G, bool DELTA, bool ZGK>
 __device__ __attribute__((always_inline)) void decode_item(const DecDesc& d, const TensorState& ts, uint32_t c, uint32_t slice, uint32_t* wring,
                             uint16_t (*lut)[kLutSize], uint32_t (*wprefix)[65], LutTmp& T, ItemState& st,
-                            int* status)
+                            StatusWord* status)
 {
     const Header& h = ts.h;
     const int t = threadIdx.x;
@@ -1085,7 +1094,7 @@ __device__ __attribute__((always_inline)) void decode_item(const DecDesc& d, con
 // slower.)
 template <int B, int G, bool DELTA, bool ZGK>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(B * G >= (DELTA ? 16 : 32) ? 2 : 4, 8))) void k_decode(DecDesc one, const DecDesc* __restrict__ descs, int n_desc,
-                                                   const uint64_t* __restrict__ item_prefix, int* status,
+                                                   const uint64_t* __restrict__ item_prefix, StatusWord* status,
                                                    unsigned long long* __restrict__ work)
 {
     __shared__ uint16_t lut[B][kLutSize];
@@ -1173,7 +1182,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(B * G >=
 // tensor whose header is invalid or does not match (B, G, DELTA) gets no
 // items and is reported.
 __global__ __launch_bounds__(kBlock) void k_plan(const DecDesc* __restrict__ descs, int n_desc, DecClass k,
-                                                 uint64_t* __restrict__ prefix, int* status,
+                                                 uint64_t* __restrict__ prefix, StatusWord* status,
                                                  unsigned long long* __restrict__ work)
 {
     __shared__ TensorState tsv[kBlock];
@@ -1205,6 +1214,8 @@ __global__ __launch_bounds__(kBlock) void k_plan(const DecDesc* __restrict__ des
     }
 }
 
+__global__ void k_clear_status(StatusWord* st) { st->code = 0; }
+
 // A header goes to pinned host memory from a kernel: a copy engine's or a
 // copy kernel's turn-around is several microseconds longer.
 __global__ void k_fetch_header(const uint4* __restrict__ src, uint4* host) { host[threadIdx.x] = src[threadIdx.x]; }
@@ -1219,7 +1230,7 @@ __global__ void k_gather_headers(const uint8_t* __restrict__ arena, const uint64
 }
 
 template <int B, int G, bool D, bool Z>
-hipError_t launch_k(const DecDesc& one, const DecDesc* descs, int n, const uint64_t* prefix, int* st, int grid,
+hipError_t launch_k(const DecDesc& one, const DecDesc* descs, int n, const uint64_t* prefix, StatusWord* st, int grid,
                     hipStream_t s, unsigned long long* work)
 {
     k_decode<B, G, D, Z><<<grid, kBlock, 0, s>>>(one, descs, n, prefix, st, work);
@@ -1227,7 +1238,7 @@ hipError_t launch_k(const DecDesc& one, const DecDesc* descs, int n, const uint6
 }
 
 hipError_t dispatch(const DecClass& k, const DecDesc& one, const DecDesc* descs, int n, const uint64_t* prefix,
-                    int* st, int grid, hipStream_t s, unsigned long long* work = nullptr)
+                    StatusWord* st, int grid, hipStream_t s, unsigned long long* work = nullptr)
 {
 #define ZIPNN_K(BB, GG)                                                                                       \
     if (k.B == BB && k.G == GG) {                                                                            \
@@ -1276,13 +1287,13 @@ int decode_grid_size(int device, const DecClass& k)
     return prop.multiProcessorCount * per_cu;
 }
 
-hipError_t launch_decode_one(const Header& h, const DecDesc& one, int* status, int grid, hipStream_t s)
+hipError_t launch_decode_one(const Header& h, const DecDesc& one, StatusWord* status, int grid, hipStream_t s)
 {
     return dispatch(dec_class(h), one, nullptr, 1, nullptr, status, grid, s);
 }
 
 hipError_t launch_decode_batch(const DecClass& k, const DecDesc* d_descs, int n_desc, uint64_t* d_item_prefix,
-                               int* status, int grid, hipStream_t s)
+                               StatusWord* status, int grid, hipStream_t s)
 {
     // the shared item counter sits after the prefix's n_desc + 1 entries
     unsigned long long* work = reinterpret_cast<unsigned long long*>(d_item_prefix + n_desc + 1);
@@ -1294,7 +1305,7 @@ hipError_t launch_decode_batch(const DecClass& k, const DecDesc* d_descs, int n_
 }
 
 hipError_t launch_decode_planned(const DecClass& k, const DecDesc* d_descs, int n_desc, uint64_t* d_item_prefix,
-                                 int* status, int grid, hipStream_t s)
+                                 StatusWord* status, int grid, hipStream_t s)
 {
     DecDesc none = {};
     unsigned long long* work = reinterpret_cast<unsigned long long*>(d_item_prefix + n_desc + 1);
@@ -1304,6 +1315,12 @@ hipError_t launch_decode_planned(const DecClass& k, const DecDesc* d_descs, int 
 hipError_t launch_gather_headers(const uint8_t* arena, const uint64_t* d_offs, int n, void* d_out, hipStream_t s)
 {
     k_gather_headers<<<(4 * n + 255) / 256, 256, 0, s>>>(arena, d_offs, n, (uint4*)d_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear_status(StatusWord* status, hipStream_t s)
+{
+    k_clear_status<<<1, 1, 0, s>>>(status);
     return hipGetLastError();
 }
 

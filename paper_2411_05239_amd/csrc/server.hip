@@ -291,10 +291,10 @@ bool launch_iteration(zipnn_server s)
         at.push_back({dd, pp});
     }
     it.status_off = off;
-    const size_t total = off + it.members.size() * sizeof(int);
+    const size_t total = off + it.members.size() * sizeof(StatusWord);
     int rc = grow_iter(it, total) ? ZIPNN_OK : ZIPNN_E_NOMEM;
     if (rc == ZIPNN_OK) {
-        int* d_status = (int*)(it.d_buf + it.status_off);
+        StatusWord* d_status = (StatusWord*)(it.d_buf + it.status_off);
         size_t ci = 0;
         for (auto& kv : classes) {
             Class& c = kv.second;
@@ -304,7 +304,7 @@ bool launch_iteration(zipnn_server s)
             memset(it.h_buf + at[ci].second + c.prefix.size() * sizeof(uint64_t), 0, sizeof(uint64_t));
             ci++;
         }
-        memset(it.h_buf + it.status_off, 0, it.members.size() * sizeof(int));
+        memset(it.h_buf + it.status_off, 0, it.members.size() * sizeof(StatusWord));
         hipError_t e = hipMemcpyAsync(it.d_buf, it.h_buf, total, hipMemcpyHostToDevice, it.st[0]);
         const size_t used = std::min<size_t>(classes.size(), kIterStreams);
         if (e == hipSuccess && used > 1) e = hipEventRecord(it.fork, it.st[0]);
@@ -327,7 +327,7 @@ bool launch_iteration(zipnn_server s)
             if (e == hipSuccess) e = hipStreamWaitEvent(it.st[0], it.join[i], 0);
         }
         if (e == hipSuccess)
-            e = hipMemcpyAsync(it.h_buf + it.status_off, it.d_buf + it.status_off, it.members.size() * sizeof(int),
+            e = hipMemcpyAsync(it.h_buf + it.status_off, it.d_buf + it.status_off, it.members.size() * sizeof(StatusWord),
                                hipMemcpyDeviceToHost, it.st[0]);
         if (e == hipSuccess) e = hipEventRecord(it.ev, it.st[0]);
         if (e != hipSuccess) rc = ZIPNN_E_HIP;
@@ -366,10 +366,10 @@ int retire(zipnn_server s)
         const hipError_t q = hipEventQuery(it.ev);
         if (q == hipErrorNotReady) break;
         const double t = now_s();
-        const int* hs = (const int*)(it.h_buf + it.status_off);
+        const StatusWord* hs = (const StatusWord*)(it.h_buf + it.status_off);
         for (size_t i = 0; i < it.members.size(); i++) {
             Req& r = s->reqs[it.members[i]];
-            const int code = q == hipSuccess ? hs[i] : ZIPNN_E_HIP;
+            const int code = q == hipSuccess ? hs[i].code : ZIPNN_E_HIP;
             if (code != ZIPNN_OK && r.status == ZIPNN_OK) r.status = code;
             if (it.finishing[i]) finish(s, it.members[i], r, t);
         }
@@ -446,7 +446,7 @@ int zipnn_server_create(zipnn_ctx ctx, const zipnn_server_config* cfg, zipnn_ser
             ok = hipStreamCreateWithFlags(&it.st[j], hipStreamNonBlocking) == hipSuccess &&
                  hipEventCreateWithFlags(&it.join[j], hipEventDisableTiming) == hipSuccess;
         if (!ok) rc = ZIPNN_E_HIP;
-        else if (!grow_iter(s->it[i], size_t(s->cfg.max_inflight) * 96 + 4096)) rc = ZIPNN_E_NOMEM;
+        else if (!grow_iter(s->it[i], size_t(s->cfg.max_inflight) * 112 + 4096)) rc = ZIPNN_E_NOMEM;
     }
     if (prev >= 0) (void)hipSetDevice(prev);
     if (rc != ZIPNN_OK) {

@@ -146,6 +146,16 @@ __host__ __device__ inline int parse_header(const uint32_t* w, uint64_t src_len,
     return ZIPNN_OK;
 }
 
+// A sticky status in device memory: the first error recorded stays until it is
+// cleared.  `host` (a context's; else nullptr) is pinned host memory that gets
+// a copy of it, for a host that reads it once its stream is done: the copy is
+// a plain store, as read-modify-write over the bus may not be supported.
+struct StatusWord {
+    int code;
+    int pad;
+    int* host;
+};
+
 // One tensor of a (possibly batched) decode.
 struct DecDesc {
     const uint8_t* src;
@@ -155,7 +165,7 @@ struct DecDesc {
     uint64_t dst_cap;
     uint32_t c_begin;      // chunks [c_begin, min(c_end, n_chunks)) are decoded
     uint32_t c_end;
-    int* status;           // where corruption found in its chunks is reported (nullptr: the launch's)
+    StatusWord* status;    // where corruption found in its chunks is reported (nullptr: the launch's)
     uint32_t zg;           // the ZG flag its header had when the launch was prepared
     uint32_t pad;
 };
@@ -273,17 +283,18 @@ __host__ __device__ inline DecClass dec_class(const Header& h)
 {
     return DecClass{h.B, h.g, (h.flags & kFlagDelta) != 0, (h.flags & kFlagZg) != 0};
 }
-hipError_t launch_decode_one(const Header& h, const DecDesc& one, int* status, int grid, hipStream_t s);
+hipError_t launch_decode_one(const Header& h, const DecDesc& one, StatusWord* status, int grid, hipStream_t s);
 // Batched decode: k_plan writes the item prefix (n_desc + 1 entries) and
 // zeroes the item counter after it, from which the workgroups take their
 // items; d_item_prefix has room for n_desc + 2 entries.
 hipError_t launch_decode_batch(const DecClass& k, const DecDesc* d_descs, int n_desc, uint64_t* d_item_prefix,
-                               int* status, int grid, hipStream_t s);
+                               StatusWord* status, int grid, hipStream_t s);
 // Batched decode whose item prefix (plan_items per descriptor) was computed
 // on the host and copied beside the descriptors, followed by the item
 // counter, zero at launch (n_desc + 2 entries).
 hipError_t launch_decode_planned(const DecClass& k, const DecDesc* d_descs, int n_desc, uint64_t* d_item_prefix,
-                                 int* status, int grid, hipStream_t s);
+                                 StatusWord* status, int grid, hipStream_t s);
+hipError_t launch_clear_status(StatusWord* status, hipStream_t s);
 // Copy a 64-byte header (16-byte aligned) to pinned host memory.
 hipError_t launch_fetch_header(const void* src, void* host, hipStream_t s);
 hipError_t launch_gather_headers(const uint8_t* arena, const uint64_t* d_offs, int n, void* d_out, hipStream_t s);
@@ -342,7 +353,8 @@ inline EncScratch enc_scratch_layout(size_t chunks, size_t B, size_t n, size_t s
 struct zipnn_ctx_s {
     int device = 0;
     int dec_grid[zipnn::kDecClasses] = {};   // persistent decode grid of each kernel class
-    int* status = nullptr;        // sticky device-side status (pinned host memory: kernels write it, the host reads it)
+    zipnn::StatusWord* status = nullptr;     // sticky device-side status
+    int* h_status = nullptr;      // its copy in pinned host memory
     uint64_t* h_total = nullptr;  // pinned, encode sizes
     size_t h_total_cap = 0;
     void* d_scratch = nullptr;    // encode scratch (grown on demand)
