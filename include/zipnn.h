@@ -261,7 +261,8 @@ int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* tensor
 
 /* Replay the graph on `stream` and wait; offsets (host, n+1 entries) receive
  * the containers' offsets and, last, the arena bytes used (ZIPNN_E_NOSPACE if
- * that exceeds arena_cap: the arena then holds unspecified bytes). */
+ * that exceeds arena_cap: the arena then holds unspecified bytes).  Runs of
+ * one encoder from several threads take place one after another. */
 int zipnn_encoder_run(zipnn_encoder e, void* stream, uint64_t* offsets);
 
 /* Wait for the device, then release the encoder.  NULL is ignored. */

@@ -404,6 +404,7 @@ int zipnn_compress_batch(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* tensor
 
 struct zipnn_encoder_s {
     zipnn_ctx ctx = nullptr;
+    std::mutex mu;                // one run at a time: they share the scratch, its counters and the arena
     int n = 0;
     uint64_t cap = 0;
     void* d_mem = nullptr;        // scratch, descriptors and chunk prefix of this batch
@@ -497,6 +498,7 @@ int zipnn_encoder_create(zipnn_ctx ctx, int dtype, const zipnn_tensor_in* t, int
 int zipnn_encoder_run(zipnn_encoder e, void* stream, uint64_t* offsets)
 {
     if (!e || !offsets) return ZIPNN_E_INVAL;
+    std::lock_guard<std::mutex> lk(e->mu);
     DeviceGuard g(e->ctx->device);
     hipStream_t s = (hipStream_t)stream;
     if (hipGraphLaunch(e->exec, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return ZIPNN_E_HIP;
