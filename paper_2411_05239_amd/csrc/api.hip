@@ -633,7 +633,11 @@ int zipnn_batch_create(zipnn_ctx ctx, const void* arena, const uint64_t* offsets
         hipStreamSynchronize(s0) != hipSuccess)
         return ZIPNN_E_HIP;
     // group the tensors by kernel class (B, g, delta, zg)
-    std::map<std::tuple<uint32_t, uint32_t, bool, bool>, std::vector<DecDesc>> groups;
+    struct Group {
+        std::vector<DecDesc> descs;
+        uint64_t bytes = 0;   // of the tensors
+    };
+    std::map<std::tuple<uint32_t, uint32_t, bool, bool>, Group> groups;
     for (int i = 0; i < n; i++) {
         Header h;
         rc = parse_header((const uint32_t*)((const uint8_t*)ctx->h_total + 64 * size_t(i)), offsets[i + 1] - offsets[i],
@@ -655,7 +659,9 @@ int zipnn_batch_create(zipnn_ctx ctx, const void* arena, const uint64_t* offsets
         d.status = nullptr;
         d.zg = (h.flags & kFlagZg) ? 1 : 0;
         d.pad = 0;
-        groups[std::make_tuple(h.B, h.g, delta, d.zg != 0)].push_back(d);
+        Group& gr = groups[std::make_tuple(h.B, h.g, delta, d.zg != 0)];
+        gr.descs.push_back(d);
+        gr.bytes += h.n * h.B;
     }
     // A few plain containers beside many with ZG entries (the norm vectors of
     // a delta checkpoint) join their launch: alone they are a launch that
@@ -665,37 +671,36 @@ int zipnn_batch_create(zipnn_ctx ctx, const void* arena, const uint64_t* offsets
     for (auto it = groups.begin(); it != groups.end();) {
         const auto& k = it->first;
         auto zgs = groups.find(std::make_tuple(std::get<0>(k), std::get<1>(k), std::get<2>(k), true));
-        auto bytes = [](const std::vector<DecDesc>& v) {
-            uint64_t b = 0;
-            for (const auto& d : v) b += d.dst_cap;
-            return b;
-        };
-        if (std::get<3>(k) || zgs == groups.end() || bytes(it->second) > bytes(zgs->second) / 8) {
+        if (std::get<3>(k) || zgs == groups.end() || it->second.bytes > zgs->second.bytes / 8) {
             ++it;
             continue;
         }
-        zgs->second.insert(zgs->second.begin(), it->second.begin(), it->second.end());
+        zgs->second.descs.insert(zgs->second.descs.begin(), it->second.descs.begin(), it->second.descs.end());
         it = groups.erase(it);
     }
     zipnn_batch b = new (std::nothrow) zipnn_batch_s;
     if (!b) return ZIPNN_E_NOMEM;
     b->ctx = ctx;
     size_t bytes = 0;
-    for (auto& kv : groups) bytes += align256(kv.second.size() * sizeof(DecDesc)) + align256((kv.second.size() + 2) * 8);
+    for (auto& kv : groups) {
+        const size_t nd = kv.second.descs.size();
+        bytes += align256(nd * sizeof(DecDesc)) + align256((nd + 2) * 8);
+    }
     if (bytes && dev_malloc((void**)&b->d_mem, bytes) != hipSuccess) {
         delete b;
         return ZIPNN_E_NOMEM;
     }
     size_t off = 0;
     for (auto& kv : groups) {
+        const std::vector<DecDesc>& ds = kv.second.descs;
         zipnn_batch_s::Class c;
         c.k = DecClass{std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), std::get<3>(kv.first)};
-        c.n = int(kv.second.size());
+        c.n = int(ds.size());
         c.d_descs = (DecDesc*)((uint8_t*)b->d_mem + off);
-        off += align256(kv.second.size() * sizeof(DecDesc));
+        off += align256(ds.size() * sizeof(DecDesc));
         c.d_prefix = (uint64_t*)((uint8_t*)b->d_mem + off);
-        off += align256((kv.second.size() + 2) * 8);
-        if (hipMemcpy(c.d_descs, kv.second.data(), kv.second.size() * sizeof(DecDesc), hipMemcpyHostToDevice) !=
+        off += align256((ds.size() + 2) * 8);
+        if (hipMemcpy(c.d_descs, ds.data(), ds.size() * sizeof(DecDesc), hipMemcpyHostToDevice) !=
             hipSuccess) {
             zipnn_batch_destroy(b);
             return ZIPNN_E_HIP;
