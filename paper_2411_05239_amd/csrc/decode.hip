@@ -431,46 +431,6 @@ __device__ inline uint32_t sym_pair(uint32_t e0, uint32_t e1, uint32_t pos)
     return __builtin_amdgcn_perm(e1, e0, pos == 0 ? 0x0c0c0501u : 0x05010c0cu);
 }
 
-template <int G>
-__device__ inline void raw_load(const uint8_t* p, uint32_t* o)
-{
-    if constexpr (G == 2) o[0] = *(const uint16_t*)p;
-    else if constexpr (G == 4) o[0] = __builtin_nontemporal_load((const uint32_t*)p);
-    else {
-        u32x2 v = __builtin_nontemporal_load((const u32x2*)p);
-        o[0] = v.x;
-        o[1] = v.y;
-    }
-}
-
-template <int NB>
-__device__ inline void store_words(uint8_t* d, const uint32_t* w)
-{
-    if constexpr (NB == 2) *(uint16_t*)d = uint16_t(w[0]);
-    else if constexpr (NB == 4) __builtin_nontemporal_store(w[0], (uint32_t*)d);
-    else if constexpr (NB == 8) __builtin_nontemporal_store(u32x2{w[0], w[1]}, (u32x2*)d);
-    else if constexpr (NB == 16) __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, (u32x4*)d);
-    else {
-        __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]}, (u32x4*)d);
-        __builtin_nontemporal_store(u32x4{w[4], w[5], w[6], w[7]}, (u32x4*)(d + 16));
-    }
-}
-
-template <int NB>
-__device__ inline void load_words(const uint8_t* b, uint32_t* w)
-{
-    if constexpr (NB == 2) w[0] = *(const uint16_t*)b;
-    else if constexpr (NB == 4) w[0] = __builtin_nontemporal_load((const uint32_t*)b);
-    else {
-#pragma unroll
-        for (int i = 0; i < NB / 8; i++) {
-            u32x2 v = __builtin_nontemporal_load((const u32x2*)(b + 8 * i));
-            w[2 * i] = v.x;
-            w[2 * i + 1] = v.y;
-        }
-    }
-}
-
 // Interleave the B byte groups of G elements back into words (the inverse of
 // byte grouping): pk[k][x] holds symbols 4x..4x+3 of stream k; element i's
 // little-endian word is (s_{B-1}[i], ..., s_1[i], s_0[i]).  v_perm_b32 picks
