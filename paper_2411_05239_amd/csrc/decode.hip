@@ -242,7 +242,7 @@ template <int B>
 struct Ring {
     static constexpr int RW = B == 4 ? 256 : 512;   // words per ring
     static constexpr int PN = RW / 128;             // words per lane of a pending half block
-    static constexpr int CHECK = RW / 128;          // rounds between refill checks, at most
+    static constexpr int CHECK = RW / 128;          // rounds between refill checks of the general path, at most
 };
 
 // Steps between the refill points of the fast loop: about 16 symbols a lane
